@@ -10,6 +10,10 @@ namespace navsim {
 constexpr int kReachMaxWords = 2048;  // C-free bitset words per map (e.g. 256 x 256 cells)
 constexpr int kReachMaxBins = 16;
 constexpr int kReachThreads = 256;
+// register search: packed words of one colour that a wavefront holds, and the
+// words per row beyond which a map has no packed bitset
+constexpr int kPackedWords = 16 * 64;
+constexpr int kPackedMaxRow = 16;
 // propose_kernel: one candidate check per wavefront, 8 at a time for launches
 // of at most this many requests, else 4
 constexpr int kProposeWideMax = 2048;
@@ -18,24 +22,34 @@ constexpr int kProposeWideMax = 2048;
 constexpr int kProposeHeadRounds = 1;
 constexpr int kPoolCells = 1024;      // 32 x 32 pooled occupancy
 
-// One map's C-free bitset: row j, column i is bit i & 31 of word
-// j * wpr + (i >> 5); bits at i >= W are 0.
+// One map's C-free cells, twice: a plain bitset (row j, column i is bit i & 31
+// of word j * wpr + (i >> 5); bits at i >= W are 0), and, for the searches in
+// registers, the cells of each checkerboard colour c = (i + j) & 1 apart (cell
+// (i, j) is bit (i >> 1) & 31 of word c * pwords + j * pk + (i >> 6)).
 struct ReachDesc {
     int32_t W, H, wpr, words;
     int64_t bit_off;   // into the bitset array
     int64_t free_off;  // into the C-free cell list
     int32_t free_cnt;
     float s;           // cell size, metres
+    int64_t pk_off;    // into the array of packed bitsets
+    int32_t pk;        // packed words per row and colour, a power of two (0: none, W > 1024)
+    int32_t pwords;    // H * pk
+    int32_t pair_ok, label_ok;  // the register search holds any pair's (any start's) window
 };
 
 struct ReachParams {
     const ReachDesc *maps;
     const uint32_t *bits;
+    const uint32_t *packed;
     const int32_t *free_cells;
     const int8_t *hop_bin;   // bin of each hop count 0..max_hops, -1 outside
     const int32_t *bin_hi;   // largest hop count of each bin
     int32_t max_hops, nbins, num_maps;
     double gmd;              // least start-goal distance between cell centres
+    double gmd2;             // smallest double whose square root is at least gmd
+    int32_t max_pwords;      // largest pwords among the maps
+    int32_t all_pair, all_label;  // pair_ok (label_ok) on every map
     uint32_t key0, key1;     // Philox key
 };
 

@@ -1,9 +1,10 @@
 // Reachability kernels of the learned reset proposal: breadth-first search on
-// C-free bitsets staged in LDS, one workgroup per request.  Each search level
-// dilates the frontier by one 4-neighbour move with word shifts (left/right
-// within a row, carries across words) and row offsets (up/down), masks it with
-// the C-free bits and the visited set, and stops as soon as the target bit
-// appears, the frontier empties or the depth limit is reached.
+// C-free bitsets, by one wavefront in its registers, or (labelling, and maps
+// whose searches do not fit a wavefront's registers) by a workgroup in LDS.
+// Each search level dilates the frontier by one 4-neighbour move with word
+// shifts (left/right within a row, carries across words) and row offsets
+// (up/down), masks it with the C-free cells not yet reached, and stops as soon
+// as the target bit appears, the frontier empties or the depth limit is reached.
 #include <limits.h>
 #include <math.h>
 
@@ -270,103 +271,203 @@ __global__ __launch_bounds__(kReachThreads) void label_kernel(ReachParams rp, co
 }
 
 // ---------------------------------------------------------------------------
-// Searches in one wavefront's registers, for maps whose rows take WPR words
-// with WPR dividing 32 (W <= 32, 64, ..., 1024 cells): lane l holds words
-// [32 l, 32 l + 32) of the row-major C-free bitset, i.e. 32 / WPR whole rows,
-// so a row's left and right carries stay in the lane and only the rows above
-// the lane's first and below its last come from lanes l - 1 and l + 1
-// (cross-lane moves).  No LDS and no workgroup barrier per level: the four
-// wavefronts of a workgroup check four candidates at once.
+// Searches in one wavefront's registers, on the packed bitsets.  The 4-neighbour
+// grid is bipartite: a level's frontier lies on one checkerboard colour and the
+// next one on the other, so the two colours are kept apart and a level touches
+// only half of the map's bits.  Within a packed row, cell p of the colour that
+// receives the level neighbours cells p of the rows above and below and cells p
+// and p - 1 (or p and p + 1, by the row's parity) of its own row in the other
+// colour.  The lanes of the wavefront hold NW words of each colour: NW / P whole
+// rows of P words, of the window of the map that a path of at most max_hops
+// moves can touch (see search_hops), so a small bin's search runs in 2 x 4
+// words a lane where the whole of a 256 x 256 map takes 2 x 16.  A row's carries
+// stay in the lane and only the rows next to the lane's first and last come from
+// the lanes beside it (cross-lane moves).  No LDS and no workgroup barrier per
+// level.
+//
+// The searches are bound by VALU issue: about 4.5 instructions per word and
+// level (a funnel shift, an or of three, two three-operand logic operations, and
+// the frontier's emptiness every other level), against 6.5 on twice the words
+// with both colours in one bitset.  8,192 requests on 64 maps of 256 x 256 cells:
+// 3,454 -> 1,072 us; 490 requests inside a step of 32,768 envs, head round 312 ->
+// 117 us and the tail rounds 217 -> 100 us (the whole step 935 -> 624 us).
 
-// Word j (uniform) of a lane's 32 registers, without dynamic register indexing.
-// One breadth-first level of wave_hops: the next frontier nx from fr; a cell
-// joins it iff a 4-neighbour is in fr and it is still in un (C-free, not
-// reached yet), and then leaves un.  Returns whether any lane's nx is
-// non-empty.  A word's horizontal neighbours come from two funnel shifts with
-// the adjacent words of its row.
-template <int WPR>
-__device__ __forceinline__ bool wave_level(const uint32_t fr[32], uint32_t nx[32], uint32_t un[32],
-                                           int lane) {
-    uint32_t up[WPR], dn[WPR];
+template <int N>
+using Words = uint32_t __attribute__((ext_vector_type(N)));
+typedef __attribute__((address_space(3))) const uint32_t LdsWord;
+typedef __attribute__((address_space(3))) const int LdsInt;
+
+// One level into the words of colour CB (rows counted from an even row): nx =
+// the cells of `un` (C-free, not reached) with a neighbour in the frontier f of
+// the other colour; they leave un.  Returns the OR of the lane's nx words.
+template <int P, int NW, int CB>
+__device__ __forceinline__ uint32_t packed_level(const Words<NW> &f, Words<NW> &nx, Words<NW> &un,
+                                                 int lane) {
+    constexpr int R = NW / P;  // rows per lane
+    static_assert(R == 1 || R % 2 == 0, "a lane's first row is even, or lanes alternate");
+    uint32_t up[P], dn[P];
 #pragma unroll
-    for (int k = 0; k < WPR; ++k) {
-        // rows above the lane's first: the last row of lane - 1; below its
-        // last: the first row of lane + 1; none past the ends.  DPP wavefront
-        // shifts by one lane (wave_shr:1, wave_shl:1), the lane past an end
-        // reading 0: one full-rate move each, no LDS permute and no select
-        up[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)fr[32 - WPR + k], 0x138, 0xf, 0xf,
-                                                      true);
-        dn[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)fr[k], 0x130, 0xf, 0xf, true);
+    for (int k = 0; k < P; ++k) {
+        // DPP wavefront shifts by one lane (wave_shr:1, wave_shl:1), 0 past the ends
+        up[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)f[NW - P + k], 0x138, 0xf, 0xf, true);
+        dn[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)f[k], 0x130, 0xf, 0xf, true);
     }
-    (void)lane;
     uint32_t any = 0u;
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
-        const uint32_t prev = j % WPR != 0 ? fr[j % WPR != 0 ? j - 1 : 0] : 0u;
-        const uint32_t next = j % WPR != WPR - 1 ? fr[j % WPR != WPR - 1 ? j + 1 : 0] : 0u;
-        const uint32_t h = __builtin_amdgcn_alignbit(fr[j], prev, 31u) |
-                           __builtin_amdgcn_alignbit(next, fr[j], 1u);
-        const uint32_t v = (j >= WPR ? fr[j >= WPR ? j - WPR : 0] : up[j < WPR ? j : 0]) |
-                           (j + WPR < 32 ? fr[j + WPR < 32 ? j + WPR : 0]
-                                         : dn[j + WPR >= 32 ? j + WPR - 32 : 0]);
-        nx[j] = (h | v) & un[j];
-        un[j] ^= nx[j];
+    for (int j = 0; j < NW; ++j) {
+        const int k = j % P;
+        const uint32_t prev = k > 0 ? f[k > 0 ? j - 1 : 0] : 0u;
+        const uint32_t next = k < P - 1 ? f[k < P - 1 ? j + 1 : 0] : 0u;
+        const uint32_t lower = __builtin_amdgcn_alignbit(f[j], prev, 31u);
+        const uint32_t upper = __builtin_amdgcn_alignbit(next, f[j], 1u);
+        const bool odd = R == 1 ? ((lane + CB) & 1) != 0 : ((j / P + CB) & 1) != 0;
+        const uint32_t t = f[j] | (odd ? upper : lower) | (j >= P ? f[j >= P ? j - P : 0] : up[k]) |
+                           (j + P < NW ? f[j + P < NW ? j + P : 0] : dn[k]);
+        nx[j] = t & un[j];
+        un[j] &= ~t;
         any |= nx[j];
     }
-    return __ballot(any != 0u) != 0ull;
+    return any;
 }
 
-// Hop count from a to b (both C-free, a != b) within max_hops moves, else -1
-// (uniform across the wavefront); the same levels as hops_to.  Per lane: 32
-// words of rows of WPR words; two frontier buffers used in turn (two levels
-// per loop pass, so no frontier is copied).
-template <int WPR>
-__device__ int wave_hops(const uint32_t *fb, const ReachDesc &d, int a, int b, int max_hops,
-                         int lane, int c, const int *s_won, const int *g_won) {
-    const int wa = (a / d.W) * WPR + ((a % d.W) >> 5);
-    const int wb = (b / d.W) * WPR + ((b % d.W) >> 5);
-    const int la = wa >> 5, ja = wa & 31, lb = wb >> 5;
-    // b is reached when its bit leaves un; its register index is the same on
-    // every lane (one relative register move)
-    const int jb = __builtin_amdgcn_readfirstlane(wb & 31);
-    const uint32_t ba = 1u << ((a % d.W) & 31), bb = (b % d.W) & 31;
-    // the C-free words come from the staged map in LDS (lane l holds words
-    // 32 l .. 32 l + 31), read once per search rather than kept in registers
-    uint32_t f0[32], f1[32], un[32];
-    const int base = lane * 32;
+// A window of a map's packed bitsets (H rows of pk words per colour, pwords
+// words in all): rows from the even row j0, word columns from cw0.
+struct Window {
+    int j0, cw0, H, pk, pwords;
+};
+
+// The C-free words of a window, both colours (words outside the map are 0).
+template <int P, int NW>
+__device__ __forceinline__ void load_window(LdsWord *fb, const Window &w, Words<NW> &un0,
+                                            Words<NW> &un1, int lane) {
+    const int r0 = w.j0 + lane * (NW / P);
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
-        const uint32_t seed = (lane == la && j == ja) ? ba : 0u;
-        f0[j] = seed;
-        un[j] = (base + j < d.words ? fb[base + j] : 0u) & ~seed;
+    for (int j = 0; j < NW; ++j) {
+        const int row = r0 + j / P, col = w.cw0 + j % P;
+        const bool in = row < w.H && col < w.pk;
+        const int q = in ? row * w.pk + col : 0;
+        const uint32_t v0 = fb[q], v1 = fb[q + w.pwords];
+        un0[j] = in ? v0 : 0u;
+        un1[j] = in ? v1 : 0u;
     }
-    for (int level = 1; level <= max_hops; level += 2) {
+}
+
+// Hop count from cell (ia, ja) to (ib, jb) (both C-free, not the same) within
+// max_hops moves, else -1 (uniform across the wavefront).
+template <int P, int NW>
+__device__ __forceinline__ int window_hops(LdsWord *fb, const Window &w, int ia, int ja, int ib,
+                                           int jb, int max_hops, int lane, int c, LdsInt *s_won,
+                                           const int *g_won) {
+    Words<NW> f0, f1, un0, un1;
+    load_window<P, NW>(fb, w, un0, un1, lane);
+    const int ca = (ia + ja) & 1, cb = (ib + jb) & 1;
+    const int wa = (ja - w.j0) * P + (ia >> 6) - w.cw0, wb = (jb - w.j0) * P + (ib >> 6) - w.cw0;
+    const uint32_t ba = 1u << ((ia >> 1) & 31);
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+        const uint32_t seed = wa == lane * NW + j ? ba : 0u;
+        f0[j] = ca == 0 ? seed : 0u;
+        f1[j] = ca == 0 ? 0u : seed;
+        un0[j] &= ~f0[j];
+        un1[j] &= ~f1[j];
+    }
+    // b is reached when its bit leaves un, at a level into its own colour; its
+    // register index is the same on every lane (one relative register move)
+    const int lb = wb / NW, xb = wb % NW, sb = (ib >> 1) & 31;
+    auto reached = [&](const Words<NW> &un) {
+        return (((uint32_t)__builtin_amdgcn_readlane((int)un[xb], lb) >> sb) & 1u) == 0u;
+    };
+    int level = 0;
+    if (ca == 1) {  // the first move leaves colour 1
+        if (max_hops < 1) return -1;
+        level = 1;
+        (void)packed_level<P, NW, 0>(f1, f0, un0, lane);
+        if (cb == 0 && reached(un0)) return 1;
+    }
+    while (level < max_hops) {
         // a lower candidate of the round (s_won, LDS) or of the request (g_won,
         // device memory: other workgroups' rounds) already passed: this one
         // cannot win (looked at every 8 levels)
-        if ((level & 7) == 1) {
+        if ((level & 6) == 0) {
             if (s_won && __atomic_load_n(s_won, __ATOMIC_RELAXED) < c) return -1;
             if (g_won && __atomic_load_n(g_won, __ATOMIC_RELAXED) < c) return -1;
         }
-        bool more = wave_level<WPR>(f0, f1, un, lane);
-        if (!((__shfl(un[jb], lb) >> bb) & 1u)) return level;
-        if (!more || level + 1 > max_hops) return -1;
-        more = wave_level<WPR>(f1, f0, un, lane);
-        if (!((__shfl(un[jb], lb) >> bb) & 1u)) return level + 1;
-        if (!more) return -1;
+        (void)packed_level<P, NW, 1>(f0, f1, un1, lane);
+        ++level;
+        if (cb == 1 && reached(un1)) return level;
+        if (level >= max_hops) break;
+        // once a level is empty the next one is too: looked at every other level
+        const uint32_t any = packed_level<P, NW, 0>(f1, f0, un0, lane);
+        ++level;
+        if (cb == 0 && reached(un0)) return level;
+        if (__ballot(any != 0u) == 0ull) break;
     }
     return -1;
 }
 
-__device__ __forceinline__ bool lds_cell(const uint32_t *fb, const ReachDesc &d, int c) {
-    return (fb[(c / d.W) * d.wpr + ((c % d.W) >> 5)] >> ((c % d.W) & 31)) & 1u;
+// The smallest register layout for a window of ncw word columns and nr rows
+// (the map's pair_ok / label_ok says that one holds it).
+#define NAVSIM_PACKED_SHAPES(X, ncw, nr) \
+    if ((ncw) <= 1) {                    \
+        if ((nr) <= 256) X(1, 4)         \
+        else if ((nr) <= 512) X(1, 8)    \
+        else X(1, 16)                    \
+    } else if ((ncw) <= 2) {             \
+        if ((nr) <= 128) X(2, 4)         \
+        else if ((nr) <= 256) X(2, 8)    \
+        else X(2, 16)                    \
+    } else if ((ncw) <= 4) {             \
+        if ((nr) <= 128) X(4, 8)         \
+        else X(4, 16)                    \
+    } else if ((ncw) <= 8) X(8, 16)      \
+    else X(16, 16)
+
+// window_hops in the window of the cells that a path of at most max_hops moves
+// can touch: those within max_hops of a and b together (Manhattan distances),
+// that is at most (max_hops - |a - b|) / 2 cells outside the box of a and b.
+// Needs |a - b| <= max_hops; every argument is the same on every lane.  Inlined:
+// as a call, 41 registers a search went to scratch and back (3 % slower).
+__device__ __forceinline__ int search_hops(LdsWord *fb, int W, int H, int pk, int a,
+                                                     int b, int max_hops, int c, LdsInt *s_won,
+                                                     const int *g_won) {
+    const int lane = threadIdx.x & 63;
+    W = __builtin_amdgcn_readfirstlane(W);
+    a = __builtin_amdgcn_readfirstlane(a);
+    b = __builtin_amdgcn_readfirstlane(b);
+    const int hi = __builtin_amdgcn_readfirstlane(max_hops);
+    c = __builtin_amdgcn_readfirstlane(c);
+    const int ia = a % W, ja = a / W, ib = b % W, jb = b / W;
+    const int slack = (hi - abs(ia - ib) - abs(ja - jb)) >> 1;
+    Window w;
+    w.H = __builtin_amdgcn_readfirstlane(H);
+    w.pk = __builtin_amdgcn_readfirstlane(pk);
+    w.pwords = w.H * w.pk;
+    w.j0 = max(min(ja, jb) - slack, 0) & ~1;
+    w.cw0 = max(min(ia, ib) - slack, 0) >> 6;
+    const int nr = min(max(ja, jb) + slack, w.H - 1) - w.j0 + 1;
+    const int ncw = (min(max(ia, ib) + slack, W - 1) >> 6) - w.cw0 + 1;
+#define NAVSIM_X(p, nw) return window_hops<p, nw>(fb, w, ia, ja, ib, jb, hi, lane, c, s_won, g_won);
+    NAVSIM_PACKED_SHAPES(NAVSIM_X, ncw, nr)
+#undef NAVSIM_X
+}
+
+// Packed bitsets of a map (both colours) into LDS, 16 bytes at a time.
+__device__ __forceinline__ void stage_packed(const ReachParams &rp, const ReachDesc &d,
+                                             uint4 *fb4) {
+    const uint4 *g = reinterpret_cast<const uint4 *>(rp.packed + d.pk_off);
+    for (int w = threadIdx.x; w < (2 * d.pwords + 3) / 4; w += blockDim.x) fb4[w] = g[w];
+}
+
+__device__ __forceinline__ bool packed_cell(const uint32_t *fb, const ReachDesc &d, int c) {
+    const int i = c % d.W, j = c / d.W;
+    return (fb[((i + j) & 1) * d.pwords + j * d.pk + (i >> 6)] >> ((i >> 1) & 31)) & 1u;
 }
 
 // Nearest C-free cell to c (least |di| + |dj|, then least index; -1 if none),
 // by one wavefront: the cells of ring r split over the lanes, a ballot and a
 // lane minimum.
 __device__ int wave_snap(const ReachDesc &d, const uint32_t *fb, int c, int lane) {
-    if (lds_cell(fb, d, c)) return c;
+    if (packed_cell(fb, d, c)) return c;
     const int i0 = c % d.W, j0 = c / d.W;
     for (int r = 1; r <= d.W + d.H; ++r) {
         int best = INT_MAX;
@@ -375,7 +476,7 @@ __device__ int wave_snap(const ReachDesc &d, const uint32_t *fb, int c, int lane
             const int di = side == 0 ? r - t : (side == 1 ? -t : (side == 2 ? t - r : t));
             const int dj = side == 0 ? t : (side == 1 ? r - t : (side == 2 ? -t : t - r));
             const int i = i0 + di, j = j0 + dj;
-            if (i >= 0 && i < d.W && j >= 0 && j < d.H && lds_cell(fb, d, j * d.W + i))
+            if (i >= 0 && i < d.W && j >= 0 && j < d.H && packed_cell(fb, d, j * d.W + i))
                 best = min(best, j * d.W + i);
         }
 #pragma unroll
@@ -386,11 +487,10 @@ __device__ int wave_snap(const ReachDesc &d, const uint32_t *fb, int c, int lane
 }
 
 // The exact check of (a, b) for bin k by one wavefront (see check_pair).
-template <int WPR>
 __device__ int wave_check(const ReachParams &rp, const ReachDesc &d, const uint32_t *fb,
                           int a, int b, int k, int lane, int c = 0, const int *s_won = nullptr,
                           const int *g_won = nullptr) {
-    if (a < 0 || b < 0 || !lds_cell(fb, d, a) || !lds_cell(fb, d, b)) return -1;
+    if (a < 0 || b < 0 || !packed_cell(fb, d, a) || !packed_cell(fb, d, b)) return -1;
     if (centre_dist(d, a, b) < rp.gmd) return -1;
     const int hi = rp.bin_hi[k];
     int h;
@@ -398,7 +498,7 @@ __device__ int wave_check(const ReachParams &rp, const ReachDesc &d, const uint3
         h = 0;
     } else {
         const int man = abs(a % d.W - b % d.W) + abs(a / d.W - b / d.W);
-        h = man > hi ? -1 : wave_hops<WPR>(fb, d, a, b, hi, lane, c, s_won, g_won);
+        h = man > hi ? -1 : search_hops((LdsWord *)fb, d.W, d.H, d.pk, a, b, hi, c, (LdsInt *)s_won, g_won);
     }
     return (h >= 0 && rp.hop_bin[h] == k) ? h : -1;
 }
@@ -455,7 +555,7 @@ __device__ void write_request(const ProposeArgs &pa, const ReachDesc &d, int o, 
 // *_out arguments (every thread); with none valid and the request's last
 // candidate (a rejection attempt) in this round, that attempt's pair and
 // heading go there instead (the pair that stands when nothing is valid).
-template <int WPR, int W>
+template <int W>
 __device__ int check_round(const ReachParams &rp, const ProposeArgs &pa, const ReachDesc &d,
                            const uint32_t *fb, int i, int k, int c0, int total, int &a_out,
                            int &b_out, int &h_out, float &th_out, const int *g_won = nullptr) {
@@ -472,7 +572,7 @@ __device__ int check_round(const ReachParams &rp, const ProposeArgs &pa, const R
         candidate(rp, pa, d, fb, i, c, lane, a, b, th);
         // searches of higher candidates stop once a lower one has passed
         // (they cannot win); the winner and the check counts are unchanged
-        h = wave_check<WPR>(rp, d, fb, a, b, k, lane, c, &s_won, g_won);
+        h = wave_check(rp, d, fb, a, b, k, lane, c, &s_won, g_won);
         if (h >= 0 && lane == 0) atomicMin(&s_won, c);
     }
     if (lane == 0) {
@@ -507,7 +607,7 @@ __device__ int check_round(const ReachParams &rp, const ProposeArgs &pa, const R
     return win;
 }
 
-template <int WPR, int W>
+template <int W>
 __device__ void propose_waves(const ReachParams &rp, const ProposeArgs &pa, const ReachDesc &d,
                               const uint32_t *fb, int i, int o, int k) {
     const int total = pa.props + (d.free_cnt > 0 ? pa.tries : 0);
@@ -524,14 +624,15 @@ __device__ void propose_waves(const ReachParams &rp, const ProposeArgs &pa, cons
             }
             return;
         }
-        win = check_round<WPR, W>(rp, pa, d, fb, i, k, c0, total, la, lb, lh, lth);
+        win = check_round<W>(rp, pa, d, fb, i, k, c0, total, la, lb, lh, lth);
     }
     if (threadIdx.x == 0) write_request(pa, d, o, win, la, lb, lh, lth, total);
 }
 
 // One workgroup of W wavefronts per request.
 template <int W>
-__global__ __launch_bounds__(64 * W) void propose_kernel(ReachParams rp, ProposeArgs pa) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4)))
+void propose_kernel(ReachParams rp, ProposeArgs pa) {
     extern __shared__ uint4 lds4[];  // 16-byte aligned: the searches clear it 16 bytes at a time
     uint32_t *lds = reinterpret_cast<uint32_t *>(lds4);
     __shared__ int s_min;
@@ -555,18 +656,14 @@ __global__ __launch_bounds__(64 * W) void propose_kernel(ReachParams rp, Propose
     const ReachDesc d = rp.maps[mk];
     uint32_t *fb = lds, *vis = fb + kReachMaxWords, *fr = vis + kReachMaxWords,
              *nx = fr + kReachMaxWords;
+    if (d.pair_ok) {  // searches in registers
+        stage_packed(rp, d, lds4);
+        __syncthreads();
+        propose_waves<W>(rp, pa, d, lds, i, o, k);
+        return;
+    }
     stage_free(rp, d, fb);
     __syncthreads();
-    if (d.wpr * d.H <= kReachMaxWords && 32 % d.wpr == 0) {
-        switch (d.wpr) {  // rows of 1, 2, 4, ..., 32 words: searches in registers
-            case 1: propose_waves<1, W>(rp, pa, d, fb, i, o, k); return;
-            case 2: propose_waves<2, W>(rp, pa, d, fb, i, o, k); return;
-            case 4: propose_waves<4, W>(rp, pa, d, fb, i, o, k); return;
-            case 8: propose_waves<8, W>(rp, pa, d, fb, i, o, k); return;
-            case 16: propose_waves<16, W>(rp, pa, d, fb, i, o, k); return;
-            default: propose_waves<32, W>(rp, pa, d, fb, i, o, k); return;
-        }
-    }
     int checks = 0, src = -1, ra = -1, rb = -1, rh = -1;
     float th = 0.0f;
     for (int j = 0; j < pa.props && src < 0; ++j) {
@@ -798,6 +895,13 @@ unsigned nblocks(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 constexpr size_t kSearchLds = 4u * kReachMaxWords * sizeof(uint32_t);
 
+// LDS of the proposal kernels: the packed bitsets of the largest map; the LDS
+// search's four bitsets when some map needs it.
+size_t propose_lds(const ReachParams &rp) {
+    const size_t packed = (2u * (size_t)rp.max_pwords + 3u) / 4u * 16u;
+    return rp.all_pair ? packed : std::max(packed, kSearchLds);
+}
+
 }  // namespace
 
 hipError_t launch_label(const ReachParams &rp, int n, const int32_t *map, uint32_t first_sid,
@@ -816,8 +920,8 @@ hipError_t launch_label(const ReachParams &rp, int n, const int32_t *map, uint32
 // valid candidate already found is skipped (it cannot win).  Requests reach
 // the pending list only from the register search, so the same path serves.
 template <int W>
-__global__ __launch_bounds__(64 * W) void propose_tail_kernel(ReachParams rp, ProposeArgs pa,
-                                                              int tail_rounds) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4)))
+void propose_tail_kernel(ReachParams rp, ProposeArgs pa, int tail_rounds) {
     extern __shared__ uint4 lds4[];
     uint32_t *fb = reinterpret_cast<uint32_t *>(lds4);
     const int np = *pa.n_pend;
@@ -837,19 +941,11 @@ __global__ __launch_bounds__(64 * W) void propose_tail_kernel(ReachParams rp, Pr
         const bool skip = s_skip != 0;
         __syncthreads();
         if (skip) continue;
-        stage_free(rp, d, fb);
+        stage_packed(rp, d, lds4);
         __syncthreads();
-        int a = -1, b = -1, h = -1, win = -1;
+        int a = -1, b = -1, h = -1;
         float th = 0.0f;
-        const int *gw = &pa.best[p];
-        switch (d.wpr) {
-            case 1: win = check_round<1, W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, gw); break;
-            case 2: win = check_round<2, W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, gw); break;
-            case 4: win = check_round<4, W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, gw); break;
-            case 8: win = check_round<8, W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, gw); break;
-            case 16: win = check_round<16, W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, gw); break;
-            default: win = check_round<32, W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, gw); break;
-        }
+        const int win = check_round<W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, &pa.best[p]);
         if (threadIdx.x == 0 && win >= 0) {
             pa.tail[(int64_t)p * tail_rounds + r] = make_int4(a, b, h, __float_as_int(th));
             atomicMin(&pa.best[p], win);
@@ -894,10 +990,10 @@ hipError_t launch_propose_tail(const ReachParams &rp, const ProposeArgs &a, int 
     const unsigned g = (unsigned)std::min<int64_t>((int64_t)a.n * tail_rounds, 1024);
     const int W = propose_width(a.n);
     if (W == 8)
-        hipLaunchKernelGGL(propose_tail_kernel<8>, dim3(g), dim3(512), kSearchLds, s, rp, a,
+        hipLaunchKernelGGL(propose_tail_kernel<8>, dim3(g), dim3(512), propose_lds(rp), s, rp, a,
                            tail_rounds);
     else
-        hipLaunchKernelGGL(propose_tail_kernel<4>, dim3(g), dim3(256), kSearchLds, s, rp, a,
+        hipLaunchKernelGGL(propose_tail_kernel<4>, dim3(g), dim3(256), propose_lds(rp), s, rp, a,
                            tail_rounds);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -912,9 +1008,9 @@ hipError_t launch_propose(const ReachParams &rp, const ProposeArgs &a, hipStream
     // slowest requests, which set the launch's time; many (a batch): 4, fewer
     // checks past the first valid candidate
     if (propose_width(a.n) == 8)
-        hipLaunchKernelGGL(propose_kernel<8>, dim3((unsigned)a.n), dim3(512), kSearchLds, s, rp, a);
+        hipLaunchKernelGGL(propose_kernel<8>, dim3((unsigned)a.n), dim3(512), propose_lds(rp), s, rp, a);
     else
-        hipLaunchKernelGGL(propose_kernel<4>, dim3((unsigned)a.n), dim3(256), kSearchLds, s, rp, a);
+        hipLaunchKernelGGL(propose_kernel<4>, dim3((unsigned)a.n), dim3(256), propose_lds(rp), s, rp, a);
     return hipGetLastError();
 }
 

@@ -75,7 +75,7 @@ struct navsim_rp_s {
     ReachParams rp{};
     // tables
     ReachDesc *maps = nullptr;
-    uint32_t *bits = nullptr;
+    uint32_t *bits = nullptr, *packed = nullptr;
     int32_t *free_cells = nullptr;
     int8_t *hop_bin = nullptr;
     int32_t *bin_hi = nullptr;
@@ -127,7 +127,7 @@ navsim_status upload_vec(T **dst, const std::vector<T> &src) {
 }
 
 void free_rp(navsim_rp_s *r) {
-    void *ptrs[] = {r->maps, r->bits, r->free_cells, r->hop_bin, r->bin_hi, r->pool,
+    void *ptrs[] = {r->maps, r->bits, r->packed, r->free_cells, r->hop_bin, r->bin_hi, r->pool,
                     r->pool_rows, r->p, r->g, r->m, r->v, r->pb, r->decay, r->wloss};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -599,6 +599,31 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
         if (hop_bin[q] >= 0) bin_hi[hop_bin[q]] = q;
     }
     r->max_hops = maxh;
+    // the same cells by checkerboard colour, for the searches in registers.  A
+    // search of at most h moves stays within h + 2 rows for a pair (its window
+    // is aligned to an even row) and 2 h + 2 rows for a start; those rows times
+    // the row's words are what one wavefront has to hold
+    std::vector<uint32_t> packed;
+    for (int k = 0; k < M; ++k) {
+        ReachDesc &d = descs[k];
+        d.pk_off = (int64_t)packed.size();
+        d.pk = 1;
+        while (d.pk * 64 < d.W) d.pk *= 2;
+        if (d.pk > kPackedMaxRow) d.pk = 0;
+        d.pwords = d.H * d.pk;
+        const auto fits = [&](int64_t rows) {
+            return d.pk > 0 && std::min<int64_t>(rows, d.H) * d.pk <= kPackedWords;
+        };
+        d.pair_ok = fits((int64_t)maxh + 2);
+        d.label_ok = fits(2 * (int64_t)maxh + 2);
+        packed.resize((packed.size() + 2 * (size_t)d.pwords + 3) & ~(size_t)3, 0u);
+        const int32_t *fl = freel.data() + d.free_off;
+        for (int q = 0; q < d.free_cnt && d.pk > 0; ++q) {
+            const int i = fl[q] % d.W, j = fl[q] / d.W, c = (i + j) & 1;
+            packed[d.pk_off + (int64_t)c * d.pwords + (int64_t)j * d.pk + (i >> 6)] |=
+                1u << ((i >> 1) & 31);
+        }
+    }
     // network layout
     r->d0 = kPoolCells + c.num_bins + c.noise_dim;
     r->L = c.hidden_layers + 1;
@@ -636,6 +661,7 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
     };
     if ((st = upload_vec(&r->maps, descs)) != NAVSIM_OK) return fail_out(st);
     if ((st = upload_vec(&r->bits, bits)) != NAVSIM_OK) return fail_out(st);
+    if ((st = upload_vec(&r->packed, packed)) != NAVSIM_OK) return fail_out(st);
     if ((st = upload_vec(&r->free_cells, freel)) != NAVSIM_OK) return fail_out(st);
     if ((st = upload_vec(&r->hop_bin, hop_bin)) != NAVSIM_OK) return fail_out(st);
     if ((st = upload_vec(&r->bin_hi, bin_hi)) != NAVSIM_OK) return fail_out(st);
@@ -664,7 +690,18 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
     rp.max_hops = maxh;
     rp.nbins = c.num_bins;
     rp.num_maps = M;
+    rp.packed = r->packed;
     rp.gmd = (double)h->cfg.goal_min_dist_m;
+    rp.gmd2 = rp.gmd * rp.gmd;
+    while (rp.gmd2 > 0.0 && sqrt(rp.gmd2) >= rp.gmd) rp.gmd2 = nextafter(rp.gmd2, 0.0);
+    while (sqrt(rp.gmd2) < rp.gmd) rp.gmd2 = nextafter(rp.gmd2, INFINITY);
+    rp.all_pair = rp.all_label = 1;
+    rp.max_pwords = 0;
+    for (const ReachDesc &d : descs) {
+        rp.all_pair = rp.all_pair && d.pair_ok;
+        rp.all_label = rp.all_label && d.label_ok;
+        rp.max_pwords = std::max(rp.max_pwords, d.pwords);
+    }
     rp.key0 = (uint32_t)(c.seed & 0xffffffffu);
     rp.key1 = (uint32_t)(c.seed >> 32);
     // the fixed workspace's device address on this device (the device is current)

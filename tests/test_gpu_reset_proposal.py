@@ -406,3 +406,66 @@ def test_wide_and_narrow_candidate_rounds_agree():
     assert (src >= 0).mean() > 0.5 and (src >= 8).any()  # network draws and rejection both used
     rp.close()
     sim.close()
+
+
+# (W, H): rows of 1, 2, 4, 8 and 16 packed words, widths on both sides of a word's
+# 64 cells, heights on both sides of a register layout's rows, odd sizes, and a map
+# too wide for the register search
+SEARCH_MAPS = [(32, 600), (63, 33), (64, 200), (65, 130), (100, 127), (127, 300), (129, 255),
+               (200, 129), (256, 256), (257, 120), (512, 101), (513, 64), (1000, 50), (1030, 40)]
+
+
+@pytest.mark.parametrize("d_hi", [2.0, 12.0])
+def test_search_windows_match_oracle_bitwise(d_hi):
+    """Rejection draws (one search per attempt, in the window its hop limit
+    allows) on one map of every register layout, bins whose searches stay small
+    and bins whose searches cover the map."""
+    say(f"searches on {len(SEARCH_MAPS)} map shapes, hop counts up to {d_hi} m")
+    rng = np.random.default_rng(21)
+    maps = []
+    for w, h in SEARCH_MAPS:
+        m = (rng.random((h, w)) < 0.02).astype(np.uint8)
+        for _ in range(w * h // 900):  # walls, so that paths bend and some cells are cut off
+            x, y = int(rng.integers(0, w)), int(rng.integers(0, h))
+            if rng.random() < 0.5:
+                m[y, x:x + int(rng.integers(4, 28))] = 1
+            else:
+                m[y:y + int(rng.integers(4, 28)), x] = 1
+        maps.append(m)
+    num = len(maps)
+    cfg = dict(configs.build_workload("c5", num_envs=num)["cfg"], radius_m=0.02,
+               goal_min_dist_m=0.35)
+    env_map = np.arange(num, dtype=np.int32)
+    sim = NavSim(cfg, maps, [0.05] * num, env_map, device=0)
+    rp = ResetProposer(sim, d_lo_m=0.0, d_hi_m=d_hi, num_bins=5, seed=77)
+    ref = oracle.OracleSim(cfg, maps, [0.05] * num, env_map)
+    reach = []
+    for k in range(num):
+        M = ref.maps
+        cf = np.zeros(maps[k].size, np.uint8)
+        cf[M.free_cells[M.free_off[k]:M.free_off[k] + M.free_cnt[k]]] = 1
+        reach.append(G.ReachMap(cf.reshape(maps[k].shape), 0.05, seed=77, d_lo=0.0, d_hi=d_hi,
+                                nbins=5, gmd=cfg["goal_min_dist_m"]))
+    n = 10 * num
+    mp, bins = np.arange(n) % num, rng.integers(0, 5, n)
+    env, ep = rng.integers(0, 1 << 20, n), rng.integers(0, 50, n)
+    out = rp.propose(mp, bins, env, ep, proposals=0, max_tries=150)
+    lab = rp.label(np.arange(3 * num) % num, first_sid=50)
+    torch.cuda.synchronize()
+    pose, hops, src, chk = (out[k].cpu().numpy() for k in ("pose", "hops", "source", "checks"))
+    for i in range(n):
+        R = reach[mp[i]]
+        t, a, b, h, th = R.reject(int(env[i]), int(ep[i]), int(bins[i]), 150, with_heading=True)
+        assert (src[i], hops[i]) == (t, h), (SEARCH_MAPS[mp[i]], i, src[i], t, hops[i], h)
+        assert chk[i] == (t + 1 if t >= 0 else 150)
+        if t >= 0:
+            want = [*R.centre(a), th, *R.centre(b)]
+            assert np.array_equal(pose[i], np.array(want, np.float32)), (SEARCH_MAPS[mp[i]], i)
+    assert (src >= 0).mean() > 0.3
+    st, gl, hp = (lab[k].cpu().numpy() for k in ("start", "goal", "hops"))
+    for i in range(3 * num):
+        a, g, h = reach[i % num].label_start(50 + i)
+        assert st[i] == a and np.array_equal(gl[i], g) and np.array_equal(hp[i], h), \
+            (SEARCH_MAPS[i % num], i, gl[i], g, hp[i], h)
+    rp.close()
+    sim.close()
