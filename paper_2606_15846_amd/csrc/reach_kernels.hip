@@ -207,14 +207,8 @@ __global__ __launch_bounds__(kReachThreads) void label_kernel(ReachParams rp, co
     const int mk = map[i];
     const ReachDesc d = rp.maps[(mk >= 0 && mk < rp.num_maps) ? mk : 0];
     const uint32_t sid = first_sid + (uint32_t)i;
-    if (d.free_cnt == 0 || mk < 0 || mk >= rp.num_maps) {
-        if (tid < rp.nbins) {
-            goal[(int64_t)i * rp.nbins + tid] = -1;
-            hops[(int64_t)i * rp.nbins + tid] = -1;
-        }
-        if (tid == 0) start[i] = -1;
-        return;
-    }
+    // those without a start, and those of label_wave_kernel
+    if (d.free_cnt == 0 || mk < 0 || mk >= rp.num_maps || d.label_ok) return;
     uint32_t *fb = lds, *vis = fb + kReachMaxWords, *fr = vis + kReachMaxWords,
              *nx = fr + kReachMaxWords;
     uint32_t c[4] = {sid, 0u, 0u, 6u};
@@ -337,8 +331,8 @@ struct Window {
 };
 
 // The C-free words of a window, both colours (words outside the map are 0).
-template <int P, int NW>
-__device__ __forceinline__ void load_window(LdsWord *fb, const Window &w, Words<NW> &un0,
+template <int P, int NW, typename Ptr>
+__device__ __forceinline__ void load_window(Ptr fb, const Window &w, Words<NW> &un0,
                                             Words<NW> &un1, int lane) {
     const int r0 = w.j0 + lane * (NW / P);
 #pragma unroll
@@ -447,6 +441,170 @@ __device__ __forceinline__ int search_hops(LdsWord *fb, int W, int H, int pk, in
     const int nr = min(max(ja, jb) + slack, w.H - 1) - w.j0 + 1;
     const int ncw = (min(max(ia, ib) + slack, W - 1) >> 6) - w.cw0 + 1;
 #define NAVSIM_X(p, nw) return window_hops<p, nw>(fb, w, ia, ja, ib, jb, hi, lane, c, s_won, g_won);
+    NAVSIM_PACKED_SHAPES(NAVSIM_X, ncw, nr)
+#undef NAVSIM_X
+}
+
+// ---------------------------------------------------------------------------
+// Labelling by one wavefront per start, for maps whose searches fit its
+// registers: the levels of packed_level from the start, and for every cell that
+// a level reaches one Philox word (the cell's random key in its bin), of which
+// each bin keeps the smallest.  A level reaches a few cells of a few lanes, so
+// they first go to a queue in LDS, one cell per lane and pass, and 64 at a time
+// are drawn with every lane busy.  Bound by VALU issue: about 0.4 of it each in
+// the draws and in the queue's passes, the rest in the levels.  16,384 starts on
+// 64 maps of 256 x 256, 12 m: 29.1 -> 4.5 ms against a workgroup's search in LDS
+// (a barrier per level, draws by the few threads that hold the level's words).
+constexpr int kLabelQueue = 512;  // entries per wavefront: level << 16 | packed bit index
+constexpr int kLabelWaves = 4;    // starts per workgroup
+typedef __attribute__((address_space(3))) uint32_t LdsQueue;
+
+template <int P, int NW>
+__device__ __forceinline__ void label_window(const ReachParams &rp, const ReachDesc &d,
+                                             const Window &w, int ia, int ja, uint32_t sid,
+                                             int lane, LdsQueue *queue, int32_t *goal,
+                                             int32_t *hops) {
+    Words<NW> f0, f1, un0, un1;
+    load_window<P, NW>(rp.packed + d.pk_off, w, un0, un1, lane);
+    const int ca = (ia + ja) & 1, wa = (ja - w.j0) * P + (ia >> 6) - w.cw0;
+    const uint32_t ba = 1u << ((ia >> 1) & 31);
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+        const uint32_t seed = wa == lane * NW + j ? ba : 0u;
+        f0[j] = ca == 0 ? seed : 0u;
+        f1[j] = ca == 0 ? 0u : seed;
+        un0[j] &= ~f0[j];
+        un1[j] &= ~f1[j];
+    }
+    const double s = (double)d.s;
+    unsigned long long best = ~0ull, found = ~0ull;  // found: lane k holds bin k's result
+    int head = 0, cnt = 0;                           // the queue's first entry and length
+    // draws of the queue's first n <= 64 cells
+    auto take = [&](int n) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t code = queue[(head + lane) & (kLabelQueue - 1)];
+        head = (head + n) & (kLabelQueue - 1);
+        cnt -= n;
+        if (lane >= n) return;
+        const int wi = (int)(code & 0xffffu) >> 5, h = (int)(code >> 16);
+        const int row = w.j0 + wi / P;
+        const int col = 64 * (w.cw0 + wi % P) + 2 * (int)(code & 31u) + ((row + ca + h) & 1);
+        const int cell = row * d.W + col;
+        const double dx = (double)(col - ia) * s, dy = (double)(row - ja) * s;
+        if (dx * dx + dy * dy < rp.gmd2) return;  // centre_dist below gmd
+        uint32_t q[4] = {sid, (uint32_t)cell, 0u, 5u};
+        philox4x32_10(q, rp.key0, rp.key1);
+        const unsigned long long v = ((unsigned long long)q[0] << 32) |
+                                     ((unsigned long long)cell << 16) | (unsigned long long)h;
+        best = v < best ? v : best;
+    };
+    // the cells of a level that bin k counts, one per lane and pass
+    auto put = [&](Words<NW> n, int level) {
+        const uint32_t base = ((uint32_t)level << 16) + (uint32_t)(lane * NW * 32);
+        uint32_t left;
+        do {
+            left = 0u;
+#pragma unroll
+            for (int j = 0; j < NW; ++j) {
+                for (;;) {
+                    const uint64_t m = __ballot(n[j] != 0u);
+                    if (m == 0ull || cnt > kLabelQueue - 64) break;
+                    if (n[j] != 0u) {
+                        const int at = head + cnt +
+                                       (int)__builtin_amdgcn_mbcnt_hi(
+                                           (uint32_t)(m >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                        queue[at & (kLabelQueue - 1)] =
+                            base + (uint32_t)(32 * j) + (uint32_t)__builtin_ctz(n[j]);
+                        n[j] &= n[j] - 1u;
+                    }
+                    cnt += __popcll(m);
+                }
+                left |= n[j];
+            }
+            while (cnt >= 64) take(64);
+        } while (__ballot(left != 0u) != 0ull);
+    };
+    // the smallest key of bin k, kept by lane k
+    auto close_bin = [&](int k) {
+        if (k < 0) return;
+        if (cnt > 0) take(cnt);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned long long v = __shfl_xor(best, o);
+            best = v < best ? v : best;
+        }
+        if (lane == k) found = best;
+        best = ~0ull;
+    };
+    int level = 0, k = -1;
+    int next = rp.hop_bin[min(1, rp.max_hops)];  // bin of the next level, loaded a level ahead
+    auto advance = [&](uint32_t any, const Words<NW> &nx) {
+        ++level;
+        const int b = __builtin_amdgcn_readfirstlane(next);
+        next = rp.hop_bin[min(level + 1, rp.max_hops)];
+        if (b != k) {
+            close_bin(k);
+            k = b;
+        }
+        if (__ballot(any != 0u) == 0ull) return false;
+        if (b >= 0) put(nx, level);
+        return level < rp.max_hops;
+    };
+    bool more = rp.max_hops > 0;
+    if (more && ca == 1) more = advance(packed_level<P, NW, 0>(f1, f0, un0, lane), f0);
+    while (more) {
+        if (!advance(packed_level<P, NW, 1>(f0, f1, un1, lane), f1)) break;
+        more = advance(packed_level<P, NW, 0>(f1, f0, un0, lane), f0);
+    }
+    close_bin(k);
+    if (lane < rp.nbins) {
+        goal[lane] = found == ~0ull ? -1 : (int32_t)((found >> 16) & 0xffffu);
+        hops[lane] = found == ~0ull ? -1 : (int32_t)(found & 0xffffu);
+    }
+}
+
+// Start i by wavefront i; starts on maps that the register search does not hold
+// are left to label_kernel.
+__global__ __launch_bounds__(64 * kLabelWaves) __attribute__((amdgpu_waves_per_eu(4)))
+void label_wave_kernel(ReachParams rp, int n, const int32_t *map, uint32_t first_sid,
+                       int32_t *start, int32_t *goal, int32_t *hops) {
+    __shared__ uint32_t s_queue[kLabelWaves][kLabelQueue];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int i = (int)blockIdx.x * kLabelWaves + wave;
+    if (i >= n) return;
+    const int mk = __builtin_amdgcn_readfirstlane(map[i]);
+    const bool known = mk >= 0 && mk < rp.num_maps;
+    const ReachDesc d = rp.maps[known ? mk : 0];
+    goal += (int64_t)i * rp.nbins;
+    hops += (int64_t)i * rp.nbins;
+    if (!known || d.free_cnt == 0) {
+        if (lane < rp.nbins) {
+            goal[lane] = -1;
+            hops[lane] = -1;
+        }
+        if (lane == 0) start[i] = -1;
+        return;
+    }
+    if (!d.label_ok) return;
+    const uint32_t sid = first_sid + (uint32_t)i;
+    uint32_t c[4] = {sid, 0u, 0u, 6u};
+    philox4x32_10(c, rp.key0, rp.key1);
+    const int a = __builtin_amdgcn_readfirstlane(
+        rp.free_cells[d.free_off + pick_of(c[0], d.free_cnt)]);
+    if (lane == 0) start[i] = a;
+    const int ia = a % d.W, ja = a / d.W;
+    Window w;
+    w.H = d.H;
+    w.pk = d.pk;
+    w.pwords = d.pwords;
+    w.j0 = max(ja - rp.max_hops, 0) & ~1;
+    w.cw0 = max(ia - rp.max_hops, 0) >> 6;
+    const int nr = min(ja + rp.max_hops, d.H - 1) - w.j0 + 1;
+    const int ncw = (min(ia + rp.max_hops, d.W - 1) >> 6) - w.cw0 + 1;
+    LdsQueue *queue = (LdsQueue *)s_queue[wave];
+#define NAVSIM_X(p, nw) label_window<p, nw>(rp, d, w, ia, ja, sid, lane, queue, goal, hops);
     NAVSIM_PACKED_SHAPES(NAVSIM_X, ncw, nr)
 #undef NAVSIM_X
 }
@@ -907,6 +1065,10 @@ size_t propose_lds(const ReachParams &rp) {
 hipError_t launch_label(const ReachParams &rp, int n, const int32_t *map, uint32_t first_sid,
                         int32_t *start, int32_t *goal, int32_t *hops, hipStream_t s) {
     if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(label_wave_kernel, dim3(nblocks(n, kLabelWaves)), dim3(64 * kLabelWaves), 0,
+                       s, rp, n, map, first_sid, start, goal, hops);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || rp.all_label) return e;
     hipLaunchKernelGGL(label_kernel, dim3((unsigned)n), dim3(kReachThreads), kSearchLds, s, rp,
                        map, first_sid, start, goal, hops);
     return hipGetLastError();

@@ -541,7 +541,7 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
     r->num_maps = M;
     // bitsets, free lists, pooled occupancy
     std::vector<ReachDesc> descs(M);
-    std::vector<uint32_t> bits;
+    std::vector<uint32_t> bits, packed;  // the C-free cells, and the same by checkerboard colour
     std::vector<int32_t> freel;
     std::vector<float> pool((size_t)M * kPoolCells, 0.0f);
     for (int k = 0; k < M; ++k) {
@@ -556,11 +556,25 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
         d.free_cnt = h->host_free_cnt[k];
         d.s = h->host_res[k];
         bits.resize(bits.size() + d.words, 0u);
+        d.pk_off = (int64_t)packed.size();
+        d.pk = 1;
+        while (d.pk * 64 < W) d.pk *= 2;
+        if (d.pk > kPackedMaxRow) d.pk = 0;
+        d.pwords = H * d.pk;
+        packed.resize((packed.size() + 2 * (size_t)d.pwords + 3) & ~(size_t)3, 0u);
         const int32_t *fl = h->host_free.data() + h->host_free_off[k];
+        freel.insert(freel.end(), fl, fl + d.free_cnt);
+        uint32_t *row = bits.data() + d.bit_off, *pk = packed.data() + d.pk_off;
+        int j = 0, first = 0;  // row of the cell and its first cell: the list is in cell order
         for (int q = 0; q < d.free_cnt; ++q) {
-            const int cell = fl[q], i = cell % W, j = cell / W;
-            bits[d.bit_off + (int64_t)j * d.wpr + (i >> 5)] |= 1u << (i & 31);
-            freel.push_back(cell);
+            while (fl[q] >= first + W) {
+                first += W;
+                ++j;
+            }
+            const int i = fl[q] - first;
+            row[j * d.wpr + (i >> 5)] |= 1u << (i & 31);
+            if (d.pk > 0)
+                pk[((i + j) & 1) * d.pwords + j * d.pk + (i >> 6)] |= 1u << ((i >> 1) & 31);
         }
         const uint8_t *occ = h->host_occ.data() + h->host_occ_off[k];
         for (int q = 0; q < 32; ++q)
@@ -599,30 +613,15 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
         if (hop_bin[q] >= 0) bin_hi[hop_bin[q]] = q;
     }
     r->max_hops = maxh;
-    // the same cells by checkerboard colour, for the searches in registers.  A
-    // search of at most h moves stays within h + 2 rows for a pair (its window
+    // A search of at most h moves stays within h + 2 rows for a pair (its window
     // is aligned to an even row) and 2 h + 2 rows for a start; those rows times
-    // the row's words are what one wavefront has to hold
-    std::vector<uint32_t> packed;
-    for (int k = 0; k < M; ++k) {
-        ReachDesc &d = descs[k];
-        d.pk_off = (int64_t)packed.size();
-        d.pk = 1;
-        while (d.pk * 64 < d.W) d.pk *= 2;
-        if (d.pk > kPackedMaxRow) d.pk = 0;
-        d.pwords = d.H * d.pk;
+    // the row's packed words are what one wavefront has to hold
+    for (ReachDesc &d : descs) {
         const auto fits = [&](int64_t rows) {
             return d.pk > 0 && std::min<int64_t>(rows, d.H) * d.pk <= kPackedWords;
         };
         d.pair_ok = fits((int64_t)maxh + 2);
         d.label_ok = fits(2 * (int64_t)maxh + 2);
-        packed.resize((packed.size() + 2 * (size_t)d.pwords + 3) & ~(size_t)3, 0u);
-        const int32_t *fl = freel.data() + d.free_off;
-        for (int q = 0; q < d.free_cnt && d.pk > 0; ++q) {
-            const int i = fl[q] % d.W, j = fl[q] / d.W, c = (i + j) & 1;
-            packed[d.pk_off + (int64_t)c * d.pwords + (int64_t)j * d.pk + (i >> 6)] |=
-                1u << ((i >> 1) & 31);
-        }
     }
     // network layout
     r->d0 = kPoolCells + c.num_bins + c.noise_dim;
