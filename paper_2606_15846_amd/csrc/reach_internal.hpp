@@ -17,9 +17,6 @@ constexpr int kPackedMaxRow = 16;
 // propose_kernel: one candidate check per wavefront, 8 at a time for launches
 // of at most this many requests, else 4
 constexpr int kProposeWideMax = 2048;
-// in-step proposals: rounds a request's own workgroup checks before its other
-// rounds go to the tail launch, all at once
-constexpr int kProposeHeadRounds = 1;
 constexpr int kPoolCells = 1024;      // 32 x 32 pooled occupancy
 
 // One map's C-free cells, twice: a plain bitset (row j, column i is bit i & 31
@@ -82,8 +79,10 @@ struct ProposeArgs {
     int32_t *pend = nullptr, *n_pend = nullptr, *best = nullptr;
     int4 *tail = nullptr;
 };
-// Candidates checked together per request (one per wavefront).
+// Candidates checked together per request (one per wavefront), and the rounds a
+// request's own workgroup checks before its other rounds go to the tail launch.
 int propose_width(int n);
+int propose_head_rounds(int n);
 hipError_t launch_propose(const ReachParams &rp, const ProposeArgs &a, hipStream_t s);
 // The rounds head_rounds .. head_rounds + tail_rounds - 1 of the pending
 // requests (a.n = the most there can be), then their outputs.
@@ -103,7 +102,9 @@ struct NoiseArgs {
     uint16_t *z;
     int32_t *row_idx;
     const int32_t *n_dev = nullptr;  // optional: requests = min(n, *n_dev) read on the device
+    int32_t *clear = nullptr;  // optional: a count set to 0 for the launches that follow
 };
+hipError_t launch_clear_count(int32_t *count, hipStream_t s);
 hipError_t launch_noise(const NoiseArgs &a, uint32_t key0, uint32_t key1, hipStream_t s);
 
 // Requests of the envs that deferred their reset in a step: in env order,

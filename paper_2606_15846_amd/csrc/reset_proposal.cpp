@@ -111,7 +111,7 @@ struct navsim_rp_s {
     } at;
     // workspaces
     DevBuf ctable, colsum, x, hid[4], y, dyf, dyb, dh, dzf, dzb, lrows, zc, ridx, yc, hc[2],
-        bmap, bbin, target, chosen, zp, rp_idx, yp;
+        bmap, bbin, target, chosen, zp, rp_idx, yp, pend;
 };
 
 namespace {
@@ -134,7 +134,7 @@ void free_rp(navsim_rp_s *r) {
     DevBuf *bufs[] = {&r->ctable, &r->colsum, &r->x, &r->hid[0], &r->hid[1], &r->hid[2],
                       &r->hid[3], &r->y, &r->dyf, &r->dyb, &r->dh, &r->dzf, &r->dzb, &r->lrows,
                       &r->zc, &r->ridx, &r->yc, &r->hc[0], &r->hc[1], &r->bmap, &r->bbin,
-                      &r->target, &r->chosen, &r->zp, &r->rp_idx, &r->yp};
+                      &r->target, &r->chosen, &r->zp, &r->rp_idx, &r->yp, &r->pend};
     for (DevBuf *b : bufs) b->release();
 }
 
@@ -336,16 +336,40 @@ navsim_status check_propose(const navsim_rp_s *r, int32_t n, const int32_t *map,
 }
 
 // Device buffers of one proposal call: the constant first-layer table, noise
-// inputs, their table rows, network outputs and two hidden activations.
+// inputs, their table rows, network outputs and two hidden activations; and the
+// tail launch's pending list (tail_bytes, NULL: every round in one launch).
 struct ProposeWork {
     float *ct = nullptr;
     uint16_t *z = nullptr;
     int32_t *row_idx = nullptr;
     float *y = nullptr;
     uint16_t *hc0 = nullptr, *hc1 = nullptr;
+    uint8_t *pend = nullptr;
 };
 
 constexpr size_t align_up(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Rounds of a call's requests that its tail launch takes (0: none left after
+// the head rounds).
+int64_t tail_rounds_of(int32_t n, int32_t proposals, int32_t max_tries) {
+    const int W = propose_width(n);
+    const int64_t rounds = ((int64_t)proposals + max_tries + W - 1) / W;
+    return std::max<int64_t>(0, rounds - propose_head_rounds(n));
+}
+
+// Bytes of the tail launch's pending count, list, best candidates and round
+// slots; 0 for a call whose requests' workgroups rather check every round: with
+// one round left its place does not matter (2 rounds of 16 attempts, 128
+// requests: 139 us, with a tail 172); a few requests with network draws mostly
+// end in their first rounds, and the two launches cost more than the slowest
+// one's rounds (32 draws, 64 attempts: 64 requests 176 against 207 us, 128
+// requests 290 against 236; without draws the tail pays from 32 requests,
+// 293 against 151 us); and 2^22 slots (64 MiB) bound the workspace.
+size_t tail_bytes(int32_t n, int32_t proposals, int32_t max_tries) {
+    const int64_t rounds = tail_rounds_of(n, proposals, max_tries);
+    if (rounds < 2 || (proposals > 0 && n < 128) || (int64_t)n * rounds > (1 << 22)) return 0;
+    return 256 + 2 * align_up((size_t)n * 4) + (size_t)(n * rounds) * 16;
+}
 
 // Fixed-workspace bytes of a call with n requests x `proposals` draws (0
 // when proposals is 0: the rejection sampler alone uses no workspace).
@@ -381,6 +405,7 @@ navsim_status propose_run(navsim_rp_s *r, int32_t n, const int32_t *map, const i
         na.bin = bin;
         na.z = w.z;
         na.row_idx = w.row_idx;
+        na.clear = (int32_t *)w.pend;
         RP_HIP(launch_noise(na, r->rp.key0, r->rp.key1, s));
         if ((st = forward_noise(r, (int)R, na.z, na.row_idx, w.y, w.ct, w.hc0, w.hc1, s)) !=
             NAVSIM_OK)
@@ -401,7 +426,17 @@ navsim_status propose_run(navsim_rp_s *r, int32_t n, const int32_t *map, const i
     pa.hops = hops;
     pa.source = source;
     pa.checks = checks;
+    const int tail_rounds = w.pend ? (int)tail_rounds_of(n, proposals, max_tries) : 0;
+    if (tail_rounds > 0) {
+        pa.head_rounds = propose_head_rounds(n);
+        pa.n_pend = (int32_t *)w.pend;
+        pa.pend = (int32_t *)(w.pend + 256);
+        pa.best = (int32_t *)(w.pend + 256 + align_up((size_t)n * 4));
+        pa.tail = (int4 *)(w.pend + 256 + 2 * align_up((size_t)n * 4));
+        if (proposals == 0) RP_HIP(launch_clear_count(pa.n_pend, s));
+    }
     RP_HIP(launch_propose(r->rp, pa, s));
+    if (tail_rounds > 0) RP_HIP(launch_propose_tail(r->rp, pa, tail_rounds, s));
     return NAVSIM_OK;
 }
 
@@ -476,11 +511,9 @@ navsim_status rp_hook_run(void *ctx, hipStream_t s) {
     // the few requests with no valid candidate in their head rounds set the
     // launch's time when their rounds run one after another: their remaining
     // rounds go to one tail launch, one workgroup per round
-    const int tail_rounds =
-        std::max(0, (int)(((int64_t)A.props + A.tries + propose_width(A.cap) - 1) /
-                          propose_width(A.cap)) - kProposeHeadRounds);
+    const int tail_rounds = (int)tail_rounds_of(A.cap, A.props, A.tries);
     if (tail_rounds > 0) {
-        pa.head_rounds = kProposeHeadRounds;
+        pa.head_rounds = propose_head_rounds(A.cap);
         pa.pend = A.pend;
         pa.n_pend = A.n_dev + 1;
         pa.best = A.best;
@@ -838,6 +871,10 @@ navsim_status navsim_rp_propose(navsim_rp_t r, int32_t n, const int32_t *map, co
         w = ProposeWork{r->ctable.as<float>(), r->zp.as<uint16_t>(), r->rp_idx.as<int32_t>(),
                         r->yp.as<float>(), r->hc[0].as<uint16_t>(), r->hc[1].as<uint16_t>()};
     }
+    if (const size_t tb = tail_bytes(n, proposals, max_tries)) {
+        RP_BUF(r->pend, tb);
+        w.pend = r->pend.as<uint8_t>();
+    }
     return propose_run(r, n, map, bin, env, episode, proposals, max_tries, pose, hops, source,
                        checks, y_out, w, (hipStream_t)stream);
 }
@@ -861,11 +898,14 @@ navsim_status navsim_rp_propose_noalloc(navsim_rp_t r, int32_t n, const int32_t 
     if (n == 0) return NAVSIM_OK;
     DeviceGuard dg(r->device);
     ProposeWork w;
+    uint8_t *base = (uint8_t *)r->scratch;
+    // the pending list takes part of what the other parts leave, if it fits
+    const size_t tb = tail_bytes(n, proposals, max_tries);
+    if (tb > 0 && need + tb <= kRpScratchBytes) w.pend = base + need;
     if (proposals > 0) {
         // carve the fixed workspace in the order noalloc_bytes() counts it
         const int64_t R = (int64_t)n * proposals;
         const int Hd = hidden_width(r);
-        uint8_t *base = (uint8_t *)r->scratch;
         size_t off = 0;
         auto take = [&](size_t bytes) {
             uint8_t *q = base + off;
@@ -977,9 +1017,7 @@ navsim_status navsim_rp_attach(navsim_rp_t r, const int32_t *bin, int32_t propos
     if (dg.err != hipSuccess) return fail(NAVSIM_E_HIP, "hipSetDevice: %s", hipGetErrorString(dg.err));
     navsim_rp_s::Attach &A = r->at;
     // rounds of candidates after the head rounds (one tail workgroup each)
-    const int W = propose_width(max_per_step);
-    const int64_t rounds = ((int64_t)proposals + max_tries + W - 1) / W;
-    const int tail_rounds = (int)std::max<int64_t>(0, rounds - kProposeHeadRounds);
+    const int tail_rounds = (int)tail_rounds_of(max_per_step, proposals, max_tries);
     if ((int64_t)max_per_step * tail_rounds > (1 << 24))
         return fail(NAVSIM_E_INVALID_ARG, "max_per_step * candidate rounds must be at most 2^24");
     if (!(A.on && A.cap == max_per_step && A.props == proposals && A.tail_rounds >= tail_rounds)) {

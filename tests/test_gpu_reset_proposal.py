@@ -469,3 +469,28 @@ def test_search_windows_match_oracle_bitwise(d_hi):
             (SEARCH_MAPS[i % num], i, gl[i], g, hp[i], h)
     rp.close()
     sim.close()
+
+
+@pytest.mark.parametrize("n,proposals,tries", [(127, 8, 24), (128, 8, 24), (128, 0, 16),
+                                               (40, 0, 17), (2049, 4, 12), (2049, 4, 13)])
+def test_pending_rounds_agree_with_single_requests(n, proposals, tries):
+    """Calls on both sides of the rules for the tail launch (rounds left, number
+    of requests): every request as the call with that request alone gives it."""
+    say(f"{n} requests, {proposals} draws, {tries} attempts == its requests 20 at a time")
+    sim, rp, ref, reach, _ = setup()
+    rng = np.random.default_rng(12)
+    mp, bins = rng.integers(0, 4, n), rng.integers(0, rp.nb, n)
+    env, ep = np.arange(n), np.arange(n) * 5 % 11
+    whole = rp.propose(mp, bins, env, ep, proposals=proposals, max_tries=tries)
+    again = rp.propose(mp, bins, env, ep, proposals=proposals, max_tries=tries)
+    fixed = rp.propose(mp, bins, env, ep, proposals=proposals, max_tries=tries, noalloc=True)
+    parts = [rp.propose(mp[i:i + 20], bins[i:i + 20], env[i:i + 20], ep[i:i + 20],
+                        proposals=proposals, max_tries=tries) for i in range(0, n, 20)]
+    torch.cuda.synchronize()
+    for k in ("pose", "hops", "source", "checks"):
+        a = whole[k].cpu().numpy()
+        assert np.array_equal(a, again[k].cpu().numpy()), k
+        assert np.array_equal(a, fixed[k].cpu().numpy()), k
+        assert np.array_equal(a, np.concatenate([p[k].cpu().numpy() for p in parts])), k
+    rp.close()
+    sim.close()
