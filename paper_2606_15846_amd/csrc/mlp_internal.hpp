@@ -37,6 +37,31 @@ struct GemmArgs {
 
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t s);
 
+// The reset proposer's network on noise rows in one launch: request i < n draws
+// rows i per .. i per + per - 1; row r = i per + j takes its nz noise columns
+// from Philox(c0[i] or i, c1[i] or c1_const, (j << 8) | q, stream) as
+// launch_noise does, the constant part of its first layer from row map[i] nbins +
+// bin[i] of ct (row 0 when out of range), and writes y[r][5].  Weights bf16 in
+// their packed image, biases float in the parameter vector p (layer l at b_off[l]).
+constexpr int kForwardMaxLayers = 5;
+struct ForwardNoiseArgs {
+    int n = 0, per = 0, nz = 0, nbins = 0, num_maps = 0, layers = 0;
+    const uint32_t *c0 = nullptr, *c1 = nullptr;
+    uint32_t c1_const = 0, stream = 0, key0 = 0, key1 = 0;
+    const int32_t *map = nullptr, *bin = nullptr;
+    const uint16_t *packed = nullptr;
+    const float *p = nullptr, *ct = nullptr;
+    int64_t b_off[kForwardMaxLayers] = {};
+    float slope = 0.0f;
+    float *y = nullptr;
+    uint16_t *z = nullptr;           // optional: the noise, [rows][nz] bf16
+    const int32_t *n_dev = nullptr;  // optional: requests = min(n, *n_dev) read on the device
+    int32_t *clear = nullptr;        // optional: a count set to 0 for the launches that follow
+};
+// Hidden widths that the one launch serves (its register layout is per width).
+bool forward_noise_supported(int hidden);
+hipError_t launch_forward_noise(const ForwardNoiseArgs &a, int hidden, hipStream_t s);
+
 // dZ = dH * act'(H) for leaky ReLU (H is the layer's bfloat16 output, whose
 // sign is that of its input); writes float dZf and bfloat16 dZb, [M, N] rows
 // of stride ld.  act 0: dZ = dH.
@@ -54,13 +79,23 @@ hipError_t launch_col_sum(int M, int N, const float *X, float *partial, float *o
 hipError_t launch_sq_loss(int M, int D, const float *Y, const float *T, const float *w,
                           float *L, float *dYf, uint16_t *dYb, hipStream_t s);
 
+// Packed image of the reset proposer's weights for launch_forward_noise (NULL:
+// none), rewritten where parameters change; packed_net_elems bf16 elements,
+// zeroed once (the entries that no parameter fills stay 0).
+struct PackedNet {
+    uint16_t *image = nullptr;
+    int layers = 0, hidden = 0, d0 = 0, col0 = 0;
+    int64_t w_off[5] = {};
+};
+int64_t packed_net_elems(int layers, int hidden);
+
 // AdamW (decoupled weight decay): for i < n,
 //   m = b1 m + (1 - b1) g,  v = b2 v + (1 - b2) g^2,
 //   p = p (1 - lr wd) - lr (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps),
-// decay applied where decay_mask[i] != 0; pb = bfloat16(p).
+// decay applied where decay_mask[i] != 0; pb = bfloat16(p), and its entry of f.
 hipError_t launch_adamw(int64_t n, float *p, uint16_t *pb, const float *g, float *m, float *v,
                         const uint8_t *decay_mask, float lr, float b1, float b2, float eps,
-                        float wd, int64_t t, hipStream_t s);
+                        float wd, int64_t t, const PackedNet &f, hipStream_t s);
 
 // Actor input rows [N][m + 4] in bfloat16: 1 / (obs - beta) for the m pooled
 // ranges (reciprocal transform, beta device scalar), the 4 other features as
@@ -100,7 +135,8 @@ hipError_t launch_actor_fused(const ActorArgs &a, hipStream_t s);
 size_t actor_fused_lds_bytes(int layers, const int *kpad, const int *npad, int kmax);
 int actor_fused_wmax(int layers, const int *kpad, const int *npad);
 
-// Float to bfloat16 (round to nearest even), n elements.
-hipError_t launch_to_bf16(int64_t n, const float *x, uint16_t *y, hipStream_t s);
+// Float to bfloat16 (round to nearest even), n elements, and their entries of f.
+hipError_t launch_to_bf16(int64_t n, const float *x, uint16_t *y, const PackedNet &f,
+                          hipStream_t s);
 
 }  // namespace navsim

@@ -5,6 +5,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "mlp_internal.hpp"
 #include "philox.hpp"
@@ -178,9 +179,32 @@ __global__ void sq_loss_kernel(int M, int D, const float *Y, const float *T, con
     if (L) L[m] = l;
 }
 
+// Parameter i (bf16 bits v) into the packed image of the weights that
+// forward_noise_kernel reads: fragments of 16 output rows by 32 inputs, the 16
+// bytes of each lane of a wavefront's load in lane order, so that a load is one
+// contiguous kilobyte.  Read from the row-major weights a fragment's 16 lanes
+// per row group lie 512 bytes apart, 64 cache lookups a load instead of 8.
+__device__ __forceinline__ void store_packed(const PackedNet &f, int64_t i, uint16_t v) {
+    const int H = f.hidden;
+    int64_t base = 0;
+    for (int l = 0; l < f.layers; ++l) {
+        const int ni = l == 0 ? f.d0 : H, no = l + 1 < f.layers ? H : 5;
+        const int q = (int)(i - f.w_off[l]);
+        const int ks = l == 0 ? 2 : H / 32;  // k blocks (layer 0: the noise columns, up to 64)
+        if (i >= f.w_off[l] && q < ni * no) {
+            const int n = q / ni, k = q - n * ni - (l == 0 ? f.col0 : 0);
+            if (k >= 0)
+                f.image[base + (((n >> 4) * ks + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (n & 15)) * 8 +
+                        (k & 7)] = v;
+            return;
+        }
+        base += (int64_t)((no + 15) / 16) * ks * 512;
+    }
+}
+
 __global__ void adamw_kernel(int64_t n, float *p, uint16_t *pb, const float *g, float *m, float *v,
                              const uint8_t *decay_mask, float lr, float b1, float b2, float eps,
-                             float wd, float bc1, float bc2) {
+                             float wd, float bc1, float bc2, PackedNet f) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float gi = g[i];
@@ -193,11 +217,14 @@ __global__ void adamw_kernel(int64_t n, float *p, uint16_t *pb, const float *g, 
     pi = pi - lr * ((mi / bc1) / (sqrtf(vi / bc2) + eps));
     p[i] = pi;
     if (pb) pb[i] = to_bf16_bits(pi);
+    if (f.image) store_packed(f, i, to_bf16_bits(pi));
 }
 
-__global__ void to_bf16_kernel(int64_t n, const float *x, uint16_t *y) {
+__global__ void to_bf16_kernel(int64_t n, const float *x, uint16_t *y, PackedNet f) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = to_bf16_bits(x[i]);
+    if (i >= n) return;
+    y[i] = to_bf16_bits(x[i]);
+    if (f.image) store_packed(f, i, to_bf16_bits(x[i]));
 }
 
 // Actor input: x[e][j] = bf16(1 / (obs[e][j] - beta)) for the m pooled
@@ -402,9 +429,216 @@ __global__ __launch_bounds__(kActorThreads) void actor_fused_kernel(ActorArgs a)
     }
 }
 
+// The proposer's network on noise rows, all layers in one launch (hidden width
+// H): request i's draw j is row i per + j.  A workgroup of 8 wavefronts takes
+// 128 rows: it draws their noise (noise_kernel's words), and runs every layer as
+// 16 x 16 x 32 bf16 MFMA tiles with the rows' activations in LDS.  The weights
+// are the A operand, so that a lane receives 4 consecutive columns of one row and
+// writes them to the next layer's input with one 8-byte store.  Each wavefront
+// owns 64 columns and 128 / (8 / (H / 64)) rows; its weights come from their
+// packed image in L2 straight into registers, and each k block's registers are
+// refilled with the next layer's weights as soon as they are used, so the loads
+// run under the products.
+// Same tiles, k order and rounding points as the layer-by-layer GEMMs (bitwise
+// the same outputs), which serve other widths.
+//
+// Bound by the matrix cores and, as long again, the epilogue's VALU work (5
+// instructions per activation) between barriers.  The GEMMs wrote and re-read
+// every activation (512 bytes a row and layer).  131,072 rows of the 16-256-256-
+// 256-5 network (36 GFLOP) in 67 us, 262,144 in 126 us (570 TFLOP/s), a step's
+// 15,700 in 17 us, against 260, 430 and 62 us with the noise kernel and four
+// GEMMs; 64 rows and 4 wavefronts a workgroup: 84, 157 and 20 us; weights from
+// the row-major matrix instead of the packed image: 109, 217 and 28 us.
+constexpr int kFwdThreads = 512;
+constexpr int kFwdRows = kFwdThreads / 4;
+constexpr int kFwdZPitch = 72;  // bf16 per noise row in LDS: up to 64 columns, 16 bytes of padding
+
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// bias + leaky ReLU on a lane's 4 columns, rounded to bf16 (nearest even)
+__device__ __forceinline__ uint2 hidden_bf16(f32x4 v, float4 b, float slope) {
+    v[0] += b.x;
+    v[1] += b.y;
+    v[2] += b.z;
+    v[3] += b.w;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = v[r] > 0.0f ? v[r] : v[r] * slope;
+    return __builtin_bit_cast(uint2, __builtin_convertvector(v, bf16x4));
+}
+
+template <int H>
+__global__ __launch_bounds__(kFwdThreads) void forward_noise_kernel(ForwardNoiseArgs a) {
+    constexpr int KS = H / 32;          // k blocks of a hidden layer
+    constexpr int WN = H / 64;          // wavefronts across the columns
+    constexpr int MT = WN;              // 16-row tiles per wavefront: 64 / (4 / WN) / 16
+    constexpr int LD = H + 8;           // LDS pitch: fragment reads hit every bank once
+    __shared__ __attribute__((aligned(16))) uint16_t s_act[kFwdRows * LD];
+    __shared__ __attribute__((aligned(16))) uint16_t s_z[kFwdRows * kFwdZPitch];
+    __shared__ int s_row[kFwdRows];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (a.clear && blockIdx.x == 0 && tid == 0) *a.clear = 0;
+    const int n = a.n_dev ? min(a.n, *a.n_dev) : a.n;
+    const int rows = n * a.per;  // at most 2^24
+    const int row0 = (int)blockIdx.x * kFwdRows;
+    if (row0 >= rows) return;
+    const int fr = lane & 15, fk = (lane >> 4) * 8;  // fragment row and first k
+    const int n0 = (wave % WN) * 64, m0 = (wave / WN) * (MT * 16);
+    // packed weights: fragment (16-row tile, k block) at ((tile) ks + k) 512
+    const uint16_t *W1 = a.packed + (n0 >> 4) * 2 * 512 + lane * 8;
+    const uint16_t *Wh = a.packed + WN * 4 * 2 * 512 + (n0 >> 4) * KS * 512 + lane * 8;
+    bf16x8 w[4][KS];
+    auto load_hidden = [&](const uint16_t *W, int i, int k) {
+        w[i][k] = *reinterpret_cast<const bf16x8 *>(W + (i * KS + k) * 512);
+    };
+    // noise: 4 threads a row, 4 columns per draw
+    {
+        const int r = tid >> 2;
+        const int row = row0 + r;
+        const bool in = row < rows;
+        const int i = in ? (int)((uint32_t)row / (uint32_t)a.per) : 0;
+        const int j = in ? row - i * a.per : 0;
+        const uint32_t c0 = a.c0 ? a.c0[i] : (uint32_t)i, c1 = a.c1 ? a.c1[i] : a.c1_const;
+        if ((tid & 3) == 0) {
+            const int m = a.map[i], b = a.bin[i];
+            s_row[r] =
+                (m >= 0 && m < a.num_maps && b >= 0 && b < a.nbins) ? m * a.nbins + b : 0;
+        }
+        // the weight loads go out before the draws, behind the loads that these need
+        if (a.layers > 2)
+#pragma unroll
+            for (int k = 0; k < KS; ++k)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) load_hidden(Wh, t, k);
+        const int cols = (a.nz + 31) & ~31;
+        for (int q = tid & 3; 4 * q < cols; q += 4) {
+            uint32_t c[4] = {c0, c1, ((uint32_t)j << 8) | (uint32_t)q, a.stream};
+            philox4x32_10(c, a.key0, a.key1);
+            uint16_t v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double u = ((double)c[t] + 0.5) / 4294967296.0;
+                v[t] = in && 4 * q + t < a.nz ? to_bf16_bits((float)(2.0 * u - 1.0)) : (uint16_t)0;
+            }
+            *reinterpret_cast<uint2 *>(&s_z[r * kFwdZPitch + 4 * q]) =
+                make_uint2((uint32_t)v[0] | ((uint32_t)v[1] << 16),
+                           (uint32_t)v[2] | ((uint32_t)v[3] << 16));
+            if (a.z && in)
+                for (int t = 0; t < 4; ++t)
+                    if (4 * q + t < a.nz) a.z[(int64_t)row * a.nz + 4 * q + t] = v[t];
+        }
+    }
+    f32x4 acc[4][MT];
+    // first layer: the noise columns; the rest of its input is the (map, bin) row
+    // of the constant table, added like a bias
+    {
+        bf16x8 w1[2][4];
+#pragma unroll
+        for (int kz = 0; kz < 2; ++kz)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                w1[kz][i] = *reinterpret_cast<const bf16x8 *>(W1 + (i * 2 + kz) * 512);
+        __syncthreads();  // noise and table rows in LDS
+        // a tile's table entries are loaded while the tile before it is computed
+        float4 cb[2][4];
+        auto load_table = [&](int j, float4(&c)[4]) {
+            const float *ct =
+                a.ct + (int64_t)s_row[m0 + 16 * j + fr] * H + n0 + (lane >> 4) * 4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] = *reinterpret_cast<const float4 *>(ct + 16 * i);
+        };
+        load_table(0, cb[0]);
+#pragma unroll
+        for (int j = 0; j < MT; ++j) {
+            if (j + 1 < MT) load_table(j + 1, cb[(j + 1) & 1]);
+            const int m = m0 + 16 * j + fr;
+            const bf16x8 z0 = *reinterpret_cast<const bf16x8 *>(&s_z[m * kFwdZPitch + fk]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    w1[0][i], z0, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+            if (a.nz > 32) {
+                const bf16x8 z1 = *reinterpret_cast<const bf16x8 *>(&s_z[m * kFwdZPitch + 32 + fk]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    acc[i][j] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[1][i], z1, acc[i][j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<uint2 *>(&s_act[m * LD + n0 + 16 * i + (lane >> 4) * 4]) =
+                    hidden_bf16(acc[i][j], cb[j & 1][i], a.slope);
+        }
+    }
+    __syncthreads();
+    auto hidden = [&](int l, auto more) {  // more: another hidden layer follows
+        const uint16_t *W = Wh + (int64_t)l * H * H;  // layer l + 1's
+        float4 bias[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            bias[i] = *reinterpret_cast<const float4 *>(a.p + a.b_off[l] + n0 + 16 * i +
+                                                        (lane >> 4) * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            bf16x8 x[MT];
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+                x[j] = *reinterpret_cast<const bf16x8 *>(&s_act[(m0 + 16 * j + fr) * LD + 32 * k + fk]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < MT; ++j)
+                    acc[i][j] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][k], x[j], acc[i][j], 0, 0, 0);
+            if constexpr (decltype(more)::value)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) load_hidden(W, i, k);
+        }
+        __syncthreads();  // every wavefront has read the layer's inputs
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<uint2 *>(
+                    &s_act[(m0 + 16 * j + fr) * LD + n0 + 16 * i + (lane >> 4) * 4]) =
+                    hidden_bf16(acc[i][j], bias[i], a.slope);
+        __syncthreads();
+    };
+    for (int l = 1; l + 2 < a.layers; ++l) hidden(l, std::true_type{});
+    if (a.layers > 2) hidden(a.layers - 2, std::false_type{});
+    // output layer (5 columns): 16 rows per wavefront
+    {
+        const int l = a.layers - 1, m = 16 * wave + fr;
+        const uint16_t *W =
+            a.packed + WN * 4 * 2 * 512 + (int64_t)(a.layers - 2) * H * H + lane * 8;
+        f32x4 o = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const bf16x8 wk = *reinterpret_cast<const bf16x8 *>(W + 512 * k);
+            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(&s_act[m * LD + 32 * k + fk]);
+            o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wk, x, o, 0, 0, 0);
+        }
+        const int row = row0 + m;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = (lane >> 4) * 4 + r;
+            if (c < 5 && row < rows) a.y[(int64_t)row * 5 + c] = o[r] + a.p[a.b_off[l] + c];
+        }
+    }
+}
+
 unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 }  // namespace
+
+int64_t packed_net_elems(int layers, int hidden) {
+    return (int64_t)(hidden / 16) * 2 * 512 + (int64_t)(layers - 2) * hidden * hidden +
+           (int64_t)(hidden / 32) * 512;
+}
 
 size_t actor_fused_lds_bytes(int layers, const int *kpad, const int *npad, int kmax) {
     return ((size_t)32 * (kmax + 8) + (size_t)actor_fused_wmax(layers, kpad, npad)) *
@@ -423,6 +657,21 @@ hipError_t launch_actor_fused(const ActorArgs &a, hipStream_t s) {
     const size_t lds = actor_fused_lds_bytes(a.layers, a.kpad, a.npad, a.kmax);
     hipLaunchKernelGGL(actor_fused_kernel, dim3((unsigned)((a.N + 15) / 16)), dim3(kActorThreads), lds,
                        s, a);
+    return hipGetLastError();
+}
+
+bool forward_noise_supported(int hidden) { return hidden == 128 || hidden == 256; }
+
+hipError_t launch_forward_noise(const ForwardNoiseArgs &a, int hidden, hipStream_t s) {
+    const int64_t rows = (int64_t)a.n * a.per;
+    if (rows <= 0) return hipSuccess;
+    const dim3 grid((unsigned)((rows + kFwdRows - 1) / kFwdRows));
+    if (hidden == 256)
+        hipLaunchKernelGGL(forward_noise_kernel<256>, grid, dim3(kFwdThreads), 0, s, a);
+    else if (hidden == 128)
+        hipLaunchKernelGGL(forward_noise_kernel<128>, grid, dim3(kFwdThreads), 0, s, a);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -471,12 +720,12 @@ hipError_t launch_sq_loss(int M, int D, const float *Y, const float *T, const fl
 
 hipError_t launch_adamw(int64_t n, float *p, uint16_t *pb, const float *g, float *m, float *v,
                         const uint8_t *decay_mask, float lr, float b1, float b2, float eps,
-                        float wd, int64_t t, hipStream_t s) {
+                        float wd, int64_t t, const PackedNet &f, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const float bc1 = (float)(1.0 - pow((double)b1, (double)t));
     const float bc2 = (float)(1.0 - pow((double)b2, (double)t));
     hipLaunchKernelGGL(adamw_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, p, pb, g, m, v,
-                       decay_mask, lr, b1, b2, eps, wd, bc1, bc2);
+                       decay_mask, lr, b1, b2, eps, wd, bc1, bc2, f);
     return hipGetLastError();
 }
 
@@ -497,9 +746,10 @@ hipError_t launch_actor_noise(int N, float *act, float std, const uint32_t *step
     return hipGetLastError();
 }
 
-hipError_t launch_to_bf16(int64_t n, const float *x, uint16_t *y, hipStream_t s) {
+hipError_t launch_to_bf16(int64_t n, const float *x, uint16_t *y, const PackedNet &f,
+                          hipStream_t s) {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, x, y);
+    hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, x, y, f);
     return hipGetLastError();
 }
 

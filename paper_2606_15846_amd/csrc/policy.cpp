@@ -228,7 +228,7 @@ navsim_status navsim_policy_set_params(navsim_policy_t q, const float *host, int
     DeviceGuard dg(q->device);
     NS_HIP(hipDeviceSynchronize());
     NS_HIP(hipMemcpy(q->p, host, (size_t)count * 4, hipMemcpyHostToDevice));
-    NS_HIP(launch_to_bf16(count, q->p, q->pb, nullptr));
+    NS_HIP(launch_to_bf16(count, q->p, q->pb, PackedNet{}, nullptr));
     if (q->fused) {
         // padded images for the one-launch actor (same bf16 rounding as the
         // layer-by-layer path: nearest even)

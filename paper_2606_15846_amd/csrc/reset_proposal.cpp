@@ -84,6 +84,7 @@ struct navsim_rp_s {
     // parameters and optimiser
     float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
     uint16_t *pb = nullptr;
+    PackedNet pf;                  // the weights again, packed for the one-launch forward pass
     uint8_t *decay = nullptr;
     float *wloss = nullptr;        // loss weights [5]
     int64_t adam_t = 0;
@@ -128,7 +129,7 @@ navsim_status upload_vec(T **dst, const std::vector<T> &src) {
 
 void free_rp(navsim_rp_s *r) {
     void *ptrs[] = {r->maps, r->bits, r->packed, r->free_cells, r->hop_bin, r->bin_hi, r->pool,
-                    r->pool_rows, r->p, r->g, r->m, r->v, r->pb, r->decay, r->wloss};
+                    r->pool_rows, r->p, r->g, r->m, r->v, r->pb, r->pf.image, r->decay, r->wloss};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     DevBuf *bufs[] = {&r->ctable, &r->colsum, &r->x, &r->hid[0], &r->hid[1], &r->hid[2],
@@ -229,6 +230,59 @@ navsim_status forward_noise(navsim_rp_s *r, int R, const uint16_t *Z, const int3
     return NAVSIM_OK;
 }
 
+// Where the noise, its table rows and two hidden activations of a call's draws
+// go (the widths that forward_noise_kernel serves need none of them, but z when
+// the noise is read again).
+struct NoiseWork {
+    uint16_t *z = nullptr;
+    int32_t *row_idx = nullptr;
+    uint16_t *hc0 = nullptr, *hc1 = nullptr;
+};
+
+bool one_launch(const navsim_rp_s *r) { return forward_noise_supported(hidden_width(r)); }
+
+// Network outputs y [n per][5] of the noise draws that na describes (its z and
+// row_idx come from w).
+navsim_status run_draws(navsim_rp_s *r, NoiseArgs na, const NoiseWork &w, const float *ct,
+                        float *y, hipStream_t s) {
+    na.nz = r->cfg.noise_dim;
+    na.nbins = r->cfg.num_bins;
+    na.num_maps = r->num_maps;
+    na.z = w.z;
+    na.row_idx = w.row_idx;
+    if (!one_launch(r)) {
+        RP_HIP(launch_noise(na, r->rp.key0, r->rp.key1, s));
+        return forward_noise(r, na.n * na.per, w.z, w.row_idx, y, ct, w.hc0, w.hc1, s, na.n_dev,
+                             na.per);
+    }
+    ForwardNoiseArgs a;
+    a.n = na.n;
+    a.per = na.per;
+    a.nz = na.nz;
+    a.nbins = na.nbins;
+    a.num_maps = na.num_maps;
+    a.layers = r->L;
+    a.c0 = na.c0;
+    a.c1 = na.c1;
+    a.c1_const = na.c1_const;
+    a.stream = na.stream;
+    a.key0 = r->rp.key0;
+    a.key1 = r->rp.key1;
+    a.map = na.map;
+    a.bin = na.bin;
+    a.packed = r->pf.image;
+    a.p = r->p;
+    a.ct = ct;
+    for (int l = 0; l < r->L; ++l) a.b_off[l] = r->b_off[l];
+    a.slope = r->cfg.leaky_slope;
+    a.y = y;
+    a.z = w.z;
+    a.n_dev = na.n_dev;
+    a.clear = na.clear;
+    RP_HIP(launch_forward_noise(a, hidden_width(r), s));
+    return NAVSIM_OK;
+}
+
 // Forward on explicit inputs X [n][d0], keeping every layer's bf16 output in
 // r->hid[] (for the backward pass) and the float outputs in Y [n][5].
 navsim_status forward_full(navsim_rp_s *r, int n, const uint16_t *X, float *Y, hipStream_t s) {
@@ -316,7 +370,7 @@ navsim_status adamw_step(navsim_rp_s *r, const float *grad, float lr, float wd, 
     r->adam_t += 1;
     r->param_version += 1;
     RP_HIP(launch_adamw(r->nparams, r->p, r->pb, grad, r->m, r->v, r->decay, lr, 0.9f, 0.999f,
-                        1e-8f, wd, r->adam_t, s));
+                        1e-8f, wd, r->adam_t, r->pf, s));
     return NAVSIM_OK;
 }
 
@@ -339,11 +393,8 @@ navsim_status check_propose(const navsim_rp_s *r, int32_t n, const int32_t *map,
 // inputs, their table rows, network outputs and two hidden activations; and the
 // tail launch's pending list (tail_bytes, NULL: every round in one launch).
 struct ProposeWork {
-    float *ct = nullptr;
-    uint16_t *z = nullptr;
-    int32_t *row_idx = nullptr;
-    float *y = nullptr;
-    uint16_t *hc0 = nullptr, *hc1 = nullptr;
+    float *ct = nullptr, *y = nullptr;
+    NoiseWork nw;
     uint8_t *pend = nullptr;
 };
 
@@ -391,25 +442,16 @@ navsim_status propose_run(navsim_rp_s *r, int32_t n, const int32_t *map, const i
         const int64_t R = (int64_t)n * proposals;
         navsim_status st = refresh_ctable(r, w.ct, s);
         if (st != NAVSIM_OK) return st;
-        NoiseArgs na;
+        NoiseArgs na{};
         na.n = n;
         na.per = proposals;
-        na.nz = r->cfg.noise_dim;
-        na.nbins = r->cfg.num_bins;
-        na.num_maps = r->num_maps;
         na.c0 = env;
         na.c1 = episode;
-        na.c1_const = 0u;
         na.stream = 8u;
         na.map = map;
         na.bin = bin;
-        na.z = w.z;
-        na.row_idx = w.row_idx;
         na.clear = (int32_t *)w.pend;
-        RP_HIP(launch_noise(na, r->rp.key0, r->rp.key1, s));
-        if ((st = forward_noise(r, (int)R, na.z, na.row_idx, w.y, w.ct, w.hc0, w.hc1, s)) !=
-            NAVSIM_OK)
-            return st;
+        if ((st = run_draws(r, na, w.nw, w.ct, w.y, s)) != NAVSIM_OK) return st;
         y = w.y;
         if (y_out) RP_HIP(hipMemcpyAsync(y_out, y, (size_t)R * 5 * 4, hipMemcpyDeviceToDevice, s));
     }
@@ -471,24 +513,16 @@ navsim_status rp_hook_run(void *ctx, hipStream_t s) {
             if ((st = refresh_ctable(r, A.ct, s)) != NAVSIM_OK) return st;
             A.ct_version = r->param_version;
         }
-        NoiseArgs na;
+        NoiseArgs na{};
         na.n = A.cap;
         na.per = A.props;
-        na.nz = r->cfg.noise_dim;
-        na.nbins = r->cfg.num_bins;
-        na.num_maps = r->num_maps;
         na.c0 = A.r_env;
         na.c1 = A.r_ep;
-        na.c1_const = 0u;
         na.stream = 8u;
         na.map = A.r_map;
         na.bin = A.r_bin;
-        na.z = A.z;
-        na.row_idx = A.ridx;
         na.n_dev = A.n_dev;
-        RP_HIP(launch_noise(na, r->rp.key0, r->rp.key1, s));
-        if ((st = forward_noise(r, A.cap * A.props, A.z, A.ridx, A.y, A.ct, A.hc0, A.hc1, s,
-                                A.n_dev, A.props)) != NAVSIM_OK)
+        if ((st = run_draws(r, na, NoiseWork{A.z, A.ridx, A.hc0, A.hc1}, A.ct, A.y, s)) != NAVSIM_OK)
             return st;
         y = A.y;
     }
@@ -709,7 +743,19 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
         hipMalloc((void **)&r->pool_rows,
                   (size_t)M * c.num_bins * (kPoolCells + c.num_bins) * 2) != hipSuccess)
         return fail_out(fail(NAVSIM_E_OOM, "hipMalloc of the network failed"));
-    if (launch_to_bf16(off, r->p, r->pb, nullptr) != hipSuccess ||
+    if (one_launch(r)) {
+        r->pf.layers = r->L;
+        r->pf.hidden = c.hidden;
+        r->pf.d0 = r->d0;
+        r->pf.col0 = kPoolCells + c.num_bins;
+        for (int l = 0; l < r->L; ++l) r->pf.w_off[l] = r->w_off[l];
+        const size_t bytes = (size_t)packed_net_elems(r->L, c.hidden) * 2;
+        if (hipMalloc((void **)&r->pf.image, bytes) != hipSuccess)
+            return fail_out(fail(NAVSIM_E_OOM, "hipMalloc of the network failed"));
+        if (hipMemset(r->pf.image, 0, bytes) != hipSuccess)
+            return fail_out(fail(NAVSIM_E_HIP, "hipMemset of the network failed"));
+    }
+    if (launch_to_bf16(off, r->p, r->pb, r->pf, nullptr) != hipSuccess ||
         launch_pool_rows(M, c.num_bins, r->pool, r->pool_rows, nullptr) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess)
         return fail_out(fail(NAVSIM_E_HIP, "initialising the proposer failed"));
@@ -776,14 +822,18 @@ navsim_status navsim_rp_train(navsim_rp_t r, int32_t num_pairs, const int32_t *p
     RP_BUF(r->target, (size_t)batch * 5 * 4);
     RP_BUF(r->chosen, (size_t)batch * 4);
     RP_BUF(r->zc, (size_t)R * nz * 2);
-    RP_BUF(r->ridx, (size_t)R * 4);
     RP_BUF(r->yc, (size_t)R * 5 * 4);
     RP_BUF(r->x, (size_t)batch * r->d0 * 2);
     RP_BUF(r->y, (size_t)batch * 5 * 4);
     RP_BUF(r->lrows, (size_t)batch * 4);
     RP_BUF(r->ctable, ctable_bytes(r));
-    RP_BUF(r->hc[0], (size_t)R * Hd * 2);
-    RP_BUF(r->hc[1], (size_t)R * Hd * 2);
+    if (!one_launch(r)) {
+        RP_BUF(r->ridx, (size_t)R * 4);
+        RP_BUF(r->hc[0], (size_t)R * Hd * 2);
+        RP_BUF(r->hc[1], (size_t)R * Hd * 2);
+    }
+    const NoiseWork nw{r->zc.as<uint16_t>(), r->ridx.as<int32_t>(), r->hc[0].as<uint16_t>(),
+                       r->hc[1].as<uint16_t>()};
     for (int t = 0; t < steps; ++t) {
         const uint32_t step = r->train_step++;
         navsim_status st = refresh_ctable(r, r->ctable.as<float>(), s);
@@ -803,23 +853,14 @@ navsim_status navsim_rp_train(navsim_rp_t r, int32_t num_pairs, const int32_t *p
         ba.bin = r->bbin.as<int32_t>();
         ba.target = r->target.as<float>();
         RP_HIP(launch_batch(ba, r->rp.key0, r->rp.key1, s));
-        NoiseArgs na;
+        NoiseArgs na{};
         na.n = batch;
         na.per = samples;
-        na.nz = nz;
-        na.nbins = nb;
-        na.num_maps = r->num_maps;
-        na.c0 = nullptr;
-        na.c1 = nullptr;
         na.c1_const = step;
         na.stream = 9u;
         na.map = ba.map;
         na.bin = ba.bin;
-        na.z = r->zc.as<uint16_t>();
-        na.row_idx = r->ridx.as<int32_t>();
-        RP_HIP(launch_noise(na, r->rp.key0, r->rp.key1, s));
-        if ((st = forward_noise(r, R, na.z, na.row_idx, r->yc.as<float>(), r->ctable.as<float>(),
-                                r->hc[0].as<uint16_t>(), r->hc[1].as<uint16_t>(), s)) != NAVSIM_OK)
+        if ((st = run_draws(r, na, nw, r->ctable.as<float>(), r->yc.as<float>(), s)) != NAVSIM_OK)
             return st;
         SelectArgs sa;
         sa.batch = batch;
@@ -829,7 +870,7 @@ navsim_status navsim_rp_train(navsim_rp_t r, int32_t num_pairs, const int32_t *p
         sa.y = r->yc.as<float>();
         sa.target = ba.target;
         sa.w = r->wloss;
-        sa.z = na.z;
+        sa.z = nw.z;
         sa.map = ba.map;
         sa.bin = ba.bin;
         sa.pool = r->pool;
@@ -863,13 +904,17 @@ navsim_status navsim_rp_propose(navsim_rp_t r, int32_t n, const int32_t *map, co
         const int64_t R = (int64_t)n * proposals;
         const int Hd = hidden_width(r);
         RP_BUF(r->ctable, ctable_bytes(r));
-        RP_BUF(r->zp, (size_t)R * r->cfg.noise_dim * 2);
-        RP_BUF(r->rp_idx, (size_t)R * 4);
         RP_BUF(r->yp, (size_t)R * 5 * 4);
-        RP_BUF(r->hc[0], (size_t)R * Hd * 2);
-        RP_BUF(r->hc[1], (size_t)R * Hd * 2);
-        w = ProposeWork{r->ctable.as<float>(), r->zp.as<uint16_t>(), r->rp_idx.as<int32_t>(),
-                        r->yp.as<float>(), r->hc[0].as<uint16_t>(), r->hc[1].as<uint16_t>()};
+        w.ct = r->ctable.as<float>();
+        w.y = r->yp.as<float>();
+        if (!one_launch(r)) {
+            RP_BUF(r->zp, (size_t)R * r->cfg.noise_dim * 2);
+            RP_BUF(r->rp_idx, (size_t)R * 4);
+            RP_BUF(r->hc[0], (size_t)R * Hd * 2);
+            RP_BUF(r->hc[1], (size_t)R * Hd * 2);
+            w.nw = NoiseWork{r->zp.as<uint16_t>(), r->rp_idx.as<int32_t>(),
+                             r->hc[0].as<uint16_t>(), r->hc[1].as<uint16_t>()};
+        }
     }
     if (const size_t tb = tail_bytes(n, proposals, max_tries)) {
         RP_BUF(r->pend, tb);
@@ -913,11 +958,12 @@ navsim_status navsim_rp_propose_noalloc(navsim_rp_t r, int32_t n, const int32_t 
             return (void *)q;
         };
         w.ct = (float *)take(ctable_bytes(r));
-        w.z = (uint16_t *)take((size_t)R * r->cfg.noise_dim * 2);
-        w.row_idx = (int32_t *)take((size_t)R * 4);
+        w.nw.z = (uint16_t *)take((size_t)R * r->cfg.noise_dim * 2);
+        w.nw.row_idx = (int32_t *)take((size_t)R * 4);
         w.y = (float *)take((size_t)R * 5 * 4);
-        w.hc0 = (uint16_t *)take((size_t)R * Hd * 2);
-        w.hc1 = (uint16_t *)take((size_t)R * Hd * 2);
+        w.nw.hc0 = (uint16_t *)take((size_t)R * Hd * 2);
+        w.nw.hc1 = (uint16_t *)take((size_t)R * Hd * 2);
+        if (one_launch(r)) w.nw = NoiseWork{};  // not used; the limit stays the same for every width
     }
     return propose_run(r, n, map, bin, env, episode, proposals, max_tries, pose, hops, source,
                        checks, y_out, w, (hipStream_t)stream);
@@ -991,7 +1037,7 @@ navsim_status navsim_rp_set_params(navsim_rp_t r, const float *host, int64_t cou
     DeviceGuard dg(r->device);
     NS_HIP(hipDeviceSynchronize());
     NS_HIP(hipMemcpy(r->p, host, (size_t)count * 4, hipMemcpyHostToDevice));
-    NS_HIP(launch_to_bf16(count, r->p, r->pb, nullptr));
+    NS_HIP(launch_to_bf16(count, r->p, r->pb, r->pf, nullptr));
     NS_HIP(hipDeviceSynchronize());
     r->param_version += 1;
     return NAVSIM_OK;
@@ -1023,11 +1069,12 @@ navsim_status navsim_rp_attach(navsim_rp_t r, const int32_t *bin, int32_t propos
     if (!(A.on && A.cap == max_per_step && A.props == proposals && A.tail_rounds >= tail_rounds)) {
         detach_rp(r);
         const size_t R = (size_t)max_per_step * (size_t)proposals, Hd = (size_t)r->cfg.hidden;
+        const size_t RG = one_launch(r) ? 0 : R;  // rows of the layer-by-layer path's buffers
         const size_t parts[] = {(size_t)N * 4, (size_t)N * 4, (size_t)N * 4, (size_t)N,
                                 (size_t)N * 20, (size_t)max_per_step * 4, (size_t)max_per_step * 4,
                                 (size_t)max_per_step * 4, (size_t)max_per_step * 4, 256, 64,
                                 proposals ? ctable_bytes(r) : 0, R * 20,
-                                R * (size_t)r->cfg.noise_dim * 2, R * Hd * 2, R * Hd * 2, R * 4,
+                                RG * (size_t)r->cfg.noise_dim * 2, RG * Hd * 2, RG * Hd * 2, RG * 4,
                                 (size_t)max_per_step * 4, (size_t)max_per_step * 4,
                                 (size_t)max_per_step * (size_t)tail_rounds * 16};
         constexpr int kParts = (int)(sizeof parts / sizeof parts[0]);
@@ -1060,7 +1107,7 @@ navsim_status navsim_rp_attach(navsim_rp_t r, const int32_t *bin, int32_t propos
         A.stats = (unsigned long long *)ptrs[10];
         A.ct = (float *)ptrs[11];
         A.y = (float *)ptrs[12];
-        A.z = (uint16_t *)ptrs[13];
+        A.z = RG ? (uint16_t *)ptrs[13] : nullptr;
         A.hc0 = (uint16_t *)ptrs[14];
         A.hc1 = (uint16_t *)ptrs[15];
         A.ridx = (int32_t *)ptrs[16];

@@ -494,3 +494,47 @@ def test_pending_rounds_agree_with_single_requests(n, proposals, tries):
         assert np.array_equal(a, np.concatenate([p[k].cpu().numpy() for p in parts])), k
     rp.close()
     sim.close()
+
+
+# hidden widths of the one-launch forward pass (128, 256) and of the layer-by-layer
+# one (64), noise of one and of two 32-column blocks, rows on both sides of a tile
+@pytest.mark.parametrize("hidden,layers,nz,nb,n,per",
+                         [(256, 3, 16, 8, 37, 7), (256, 1, 1, 8, 1, 1), (256, 2, 33, 5, 8, 16),
+                          (256, 4, 64, 16, 43, 3), (128, 3, 16, 8, 43, 3), (128, 1, 32, 3, 9, 15),
+                          (64, 2, 16, 8, 13, 10)])
+def test_draw_outputs_match_oracle(hidden, layers, nz, nb, n, per):
+    """The network's outputs for a proposal call's noise draws against the
+    oracle's network on the same input rows; before and after a training step
+    (the same rounding points and tolerances as the explicit-input forward)."""
+    say(f"draws: hidden {layers} x {hidden}, {nz} noise inputs, {nb} bins, {n} x {per} rows")
+    sim, rp0, ref, reach, maps = setup(num_envs=8)
+    rp0.close()
+    rp = ResetProposer(sim, hidden=hidden, hidden_layers=layers, noise_dim=nz, num_bins=nb, seed=9)
+    prm, rng = rp.get_params(), np.random.default_rng(17)
+    for l, (wo, bo) in enumerate(rp.offsets):
+        prm[bo:bo + rp.dims[l + 1]] = rng.uniform(-0.2, 0.2, rp.dims[l + 1])
+    rp.set_params(prm)
+    mp, bins = rng.integers(0, 4, n), rng.integers(0, nb, n)
+    env, ep = rng.integers(0, 1 << 32, n), rng.integers(0, 1 << 32, n)
+    x = np.zeros((n, per, rp.d0))
+    for i in range(n):
+        x[i, :, :1024] = G.pool32(maps[mp[i]])
+        x[i, :, 1024 + bins[i]] = 1.0
+        for j in range(per):
+            for q in range((nz + 3) // 4):
+                w = oracle.philox4x32_10([int(env[i]), int(ep[i]), (j << 8) | q, 8], [9, 0])
+                for t in range(min(4, nz - 4 * q)):
+                    x[i, j, 1024 + nb + 4 * q + t] = 2.0 * ((w[t] + 0.5) / 2.0 ** 32) - 1.0
+    x = OM.from_bf16_bits(OM.bf16_bits(x.reshape(n * per, rp.d0)))
+    for step in range(2):
+        if step:
+            one = [torch.tensor([v], dtype=torch.int32, device=sim.device) for v in (1, 0, 5, 9)]
+            rp.train(dict(zip(("map", "bin", "start", "goal"), one)), 1, batch=65, samples=2)
+        y = rp.propose(mp, bins, env, ep, proposals=per, max_tries=1, want_y=True)["y"]
+        torch.cuda.synchronize()
+        yo, _ = _oracle_net(rp).forward(x, emulate=True)
+        d = np.abs(y.cpu().numpy().reshape(n * per, 5) - yo)
+        assert d.max() <= 2e-3 * (1.0 + np.abs(yo).max())
+        assert np.median(d) <= 1e-5 * (1.0 + np.abs(yo).max())
+    rp.close()
+    sim.close()
