@@ -9,8 +9,9 @@ namespace navsim {
 // C[m, n] = sum_k A(m, k) B(n, k), bfloat16 operands, float accumulation.
 // A(m, k) = A[m lda + k] when a_kmajor, else A[k lda + m]; B likewise.
 // Epilogue: + bias[n] (optional) + bias_rows[row_idx[m] ldbr + n] (optional),
-// activation (0 none, 1 leaky ReLU with `slope`, 2 tanh), then stored as float to Cf
-// and/or as bfloat16 (round to nearest even) to Cb.
+// activation (0 none, 1 leaky ReLU with `slope`, 2 tanh, 3 the derivative of leaky
+// ReLU: times slope where the layer's bfloat16 output H[m, n] is not positive), then
+// stored as float to Cf and/or as bfloat16 (round to nearest even) to Cb.
 struct GemmArgs {
     int M = 0, N = 0, K = 0;
     const uint16_t *A = nullptr;
@@ -25,6 +26,8 @@ struct GemmArgs {
     int64_t ldbr = 0;
     int act = 0;
     float slope = 0.0f;
+    const uint16_t *H = nullptr;
+    int64_t ldh = 0;
     float *Cf = nullptr;
     int64_t ldcf = 0;
     uint16_t *Cb = nullptr;
@@ -62,17 +65,23 @@ struct ForwardNoiseArgs {
 bool forward_noise_supported(int hidden);
 hipError_t launch_forward_noise(const ForwardNoiseArgs &a, int hidden, hipStream_t s);
 
-// dZ = dH * act'(H) for leaky ReLU (H is the layer's bfloat16 output, whose
-// sign is that of its input); writes float dZf and bfloat16 dZb, [M, N] rows
-// of stride ld.  act 0: dZ = dH.
-hipError_t launch_act_backward(int M, int N, const float *dH, const uint16_t *H, int act,
-                               float slope, float *dZf, uint16_t *dZb, hipStream_t s);
-
 // out[n] = sum over m of X[m, n] (float, [M, N] rows), in a fixed order:
-// chunks of 32 rows in order, then the chunk sums in order.  `partial`
-// holds ceil(M / 32) * N floats.
-hipError_t launch_col_sum(int M, int N, const float *X, float *partial, float *out,
-                          hipStream_t s);
+// chunks of 32 rows in order, then the chunk sums in order.
+struct ColSum {
+    int M = 0, N = 0;
+    const float *X = nullptr;
+    float *out = nullptr;
+};
+
+// A network's weight gradients (products with both operands transposed, not
+// a_kmajor and not b_kmajor) and column sums in one launch.
+constexpr int kGradientMax = 6;
+struct GradientArgs {
+    int gemms = 0, sums = 0;
+    GemmArgs gemm[kGradientMax];
+    ColSum sum[kGradientMax];
+};
+hipError_t launch_gradient(const GradientArgs &a, hipStream_t s);
 
 // Weighted squared error of outputs Y [M, D] to targets T [M, D]: row loss
 // L[m] = sum_d w[d] (Y - T)^2 and dY = 2 w (Y - T) / M (float and bfloat16).

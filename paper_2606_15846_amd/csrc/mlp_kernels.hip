@@ -20,6 +20,7 @@ constexpr int kBM = 64, kBN = 64, kBK = 32;
 constexpr int kLdsK = kBK + 8;  // padded row (80 bytes) of a staged tile
 constexpr int kGemmThreads = 256;
 constexpr int kColChunk = 32;  // rows per partial column sum
+constexpr int kColWidth = 32;  // columns per workgroup of a column sum
 
 __device__ __forceinline__ uint16_t to_bf16_bits(float f) {
     uint32_t u = __float_as_uint(f);
@@ -69,6 +70,17 @@ __device__ __forceinline__ void stage_tile(uint16_t (*T)[kLdsK], const uint16_t 
 #pragma unroll
         for (int j = 0; j < 8; ++j) T[rr + j][kr] = v[j];
     }
+}
+
+// Bias, activation (or the derivative of one), stores of element (m, n).
+__device__ __forceinline__ void gemm_store(const GemmArgs &g, int m, int n, float v) {
+    if (g.bias) v += g.bias[n];
+    if (g.bias_rows) v += g.bias_rows[(int64_t)g.row_idx[m] * g.ldbr + n];
+    if (g.act == 1 && !(v > 0.0f)) v *= g.slope;
+    if (g.act == 2) v = tanhf(v);
+    if (g.act == 3 && !(from_bf16_bits(g.H[(int64_t)m * g.ldh + n]) > 0.0f)) v *= g.slope;
+    if (g.Cf) g.Cf[(int64_t)m * g.ldcf + n] = v;
+    if (g.Cb) g.Cb[(int64_t)m * g.ldcb + n] = to_bf16_bits(v);
 }
 
 // One workgroup computes a 64 x 64 block of C; each of its four wavefronts a
@@ -125,43 +137,205 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(GemmArgs g) {
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + wm + 16 * i + (lane >> 4) * 4 + r;
                 if (m >= M) continue;
-                float v = acc[i][j][r];
-                if (g.bias) v += g.bias[n];
-                if (g.bias_rows) v += g.bias_rows[(int64_t)g.row_idx[m] * g.ldbr + n];
-                if (g.act == 1 && !(v > 0.0f)) v *= g.slope;
-                if (g.act == 2) v = tanhf(v);
-                if (g.Cf) g.Cf[(int64_t)m * g.ldcf + n] = v;
-                if (g.Cb) g.Cb[(int64_t)m * g.ldcb + n] = to_bf16_bits(v);
+                gemm_store(g, m, n, acc[i][j][r]);
             }
         }
 }
 
-__global__ void act_backward_kernel(int64_t n, int N, const float *dH, const uint16_t *H, int act,
-                                    float slope, float *dZf, uint16_t *dZb) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float d = dH[i];
-    if (act == 1 && !(from_bf16_bits(H[i]) > 0.0f)) d *= slope;
-    if (dZf) dZf[i] = d;
-    if (dZb) dZb[i] = to_bf16_bits(d);
+// The same product where the 64 x 64 blocks leave most of the chip idle (a
+// training batch: 16 to 68 of them, each a chain of ceil(K / 32) trips to memory
+// and back, about a microsecond a trip): a 32 x 32 block per workgroup, one
+// 16 x 16 tile per wavefront, and 128 k's a trip, the loads of the next trips in
+// flight.  A transposed operand is turned in
+// registers, 4 k's by 8 rows per thread, on its way to LDS.  Same tiles and k
+// order, so bitwise the same sums.  A batch of 1,024 on the 1048-256-256-256-5
+// network, us a product: first layer 38 -> 13, hidden layers 9 -> 5.6, weight
+// gradients 32 -> 13, the table of 512 (map, bin) rows 38 -> 13.  Bound by the
+// trips to memory that are left and by the launches (about 5 us each).
+constexpr int kSB = 32, kSK = 128;
+constexpr int kSAhead = 2;  // trips in flight (even: they alternate between two LDS buffers)
+constexpr int kSLds = kSK + 8;
+
+// A thread's share of a 32 x 128 tile (element (r, k) as in stage_tile), t < 128:
+// four 16-byte pieces, 8 k's of rows t / 16 + 8 p or 8 rows of k's 4 (t / 4) + p.
+template <bool KMAJOR>
+__device__ __forceinline__ void small_load(uint4 q[4], const uint16_t *X, int64_t ld, int R, int K,
+                                           int r0, int k0, bool whole, int t) {
+    // No load stands behind a branch (the compiler waits for each of those where
+    // the paths join): addresses outside are clamped, and what they give is cleared
+    // in small_store, where it is needed first.  `whole`: 16-byte pieces are
+    // aligned and lie inside or outside as a whole; otherwise element by element.
+    if (whole) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int r = r0 + (KMAJOR ? (t >> 4) + 8 * p : (t & 3) * 8);
+            const int k = k0 + (KMAJOR ? (t & 15) * 8 : (t >> 2) * 4 + p);
+            q[p] = *reinterpret_cast<const uint4 *>(
+                X + (r < R && k < K ? (KMAJOR ? (int64_t)r * ld + k : (int64_t)k * ld + r) : 0));
+        }
+        return;
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int r = r0 + (KMAJOR ? (t >> 4) + 8 * p : (t & 3) * 8);
+        const int k = k0 + (KMAJOR ? (t & 15) * 8 : (t >> 2) * 4 + p);
+        uint16_t v[8];
+        bool in[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int rj = KMAJOR ? r : r + j, kj = KMAJOR ? k + j : k;
+            in[j] = rj < R && kj < K;
+            v[j] = X[!in[j] ? 0 : KMAJOR ? (int64_t)rj * ld + kj : (int64_t)kj * ld + rj];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = in[j] ? v[j] : (uint16_t)0;
+        __builtin_memcpy(&q[p], v, 16);
+    }
 }
 
-__global__ void col_sum_chunks_kernel(int M, int N, const float *X, float *partial) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (n >= N) return;
-    const int m1 = min(M, (c + 1) * kColChunk);
-    float s = 0.0f;
-    for (int m = c * kColChunk; m < m1; ++m) s += X[(int64_t)m * N + n];
-    partial[(int64_t)c * N + n] = s;
+template <bool KMAJOR>
+__device__ __forceinline__ void small_store(uint16_t (*T)[kSLds], uint4 q[4], int R, int K, int r0,
+                                            int k0, bool whole, int t) {
+    if (whole) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int r = r0 + (KMAJOR ? (t >> 4) + 8 * p : (t & 3) * 8);
+            const int k = k0 + (KMAJOR ? (t & 15) * 8 : (t >> 2) * 4 + p);
+            if (!(r < R && k < K)) q[p] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+    if (KMAJOR) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            *reinterpret_cast<uint4 *>(&T[(t >> 4) + 8 * p][(t & 15) * 8]) = q[p];
+    } else {
+        const uint32_t *w[4] = {&q[0].x, &q[1].x, &q[2].x, &q[3].x};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            // element j of the four pieces: the low or high half of dword j / 2
+            const uint32_t sel = j & 1 ? 0x07060302u : 0x05040100u;
+            *reinterpret_cast<uint2 *>(&T[(t & 3) * 8 + j][(t >> 2) * 4]) =
+                make_uint2(__builtin_amdgcn_perm(w[1][j >> 1], w[0][j >> 1], sel),
+                           __builtin_amdgcn_perm(w[3][j >> 1], w[2][j >> 1], sel));
+        }
+    }
 }
 
-__global__ void col_sum_final_kernel(int chunks, int N, const float *partial, float *out) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    float s = 0.0f;
-    for (int c = 0; c < chunks; ++c) s += partial[(int64_t)c * N + n];
-    out[n] = s;
+template <bool AK, bool BK>
+__device__ __forceinline__ void gemm_small_block(const GemmArgs &g, int bm, int bn) {
+    __shared__ __attribute__((aligned(16))) uint16_t T[2][2][kSB][kSLds];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = bm * kSB, n0 = bn * kSB;
+    int M = g.M;
+    if (g.m_dev) {
+        const int64_t md = (int64_t)*g.m_dev * g.m_mul;
+        M = md < (int64_t)M ? (int)(md > 0 ? md : 0) : M;
+        if (m0 >= M) return;
+    }
+    const bool a_vec = g.lda % 8 == 0 && ((uintptr_t)g.A & 15) == 0 && (AK ? g.K : M) % 8 == 0;
+    const bool b_vec = g.ldb % 8 == 0 && ((uintptr_t)g.B & 15) == 0 && (BK ? g.K : g.N) % 8 == 0;
+    const bool is_a = wave < 2;  // two wavefronts load A, two load B
+    const int t = tid & 127;
+    uint4 q[kSAhead][4];
+    auto load = [&](uint4(&d)[4], int k0) {
+        if (k0 >= g.K) return;
+        if (is_a)
+            small_load<AK>(d, g.A, g.lda, M, g.K, m0, k0, a_vec, t);
+        else
+            small_load<BK>(d, g.B, g.ldb, g.N, g.K, n0, k0, b_vec, t);
+    };
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+    const int fr = lane & 15, fk = (lane >> 4) * 8;
+    f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < kSAhead; ++i) load(q[i], i * kSK);
+    for (int kg = 0; kg < g.K; kg += kSAhead * kSK) {
+#pragma unroll
+        for (int i = 0; i < kSAhead; ++i) {
+            const int k0 = kg + i * kSK;
+            if (k0 >= g.K) break;
+            if (is_a)
+                small_store<AK>(T[i & 1][0], q[i], M, g.K, m0, k0, a_vec, t);
+            else
+                small_store<BK>(T[i & 1][1], q[i], g.N, g.K, n0, k0, b_vec, t);
+            __syncthreads();  // the other buffer's readers are past their reads
+            load(q[i], k0 + kSAhead * kSK);
+#pragma unroll
+            for (int kb = 0; kb < kSK / 32; ++kb) {
+                if (k0 + 32 * kb >= g.K) break;
+                const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&T[i & 1][0][wm + fr][32 * kb + fk]);
+                const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&T[i & 1][1][wn + fr][32 * kb + fk]);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+            }
+        }
+    }
+    const int n = n0 + wn + fr;
+    if (n >= g.N) return;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + wm + (lane >> 4) * 4 + r;
+        if (m < M) gemm_store(g, m, n, acc[r]);
+    }
+}
+
+template <bool AK, bool BK>
+__global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs g) {
+    gemm_small_block<AK, BK>(g, (int)blockIdx.y, (int)blockIdx.x);
+}
+
+// out[n] = sum over m of X[m, n] for 32 columns: chunks of 32 rows in order, 8
+// chunks at a time, then the chunk sums in order.
+__device__ __forceinline__ void col_sum_block(const ColSum &c, int block) {
+    __shared__ float s_part[256 / kColWidth][kColWidth];
+    const int col = threadIdx.x % kColWidth, lane = threadIdx.x / kColWidth;
+    const int n = block * kColWidth + col;
+    const int chunks = (c.M + kColChunk - 1) / kColChunk;
+    float total = 0.0f;
+    for (int b = 0; b < chunks; b += 256 / kColWidth) {
+        // all of a chunk's loads go out together, rows past M as zeros (which
+        // leave a sum that starts at +0 as it is)
+        const int m0 = (b + lane) * kColChunk;
+        float v[kColChunk];
+#pragma unroll
+        for (int q = 0; q < kColChunk; ++q)
+            v[q] = c.X[(int64_t)min(m0 + q, c.M - 1) * c.N + min(n, c.N - 1)];
+        float s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kColChunk; ++q) s += m0 + q < c.M ? v[q] : 0.0f;
+        s_part[lane][col] = s;
+        __syncthreads();
+        if (lane == 0)
+            for (int q = 0; q < 256 / kColWidth && b + q < chunks; ++q) total += s_part[q][col];
+        __syncthreads();
+    }
+    if (lane == 0 && n < c.N) c.out[n] = total;
+}
+
+// Every weight and bias gradient of a network in one launch: dW = dz^T Hin tiles
+// of each layer, then the column sums.  They only wait for the layers' dz, and
+// each alone leaves most of the chip idle: a batch of 1,024 on the 1048-256-256-
+// 256-5 network took 4 x 13 us for the products and 4 x 13 us for the sums (two
+// launches each), together 20 us.
+__global__ __launch_bounds__(256) void gradient_kernel(GradientArgs a) {
+    int b = (int)blockIdx.x;
+    for (int l = 0; l < a.gemms; ++l) {
+        const GemmArgs &g = a.gemm[l];
+        const int nbn = (g.N + kSB - 1) / kSB, nb = nbn * ((g.M + kSB - 1) / kSB);
+        if (b < nb) {
+            gemm_small_block<false, false>(g, b / nbn, b % nbn);
+            return;
+        }
+        b -= nb;
+    }
+    for (int l = 0; l < a.sums; ++l) {
+        const int nb = (a.sum[l].N + kColWidth - 1) / kColWidth;
+        if (b < nb) {
+            col_sum_block(a.sum[l], b);
+            return;
+        }
+        b -= nb;
+    }
 }
 
 __global__ void sq_loss_kernel(int M, int D, const float *Y, const float *T, const float *w,
@@ -675,8 +849,26 @@ hipError_t launch_forward_noise(const ForwardNoiseArgs &a, int hidden, hipStream
     return hipGetLastError();
 }
 
+// Products of at least this many 64 x 64 blocks (two per CU) take those: they
+// read each operand half as often.  A 256-wide forward pass of 4,096 rows (256
+// blocks) 54 us in small blocks against 61, of 8,192 rows (512) 83 against 65.
+constexpr int64_t kLargeBlocks = 512;
+
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
+    const int64_t blocks = (int64_t)((g.M + kBM - 1) / kBM) * ((g.N + kBN - 1) / kBN);
+    if (blocks < kLargeBlocks) {
+        const dim3 sg((unsigned)((g.N + kSB - 1) / kSB), (unsigned)((g.M + kSB - 1) / kSB));
+        if (g.a_kmajor && g.b_kmajor)
+            hipLaunchKernelGGL((gemm_small_kernel<true, true>), sg, dim3(256), 0, s, g);
+        else if (g.a_kmajor)
+            hipLaunchKernelGGL((gemm_small_kernel<true, false>), sg, dim3(256), 0, s, g);
+        else if (g.b_kmajor)
+            hipLaunchKernelGGL((gemm_small_kernel<false, true>), sg, dim3(256), 0, s, g);
+        else
+            hipLaunchKernelGGL((gemm_small_kernel<false, false>), sg, dim3(256), 0, s, g);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)((g.N + kBN - 1) / kBN), (unsigned)((g.M + kBM - 1) / kBM));
     if (g.a_kmajor && g.b_kmajor)
         hipLaunchKernelGGL((gemm_kernel<true, true>), grid, dim3(kGemmThreads), 0, s, g);
@@ -689,24 +881,13 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_act_backward(int M, int N, const float *dH, const uint16_t *H, int act,
-                               float slope, float *dZf, uint16_t *dZb, hipStream_t s) {
-    const int64_t n = (int64_t)M * N;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(act_backward_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, N, dH, H,
-                       act, slope, dZf, dZb);
-    return hipGetLastError();
-}
-
-hipError_t launch_col_sum(int M, int N, const float *X, float *partial, float *out,
-                          hipStream_t s) {
-    if (N == 0) return hipSuccess;
-    const int chunks = (M + kColChunk - 1) / kColChunk;
-    if (chunks > 0)
-        hipLaunchKernelGGL(col_sum_chunks_kernel, dim3(blocks_for(N, 256), (unsigned)chunks),
-                           dim3(256), 0, s, M, N, X, partial);
-    hipLaunchKernelGGL(col_sum_final_kernel, dim3(blocks_for(N, 256)), dim3(256), 0, s, chunks, N,
-                       partial, out);
+hipError_t launch_gradient(const GradientArgs &a, hipStream_t s) {
+    int64_t blocks = 0;
+    for (int l = 0; l < a.gemms; ++l)
+        blocks += (int64_t)((a.gemm[l].N + kSB - 1) / kSB) * ((a.gemm[l].M + kSB - 1) / kSB);
+    for (int l = 0; l < a.sums; ++l) blocks += (a.sum[l].N + kColWidth - 1) / kColWidth;
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(gradient_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

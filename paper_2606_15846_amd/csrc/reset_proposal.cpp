@@ -111,7 +111,7 @@ struct navsim_rp_s {
         uint64_t ct_version = ~0ull;
     } at;
     // workspaces
-    DevBuf ctable, colsum, x, hid[4], y, dyf, dyb, dh, dzf, dzb, lrows, zc, ridx, yc, hc[2],
+    DevBuf ctable, x, hid[4], y, dzf, dzb, lrows, zc, ridx, yc, hc[2],
         bmap, bbin, target, chosen, zp, rp_idx, yp, pend;
 };
 
@@ -132,8 +132,8 @@ void free_rp(navsim_rp_s *r) {
                     r->pool_rows, r->p, r->g, r->m, r->v, r->pb, r->pf.image, r->decay, r->wloss};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
-    DevBuf *bufs[] = {&r->ctable, &r->colsum, &r->x, &r->hid[0], &r->hid[1], &r->hid[2],
-                      &r->hid[3], &r->y, &r->dyf, &r->dyb, &r->dh, &r->dzf, &r->dzb, &r->lrows,
+    DevBuf *bufs[] = {&r->ctable, &r->x, &r->hid[0], &r->hid[1], &r->hid[2],
+                      &r->hid[3], &r->y, &r->dzf, &r->dzb, &r->lrows,
                       &r->zc, &r->ridx, &r->yc, &r->hc[0], &r->hc[1], &r->bmap, &r->bbin,
                       &r->target, &r->chosen, &r->zp, &r->rp_idx, &r->yp, &r->pend};
     for (DevBuf *b : bufs) b->release();
@@ -313,56 +313,58 @@ navsim_status forward_full(navsim_rp_s *r, int n, const uint16_t *X, float *Y, h
     return NAVSIM_OK;
 }
 
-// Loss rows and gradient of the mean weighted squared error into r->g.
-// Layer gradients alternate between two (float, bf16) buffer pairs.
+// Loss rows and gradient of the mean weighted squared error into r->g (and the
+// sum of the loss rows to loss_sum unless NULL).  Every layer keeps its dz (float
+// and bf16) until one launch turns them into the weights' and biases' gradients.
 navsim_status backward_full(navsim_rp_s *r, int n, const uint16_t *X, const float *Y,
-                            const float *T, float *loss_rows, hipStream_t s) {
+                            const float *T, float *loss_rows, float *loss_sum, hipStream_t s) {
     const int out = r->dims[r->L];
-    const int Hmax = *std::max_element(r->dims.begin() + 1, r->dims.end());
-    RP_BUF(r->dyf, (size_t)n * Hmax * 4);
-    RP_BUF(r->dyb, (size_t)n * Hmax * 2);
-    RP_BUF(r->dzf, (size_t)n * Hmax * 4);
-    RP_BUF(r->dzb, (size_t)n * Hmax * 2);
-    RP_BUF(r->dh, (size_t)n * Hmax * 4);
-    RP_BUF(r->colsum, (size_t)((n + 31) / 32 + 1) * Hmax * 4);
-    float *zf[2] = {r->dyf.as<float>(), r->dzf.as<float>()};
-    uint16_t *zb[2] = {r->dyb.as<uint16_t>(), r->dzb.as<uint16_t>()};
-    RP_HIP(launch_sq_loss(n, out, Y, T, r->wloss, loss_rows, zf[0], zb[0], s));
-    int cur = 0;
-    for (int l = r->L - 1; l >= 0; --l) {
-        const int no = r->dims[l + 1], ni = r->dims[l];
-        const uint16_t *Hin = l == 0 ? X : r->hid[l - 1].as<uint16_t>();
-        GemmArgs gw;  // dW = dz^T Hin
-        gw.M = no;
-        gw.N = ni;
+    size_t off[kForwardMaxLayers + 1] = {};  // a layer's dz, in elements (16-byte aligned)
+    for (int l = 0; l < r->L; ++l) off[l + 1] = off[l] + (((size_t)n * r->dims[l + 1] + 7) & ~(size_t)7);
+    RP_BUF(r->dzf, off[r->L] * 4);
+    RP_BUF(r->dzb, off[r->L] * 2);
+    float *zf = r->dzf.as<float>();
+    uint16_t *zb = r->dzb.as<uint16_t>();
+    RP_HIP(launch_sq_loss(n, out, Y, T, r->wloss, loss_rows, zf + off[r->L - 1],
+                          zb + off[r->L - 1], s));
+    for (int l = r->L - 1; l > 0; --l) {  // dz of layer l - 1 = (dz W) act'
+        GemmArgs gx;
+        gx.M = n;
+        gx.N = r->dims[l];
+        gx.K = r->dims[l + 1];
+        gx.A = zb + off[l];
+        gx.lda = r->dims[l + 1];
+        gx.B = r->pb + r->w_off[l];
+        gx.ldb = r->dims[l];
+        gx.b_kmajor = false;
+        gx.act = 3;
+        gx.slope = r->cfg.leaky_slope;
+        gx.H = r->hid[l - 1].as<uint16_t>();
+        gx.ldh = r->dims[l];
+        gx.Cf = zf + off[l - 1];
+        gx.ldcf = r->dims[l];
+        gx.Cb = zb + off[l - 1];
+        gx.ldcb = r->dims[l];
+        RP_HIP(launch_gemm(gx, s));
+    }
+    GradientArgs ga;
+    for (int l = 0; l < r->L; ++l) {
+        GemmArgs &gw = ga.gemm[ga.gemms++];  // dW = dz^T Hin
+        gw.M = r->dims[l + 1];
+        gw.N = r->dims[l];
         gw.K = n;
-        gw.A = zb[cur];
-        gw.lda = no;
+        gw.A = zb + off[l];
+        gw.lda = r->dims[l + 1];
         gw.a_kmajor = false;
-        gw.B = Hin;
-        gw.ldb = ni;
+        gw.B = l == 0 ? X : r->hid[l - 1].as<uint16_t>();
+        gw.ldb = r->dims[l];
         gw.b_kmajor = false;
         gw.Cf = r->g + r->w_off[l];
-        gw.ldcf = ni;
-        RP_HIP(launch_gemm(gw, s));
-        RP_HIP(launch_col_sum(n, no, zf[cur], r->colsum.as<float>(), r->g + r->b_off[l], s));
-        if (l == 0) break;
-        GemmArgs gx;  // dH = dz W
-        gx.M = n;
-        gx.N = ni;
-        gx.K = no;
-        gx.A = zb[cur];
-        gx.lda = no;
-        gx.B = r->pb + r->w_off[l];
-        gx.ldb = ni;
-        gx.b_kmajor = false;
-        gx.Cf = r->dh.as<float>();
-        gx.ldcf = ni;
-        RP_HIP(launch_gemm(gx, s));
-        RP_HIP(launch_act_backward(n, ni, r->dh.as<float>(), r->hid[l - 1].as<uint16_t>(), 1,
-                                   r->cfg.leaky_slope, zf[1 - cur], zb[1 - cur], s));
-        cur = 1 - cur;
+        gw.ldcf = r->dims[l];
+        ga.sum[ga.sums++] = ColSum{n, r->dims[l + 1], zf + off[l], r->g + r->b_off[l]};
     }
+    if (loss_sum) ga.sum[ga.sums++] = ColSum{n, 1, loss_rows, loss_sum};
+    RP_HIP(launch_gradient(ga, s));
     return NAVSIM_OK;
 }
 
@@ -879,14 +881,9 @@ navsim_status navsim_rp_train(navsim_rp_t r, int32_t num_pairs, const int32_t *p
         RP_HIP(launch_select(sa, s));
         if ((st = forward_full(r, batch, sa.x, r->y.as<float>(), s)) != NAVSIM_OK) return st;
         if ((st = backward_full(r, batch, sa.x, r->y.as<float>(), ba.target,
-                                r->lrows.as<float>(), s)) != NAVSIM_OK)
+                                r->lrows.as<float>(), loss ? loss + t : nullptr, s)) != NAVSIM_OK)
             return st;
         if ((st = adamw_step(r, r->g, lr, weight_decay, s)) != NAVSIM_OK) return st;
-        if (loss) {
-            RP_BUF(r->colsum, (size_t)((batch + 31) / 32 + 1) * 4);
-            RP_HIP(launch_col_sum(batch, 1, r->lrows.as<float>(), r->colsum.as<float>(),
-                                  loss + t, s));
-        }
     }
     return NAVSIM_OK;
 }
@@ -988,7 +985,7 @@ navsim_status navsim_rp_loss_grad(navsim_rp_t r, int32_t n, const uint16_t *x,
     RP_BUF(r->y, (size_t)n * 5 * 4);
     navsim_status st = forward_full(r, n, x, r->y.as<float>(), s);
     if (st != NAVSIM_OK) return st;
-    if ((st = backward_full(r, n, x, r->y.as<float>(), target, loss_rows, s)) != NAVSIM_OK)
+    if ((st = backward_full(r, n, x, r->y.as<float>(), target, loss_rows, nullptr, s)) != NAVSIM_OK)
         return st;
     RP_HIP(hipMemcpyAsync(grad, r->g, (size_t)r->nparams * 4, hipMemcpyDeviceToDevice, s));
     return NAVSIM_OK;

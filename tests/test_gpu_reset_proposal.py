@@ -538,3 +538,68 @@ def test_draw_outputs_match_oracle(hidden, layers, nz, nb, n, per):
         assert np.median(d) <= 1e-5 * (1.0 + np.abs(yo).max())
     rp.close()
     sim.close()
+
+
+# rows on both sides of the products' 32- and 64-row blocks and 128-k trips, up to
+# the 64 x 64 blocks (8,192 rows of a 256-wide layer); widths that leave part of a
+# block, and a first layer whose rows are not 16-byte aligned (3 bins)
+@pytest.mark.parametrize("n,hidden,layers,nb", [(1, 256, 3, 8), (33, 16, 1, 8), (127, 48, 2, 3),
+                                                (129, 256, 3, 3), (1025, 80, 4, 8),
+                                                (8192, 256, 1, 8)])
+def test_gradient_sizes_match_oracle(n, hidden, layers, nb):
+    say(f"loss and gradient: {n} rows, hidden {layers} x {hidden}, {nb} bins")
+    sim, rp0, ref, reach, _ = setup(num_envs=8)
+    rp0.close()
+    rp = ResetProposer(sim, hidden=hidden, hidden_layers=layers, num_bins=nb, seed=3)
+    x, xb = _inputs(rp, n, 2)
+    T = np.random.default_rng(3).random((n, 5)).astype(np.float32)
+    rows, g = rp.loss_grad(xb, torch.from_numpy(T).cuda())
+    torch.cuda.synchronize()
+    loss, grads = _oracle_net(rp).loss_grad(OM.from_bf16_bits(OM.bf16_bits(x)), T,
+                                            [1.0, 1.0, 0.0, 1.0, 1.0], emulate=True)
+    g = g.cpu().numpy()
+    assert abs(rows.cpu().numpy().mean() - loss) <= 1e-4 * (1 + abs(loss))
+    for l, (gw, gb) in enumerate(grads):
+        wo, bo = rp.offsets[l]
+        for name, got, want in (("W", g[wo:wo + gw.size].reshape(gw.shape), gw),
+                                ("b", g[bo:bo + gb.size], gb)):
+            scale = np.abs(want).max()
+            d = np.abs(got - want)
+            assert d.max() <= 2e-2 * scale + 1e-7, (l, name)
+            assert np.median(d) <= 1e-3 * scale + 1e-9, (l, name)
+    rp.close()
+    sim.close()
+
+
+@pytest.mark.parametrize("samples", [1, 64, 65, 256])
+def test_training_keeps_the_nearest_draw(samples):
+    """The loss of one training step against the oracle's network on every draw:
+    per target the smallest weighted error (draws within the network's tolerance
+    of each other may swap, which moves the sum by as little)."""
+    say(f"one training step, 7 targets of {samples} draws")
+    sim, rp, ref, reach, maps = setup(num_envs=8)
+    W, H, nb, batch = maps[1].shape[1], maps[1].shape[0], rp.nb, 7
+    start, goal = 40 * W + 50, 200 * W + 130
+    net = _oracle_net(rp)  # before the step changes it
+    loss = torch.zeros(1, device=sim.device)
+    one = [torch.tensor([v], dtype=torch.int32, device=sim.device) for v in (1, 2, start, goal)]
+    rp.train(dict(zip(("map", "bin", "start", "goal"), one)), 1, batch=batch, samples=samples,
+             loss=loss)
+    torch.cuda.synchronize()
+    seed = rp.cfg["seed"]
+    x = np.zeros((batch * samples, rp.d0))
+    x[:, :1024] = G.pool32(maps[1])
+    x[:, 1024 + 2] = 1.0
+    for r in range(batch * samples):
+        for q in range(4):
+            w = oracle.philox4x32_10([r // samples, 0, ((r % samples) << 8) | q, 9],
+                                     [seed & 0xFFFFFFFF, seed >> 32])
+            x[r, 1024 + nb + 4 * q:1024 + nb + 4 * q + 4] = \
+                2.0 * ((np.array(w, np.float64) + 0.5) / 2.0 ** 32) - 1.0
+    y, _ = net.forward(OM.from_bf16_bits(OM.bf16_bits(x)), emulate=True)
+    t = np.array([(50 + 0.5) / W, (40 + 0.5) / H, 0, (130 + 0.5) / W, (200 + 0.5) / H])
+    err = ((y - t) ** 2 * [1, 1, 0, 1, 1]).sum(1).reshape(batch, samples).min(1).sum()
+    assert abs(loss.item() - err) <= 4 * 2e-3 * (1 + np.abs(y).max()) * batch
+    assert abs(loss.item() - err) <= 1e-3 * err
+    rp.close()
+    sim.close()
