@@ -121,7 +121,7 @@ void drop_graph(navsim_s *h) {
 
 void free_device(navsim_s *h) {
     drop_graph(h);
-    void *ptrs[] = {h->bits, h->maps, h->free_cells, h->env_map, h->perm, h->tiles};
+    void *ptrs[] = {h->bits, h->maps, h->free_cells, h->env_map, h->perm, h->tiles, h->clear};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     h->bits = nullptr;
@@ -130,6 +130,7 @@ void free_device(navsim_s *h) {
     h->env_map = nullptr;
     h->perm = nullptr;
     h->tiles = nullptr;
+    h->clear = nullptr;
 }
 
 template <typename T>
@@ -193,16 +194,25 @@ int staged_words(int max_words, int max_words_t, int walk, int scan_mode) {
 // walks (and the march) use ray_cap slots.  walk 2 and 4 stage the map's
 // byte-per-cell copy, walk 5 the transposed bitmap.  Fails with UNSUPPORTED
 // when nothing fits.
+// The march stages the maps' clearances after the bitmaps where they fit beside
+// at least as many ray slots as there are threads.
 struct FusedShape {
     int ray_cap = 0, cell_bytes = 0, claim = 0, resident = 0;
-    bool beams_lds = true;
+    bool beams_lds = true, clear = false;
 };
 
-navsim_status fused_shape(const navsim_s *h, int max_words_row, int max_words_t, int tile_envs,
-                          int threads, int slots, int walk, int scan_mode, FusedShape &out) {
+navsim_status fused_shape(const navsim_s *h, int max_words_row, int max_words_t, int max_clear,
+                          int tile_envs, int threads, int slots, int walk, int scan_mode,
+                          FusedShape &out) {
     const navsim_config &c = h->cfg;
     const int m = c.num_sectors, K = c.num_beams;
-    const int max_words = staged_words(max_words_row, max_words_t, walk, scan_mode);
+    int max_words = staged_words(max_words_row, max_words_t, walk, scan_mode);
+    if (scan_mode == NAVSIM_SCAN_MARCH) {
+        bool beams = false;
+        out.clear = choose_ray_cap(max_words + max_clear, c, tile_envs, threads, slots,
+                                   h->lds_block, h->lds_cu, 0, beams) >= threads;
+        if (out.clear) max_words += max_clear;
+    }
     out.claim = scan_mode == NAVSIM_SCAN_TRAVERSAL && walk >= 3;
     // the run walk packs a hit's position in the transposed bitmap in 19 bits
     if (max_words > max_words_row && (int64_t)max_words_t * 32 >= (1 << 19))
@@ -247,6 +257,46 @@ void apply_shape(navsim_s *h, const FusedShape &f) {
     h->claim = f.claim;
     h->resident = f.resident;
     h->beams_lds = f.beams_lds;
+    h->use_clear = f.clear;
+}
+
+// Clearances of the loaded maps (see MapDesc) into the device pool: chessboard
+// distance by two passes over the cells, outside counting as occupied.
+navsim_status build_clearance(navsim_s *h, const std::vector<MapDesc> &descs) {
+    std::vector<uint32_t> pool;
+    std::vector<uint8_t> dist;
+    for (int k = 0; k < h->num_maps; ++k) {
+        const MapDesc &d = descs[k];
+        const int W = d.w, H = d.h, pitch = W + 2;  // a ring of zeros around the map
+        const uint8_t *occ = h->host_occ.data() + h->host_occ_off[k];
+        dist.assign((size_t)pitch * (H + 2), 0);
+        for (int j = 0; j < H; ++j)
+            for (int i = 0; i < W; ++i) {
+                uint8_t *q = &dist[(size_t)(j + 1) * pitch + i + 1];
+                const int v = std::min(std::min(q[-1], q[-pitch]),
+                                       std::min(q[-pitch - 1], q[-pitch + 1]));
+                *q = occ[(size_t)j * W + i] ? 0 : (uint8_t)std::min(v + 1, 15);
+            }
+        for (int j = H - 1; j >= 0; --j)
+            for (int i = W - 1; i >= 0; --i) {
+                uint8_t *q = &dist[(size_t)(j + 1) * pitch + i + 1];
+                const int v = std::min(std::min(q[1], q[pitch]),
+                                       std::min(q[pitch + 1], q[pitch - 1]));
+                *q = (uint8_t)std::min<int>(*q, v + 1);
+            }
+        pool.resize((size_t)d.clr_off + d.clr_words, 0u);
+        for (int j = 0; j < H; j += 2)
+            for (int i = 0; i < W; i += 2) {
+                const uint8_t *q = &dist[(size_t)(j + 1) * pitch + i + 1];
+                int v = q[0];
+                if (i + 1 < W) v = std::min<int>(v, q[1]);
+                if (j + 1 < H) v = std::min<int>(v, q[pitch]);
+                if (i + 1 < W && j + 1 < H) v = std::min<int>(v, q[pitch + 1]);
+                const int b = (j / 2) * d.clr_w + i / 2;
+                pool[(size_t)d.clr_off + (b >> 3)] |= (uint32_t)v << (4 * (b & 7));
+            }
+    }
+    return upload(&h->clear, pool);
 }
 
 // Envs grouped by map (stable in env order) into tiles of up to tile_envs envs,
@@ -611,6 +661,11 @@ StepParams navsim::make_step_params(const navsim_s *h) {
     p.num_maps = h->num_maps;
     p.max_words = staged_words(h->max_words, h->max_words_t, h->walk_mode, h->scan_mode);
     p.tbits_off = p.max_words > h->max_words ? h->max_words : 0;
+    if (h->scan_mode == NAVSIM_SCAN_MARCH && h->use_clear) {
+        p.clear_off = p.max_words;
+        p.max_words += h->max_clear;
+        p.clear = h->clear;
+    }
     p.refill_at = h->refill_at;
     p.groups = h->groups;
     p.ray_cap = h->ray_cap;
@@ -778,7 +833,8 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     std::map<int, int32_t> beam_off;
     std::vector<uint32_t> bits;
     std::vector<int32_t> free_cells;
-    int max_words = 4, max_words_t = 4;
+    int max_words = 4, max_words_t = 4, max_clear = 4;
+    int64_t clear_words = 0;
     for (int k = 0; k < num_maps; ++k) {
         const int W = width[k], H = height[k];
         const uint8_t *m = occ + occ_off[k];
@@ -836,6 +892,11 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
             }
         }
         max_words_t = std::max(max_words_t, d.words_t);
+        d.clr_w = (W + 1) / 2;
+        d.clr_words = ((d.clr_w * ((H + 1) / 2) + 7) / 8 + 3) & ~3;
+        d.clr_off = clear_words;
+        clear_words += d.clr_words;
+        max_clear = std::max(max_clear, d.clr_words);
         d.free_off = (int64_t)free_cells.size();
         const double s = (double)res_m[k];
         for (int iy = 0; iy < H; ++iy)
@@ -853,8 +914,8 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     FusedShape shape;
     {
         DeviceGuard g(h->device);
-        const navsim_status fs = fused_shape(h, max_words, max_words_t, h->tile_envs, h->wg_threads,
-                                             h->ray_slots, h->walk_mode, h->scan_mode, shape);
+        const navsim_status fs = fused_shape(h, max_words, max_words_t, max_clear, h->tile_envs,
+                                             h->wg_threads, h->ray_slots, h->walk_mode, h->scan_mode, shape);
         if (fs != NAVSIM_OK) return fs;
     }
     std::vector<int32_t> host_env_map(env_map, env_map + N);
@@ -889,6 +950,7 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     h->num_tiles = (int)tiles.size();
     h->max_words = max_words;
     h->max_words_t = max_words_t;
+    h->max_clear = max_clear;
     apply_shape(h, shape);
     h->host_env_map.swap(host_env_map);
     h->host_map_weight.swap(map_weight);
@@ -906,6 +968,8 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
         h->host_free_cnt[k] = descs[k].free_cnt;
     }
     h->host_free.swap(free_cells);
+    h->host_descs.swap(descs);
+    if (h->use_clear && (s = build_clearance(h, h->host_descs)) != NAVSIM_OK) return s;
     h->loaded = true;
     return NAVSIM_OK;
 }
@@ -1050,9 +1114,14 @@ navsim_status navsim_set_scan(navsim_t h, int32_t mode, float step_m) {
     FusedShape shape;
     if (h->loaded) {
         DeviceGuard g(h->device);
-        const navsim_status fs = fused_shape(h, h->max_words, h->max_words_t, h->tile_envs, h->wg_threads,
-                                             h->ray_slots, h->walk_mode, mode, shape);
+        const navsim_status fs = fused_shape(h, h->max_words, h->max_words_t, h->max_clear,
+                                             h->tile_envs, h->wg_threads, h->ray_slots,
+                                             h->walk_mode, mode, shape);
         if (fs != NAVSIM_OK) return fs;
+        if (shape.clear && !h->clear) {
+            const navsim_status cs = build_clearance(h, h->host_descs);
+            if (cs != NAVSIM_OK) return cs;
+        }
     }
     {
         DeviceGuard g(h->device);
@@ -1092,9 +1161,14 @@ navsim_status navsim_set_tuning(navsim_t h, const navsim_tuning *t) {
     FusedShape shape;
     if (h->loaded) {
         DeviceGuard g(h->device);
-        const navsim_status fs = fused_shape(h, h->max_words, h->max_words_t, t->tile_envs, t->threads,
-                                             t->ray_slots, t->walk, h->scan_mode, shape);
+        const navsim_status fs = fused_shape(h, h->max_words, h->max_words_t, h->max_clear,
+                                             t->tile_envs, t->threads, t->ray_slots, t->walk,
+                                             h->scan_mode, shape);
         if (fs != NAVSIM_OK) return fs;
+        if (shape.clear && !h->clear) {
+            const navsim_status cs = build_clearance(h, h->host_descs);
+            if (cs != NAVSIM_OK) return cs;
+        }
     }
     if (h->loaded) {
         std::vector<int32_t> perm;

@@ -58,6 +58,9 @@ struct navsim_s {
     navsim::Tile *tiles = nullptr;
     int num_maps = 0, num_tiles = 0, max_words = 0;
     int max_words_t = 0;  // largest transposed bitmap (staged beside the bitmap by walk 5)
+    uint32_t *clear = nullptr;  // clearance pool, built when the march is first selected
+    int max_clear = 0;          // largest map's clearance words
+    bool use_clear = false;     // march: the clearances fit LDS in the current launch shape
     int tile_envs = navsim::kDefaultTileEnvs, refill_at = navsim::kDefaultRefillAt, groups = navsim::kDefaultGroups;
     int ray_cap = 0;
     int ray_slots = 0;  // requested cap on ray_cap (0 = automatic)
@@ -85,6 +88,7 @@ struct navsim_s {
     std::vector<int32_t> host_free;
     std::vector<int64_t> host_free_off;
     std::vector<int32_t> host_free_cnt;
+    std::vector<navsim::MapDesc> host_descs;
     // rollouts: first step index on the device, and the last captured rollout
     uint32_t *step_ctr = nullptr;
     hipStream_t capture_stream = nullptr;

@@ -55,6 +55,11 @@ struct MapDesc {
     // and shift = 18 (12) + ceil(log2 d), so that x d <= 2^shift
     uint32_t k_magic, per_magic;
     int32_t k_shift, per_shift;
+    // clearance of each block of 2 x 2 cells, for the fixed-step march: the least
+    // over its cells of the chessboard distance to an occupied or outside cell (0
+    // in one, at most 15), 4 bits a block, block (bi, bj) at 4 (bj clr_w + bi)
+    int32_t clr_w, clr_words;  // blocks per row; words, rounded up to a multiple of 4
+    int64_t clr_off;           // start in the clearance pool (multiple of 4 words)
 };
 
 // A group of up to tile_envs envs that share one map (one fused workgroup).
@@ -99,6 +104,8 @@ struct StepParams {
     const Tile *tiles;
     int32_t num_tiles, num_maps, max_words;  // max_words: LDS words of the staged bitmaps
     int32_t tbits_off;  // walk 5: LDS word offset of the staged transposed bitmap (else 0)
+    int32_t clear_off;  // march: LDS word offset of the staged clearances (0: none staged)
+    const uint32_t *clear;  // clearance pool (march)
     // inputs / outputs
     const float *act;          // normalised actions [N][2], or null in a rollout
     const uint32_t *step_ctr;  // rollout: device {lo, hi} of the first step index

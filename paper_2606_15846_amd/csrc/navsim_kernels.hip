@@ -1153,8 +1153,9 @@ __device__ __forceinline__ void run_walk(const StepParams &p, const MapView &M,
         reinterpret_cast<uint2 *>(s_ray)[2 * r] = make_uint2((uint32_t)B | ((uint32_t)k << 19), flags);
 }
 
-// Phase (2) for the fixed-step march: the refilling walk of the traversal
-// with each lane marching its ray in groups of 4 samples (bitmap in LDS);
+// Phase (2) for the fixed-step march where the clearances do not fit LDS beside
+// the bitmap and the ray slots (see march_skip_walk): the refilling walk of the
+// traversal with each lane marching its ray in groups of 4 samples (bitmap in LDS);
 // the result k | outcome << 28 goes back to the ray's slot.
 __device__ __forceinline__ void march_walk(const StepParams &p, const MapView &M,
                                            const TileJob *s_jobs, const int *s_list,
@@ -1224,6 +1225,117 @@ __device__ __forceinline__ void march_walk(const StepParams &p, const MapView &M
                     break;
                 }
                 k += 4;
+            }
+        }
+    }
+    if (r >= 0)
+        reinterpret_cast<uint2 *>(s_ray)[2 * r] = make_uint2((uint32_t)k | ((uint32_t)type << 28), 0u);
+}
+
+// The march with the map's clearances staged (p.clear_off): a sample in a block of
+// 2 x 2 cells whose clearance d is at least 2 is free, and so is every later one whose
+// point lies less than d - 1.02 cells away along both axes: those are passed
+// over without being looked at.  The sample's cell comes from a float position
+// (off by less than 0.01 cells on any map that fits LDS); it decides the sample
+// where it lies more than 0.01 cells from every grid line, else the sample is
+// evaluated exactly, so every outcome is march_sample's.  Bound by VALU issue:
+// about 40 instructions a look against about 90 for the double-precision sample
+// (two divisions).  4,096 envs of 360 beams on 128 x 128 maps of 5 cm, samples
+// every 3 cm to 6 m, tiles of 8: 389 -> 194 us a step.
+__device__ __forceinline__ void march_skip_walk(const StepParams &p, const MapView &M,
+                                           const MapDesc &md, const uint32_t *s_bits,
+                                           const TileJob *s_jobs, const int *s_list,
+                                           const double2 *s_beam, uint4 *s_ray, int *s_misc,
+                                           int c0, int Rc, int K, float inv_K, int lane) {
+    int r = -1, k = 0, type = 0;
+    bool act = false, exhausted = false, near = false;
+    double x = 0.0, y = 0.0, dx = 0.0, dy = 0.0;
+    float cx = 0.0f, cy = 0.0f, sx = 0.0f, sy = 0.0f, per_cell = 0.0f;
+    const int kmax = p.march_kmax;
+    const double h = p.march_h, hs = h / M.s;
+    const uint32_t *s_clear = s_bits + p.clear_off;
+    for (;;) {
+        uint64_t am = __ballot(act);
+        if (!exhausted && __popcll(am) <= p.refill_at) {
+            if (!act && r >= 0) {
+                reinterpret_cast<uint2 *>(s_ray)[2 * r] =
+                    make_uint2((uint32_t)k | ((uint32_t)type << 28), 0u);
+                r = -1;
+            }
+            const uint64_t idle = ~am;
+            const int nidle = 64 - __popcll(am);
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&s_misc[1], nidle);
+            // every lane is active here, so the first active one is lane 0
+            base = __builtin_amdgcn_readfirstlane(base);
+            const int my = (int)__builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(idle >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)idle, (uint32_t)base));
+            if (!act && my < Rc) {
+                const int g = c0 + my;
+                int beam;
+                const int jl = small_divmod(g, K, inv_K, beam);
+                const TileJob &j = s_jobs[s_list[jl]];
+                const double2 cs = s_beam[beam];
+                dx = j.c * cs.x - j.s * cs.y;
+                dy = j.s * cs.x + j.c * cs.y;
+                x = j.x;
+                y = j.y;
+                // position and step in cells, and samples per cell along the faster
+                // axis (rounded down)
+                cx = (float)j.xc;
+                cy = (float)j.yc;
+                sx = (float)(dx * hs);
+                sy = (float)(dy * hs);
+                per_cell = fminf(0.9999f / fmaxf(fabsf(sx), fabsf(sy)), 1.0e6f);
+                // an origin far outside (or no number) takes exact samples only
+                near = fabsf(cx) < 16384.0f && fabsf(cy) < 16384.0f;
+                r = my;
+                k = 0;
+                type = 0;
+                act = true;
+            }
+            exhausted = base + nidle >= Rc;
+            am = __ballot(act);
+        }
+        if (am == 0ull) {
+            if (exhausted) break;
+            continue;
+        }
+        if (act) {
+#pragma unroll 1
+            for (int gi = 0; gi < 4 * p.groups; ++gi) {
+                const float fx = fmaf((float)k, sx, cx), fy = fmaf((float)k, sy, cy);
+                const float ix = floorf(fx), iy = floorf(fy);
+                const float rx = fx - ix, ry = fy - iy;
+                const bool sure = near && rx > 0.01f && rx < 0.99f && ry > 0.01f && ry < 0.99f;
+                const int i = (int)ix, j = (int)iy;
+                const bool in = near && (unsigned)i < (unsigned)M.w && (unsigned)j < (unsigned)M.h;
+                const int ci = in ? i : 0, cj = in ? j : 0;
+                const int b = (cj + kPad) * M.pitch + (ci + kPad);
+                const int q = (cj >> 1) * md.clr_w + (ci >> 1);
+                const uint32_t wb = s_bits[b >> 5], wc = s_clear[q >> 3];
+                const int d = (int)__builtin_amdgcn_ubfe(wc, (uint32_t)(4 * q), 4u);
+                int on = 1;  // samples passed
+                if (in && d >= 2) {
+                    on = 1 + (int)(((float)d - 1.02f) * per_cell);
+                } else {
+                    if (sure) {
+                        type = in ? (int)__builtin_amdgcn_ubfe(wb, (uint32_t)b, 1u) : 2;
+                    } else {
+                        int cell;
+                        type = march_sample(M, x, y, dx, dy, h, k, &cell);
+                    }
+                }
+                if (type != 0) {
+                    act = false;
+                    break;
+                }
+                if (on > kmax - k) {
+                    k = kmax;
+                    act = false;
+                    break;
+                }
+                k += on;
             }
         }
     }
@@ -1702,8 +1814,11 @@ __device__ __forceinline__ int *fused_list(const StepParams &p) {
     return reinterpret_cast<int *>(s_pool + pool_words(E, p.m));
 }
 
-// One tile with a workgroup of T threads (T / 64 wavefronts).
-template <int E, int T>
+// One tile with a workgroup of T threads (T / 64 wavefronts).  SKIP: the march with
+// the map's clearances, in a kernel of its own: in the one that holds every other
+// walk (the march without clearances among them) its scalars cost the traversal
+// 1 to 2 %.
+template <int E, int T, bool SKIP>
 __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, int &staged_map) {
     extern __shared__ uint4 smem4[];
     uint8_t *s_cells = reinterpret_cast<uint8_t *>(smem4);
@@ -1760,12 +1875,17 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
         const uint4 *g = reinterpret_cast<const uint4 *>(p.bits + md.word_off);
         uint4 *b4 = reinterpret_cast<uint4 *>(s_bits);
         for (int q = tid; q < md.words / 4; q += T) b4[q] = g[q];
-        if (p.tbits_off) {
+        if (!SKIP && p.tbits_off) {
             const uint4 *gt = reinterpret_cast<const uint4 *>(p.bits + md.word_off_t);
             uint4 *t4 = reinterpret_cast<uint4 *>(s_bits + p.tbits_off);
             for (int q = tid; q < md.words_t / 4; q += T) t4[q] = gt[q];
         }
-        if (p.cell_bytes) {
+        if (SKIP) {
+            const uint4 *gc = reinterpret_cast<const uint4 *>(p.clear + md.clr_off);
+            uint4 *c4 = reinterpret_cast<uint4 *>(s_bits + p.clear_off);
+            for (int q = tid; q < md.clr_words / 4; q += T) c4[q] = gc[q];
+        }
+        if (!SKIP && p.cell_bytes) {
             // byte copy: bit b of word q becomes byte 32 q + b (0 or 1); a
             // nibble times 0x00204081 moves its bit i to bit 8 i
             const uint32_t *gw = p.bits + md.word_off;
@@ -1911,7 +2031,7 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
         }
         __builtin_amdgcn_s_setprio(0);
     }
-    if (!p.claim) __syncthreads();  // the chunked walks set up every ray at once
+    if (SKIP || !p.claim) __syncthreads();  // the chunked walks set up every ray at once
 
     // ---- scan, in chunks of at most ray_cap rays ----
     const int nj = s_misc[0];
@@ -1919,7 +2039,7 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
     const float inv_K = 1.0f / (float)K, inv_per = 1.0f / (float)per;
     const double rmax_c = walk_cells((double)p.rmax, M.s);
     const int max_n = M.w + M.h + 2 * kPad;  // a walk meets the padding ring before this
-    if (p.claim) {
+    if (!SKIP && p.claim) {
         // s_misc[1] (next ray) and the pool were cleared before the last barrier
         if (p.tbits_off)
             claim_run_walk(p, M, s_bits, s_jobs, s_list, s_beam, s_pool, s_misc, R,
@@ -1932,10 +2052,10 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
                               K, inv_K, per, inv_per, rmax_c, max_n, E, lane);
         __syncthreads();
     }
-    for (int c0 = 0; c0 < R && !p.claim; c0 += p.ray_cap) {
+    for (int c0 = 0; c0 < R && (SKIP || !p.claim); c0 += p.ray_cap) {
         const int Rc = min(p.ray_cap, R - c0);
         // (1) every ray's walk start, all lanes busy (the march needs none)
-        for (int r = tid; r < Rc && p.scan_mode != 1; r += T) {
+        for (int r = tid; r < Rc && !SKIP && p.scan_mode != 1; r += T) {
             const int g = c0 + r;
             int beam;
             const int jl = small_divmod(g, K, inv_K, beam);
@@ -1954,7 +2074,10 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
         // (2) walk: lanes take rays from s_misc[1]; a lane whose ray is done
         // writes its result back and takes a new one once at most refill_at
         // lanes of its wavefront are still walking
-        if (p.scan_mode == 1) {
+        if (SKIP) {
+            march_skip_walk(p, M, md, s_bits, s_jobs, s_list, s_beam, s_ray, s_misc, c0, Rc, K,
+                            inv_K, lane);
+        } else if (p.scan_mode == 1) {
             march_walk(p, M, s_jobs, s_list, s_beam, s_ray, s_misc, c0, Rc, K, inv_K, lane);
         } else if (p.walk_mode == 1) {
             run_walk(p, M, s_bits, s_ray, s_misc, Rc, lane);
@@ -1971,7 +2094,7 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
             const int jl = small_divmod(g, K, inv_K, beam);
             const int job = s_list[jl];
             const uint4 v = s_ray[q];
-            if (p.scan_mode == 1)
+            if (SKIP || p.scan_mode == 1)
                 finish_march(p, M, s_jobs[job], s_beam, job, beam, v.x, s_pool, per, inv_per, E);
             else
                 finish_ray(p, M, s_jobs[job], s_beam, job, beam, make_uint2(v.x, v.y), s_pool,
@@ -1998,12 +2121,12 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
 // Register budget: 128 VGPRs, so that 4 wavefronts share each SIMD and hide
 // one another's LDS latency in the walk (the compiler's own choice, ~200,
 // leaves 2); the walk loop keeps everything in registers.
-template <int E, int T, bool Q>
+template <int E, int T, bool Q, bool SKIP>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerSimd)))
 void fused_step_kernel(StepParams p) {
     int staged = -1;
     if constexpr (!Q) {
-        fused_tile<E, T>(p, (int)blockIdx.x, staged);
+        fused_tile<E, T, SKIP>(p, (int)blockIdx.x, staged);
         return;
     }
     int *s_next = fused_list<E>(p) + 4 * E + 7;
@@ -2015,7 +2138,7 @@ void fused_step_kernel(StepParams p) {
         if (t0 >= p.num_tiles) break;
         const int t1 = min(t0 + p.chunk, p.num_tiles);
         for (int t = t0; t < t1; ++t) {
-            fused_tile<E, T>(p, t, staged);
+            fused_tile<E, T, SKIP>(p, t, staged);
             __syncthreads();
         }
     }
@@ -2134,7 +2257,7 @@ __global__ __launch_bounds__(64) void plain_step_kernel(StepParams p) {
 }
 
 // ---------------------------------------------------------------------------
-template <int E, int T, bool Q>
+template <int E, int T, bool Q, bool SKIP>
 static hipError_t launch_fused_etq(const StepParams &p, hipStream_t s) {
     const size_t lds = fused_lds_bytes(p.max_words, p.m, E, p.beams_lds ? p.K : 0,
                                        p.claim ? 0 : p.ray_cap, p.cell_bytes);
@@ -2147,7 +2270,7 @@ static hipError_t launch_fused_etq(const StepParams &p, hipStream_t s) {
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= kDevices || (int)lds > raised[dev].load()) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(fused_step_kernel<E, T, Q>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(fused_step_kernel<E, T, Q, SKIP>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             if (dev >= 0 && dev < kDevices) raised[dev].store((int)lds);
@@ -2159,19 +2282,23 @@ static hipError_t launch_fused_etq(const StepParams &p, hipStream_t s) {
         const int chunks = (p.num_tiles + p.chunk - 1) / p.chunk;
         grid = (unsigned)std::max(1, std::min(chunks, p.resident));
     }
-    hipLaunchKernelGGL((fused_step_kernel<E, T, Q>), dim3(grid), dim3(T), lds, s, p);
+    hipLaunchKernelGGL((fused_step_kernel<E, T, Q, SKIP>), dim3(grid), dim3(T), lds, s, p);
     return hipGetLastError();
 }
 
 template <int E, int T>
 static hipError_t launch_fused_et(const StepParams &p, hipStream_t s) {
-    return p.queue ? launch_fused_etq<E, T, true>(p, s) : launch_fused_etq<E, T, false>(p, s);
+    if (p.clear_off)
+        return p.queue ? launch_fused_etq<E, T, true, true>(p, s)
+                       : launch_fused_etq<E, T, false, true>(p, s);
+    return p.queue ? launch_fused_etq<E, T, true, false>(p, s)
+                   : launch_fused_etq<E, T, false, false>(p, s);
 }
 
 template <int E, int T>
 static int resident_et(size_t lds) {
     int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fused_step_kernel<E, T, false>, T,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fused_step_kernel<E, T, false, false>, T,
                                                      lds) !=
             hipSuccess ||
         hipGetDevice(&dev) != hipSuccess ||
@@ -2200,9 +2327,9 @@ int fused_resident_groups(int max_words, int m, int E, int T, int K, bool beams_
 template <int E, int T>
 static int static_lds_et() {
     hipFuncAttributes fa, fq;
-    if (hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(fused_step_kernel<E, T, false>)) !=
+    if (hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(fused_step_kernel<E, T, false, false>)) !=
             hipSuccess ||
-        hipFuncGetAttributes(&fq, reinterpret_cast<const void *>(fused_step_kernel<E, T, true>)) !=
+        hipFuncGetAttributes(&fq, reinterpret_cast<const void *>(fused_step_kernel<E, T, true, false>)) !=
             hipSuccess)
         return -1;
     return (int)std::max(fa.sharedSizeBytes, fq.sharedSizeBytes);

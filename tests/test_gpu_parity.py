@@ -687,3 +687,55 @@ def test_footprint_window_beyond_limit_is_rejected():
         NavSim(cfg, maps, [0.005], np.zeros(4, np.int32), device=0)
     assert ei.value.status == -7
     assert "window" in str(ei.value)
+
+
+# (W, H, cell, sample spacing, r_max): odd sizes (blocks of 2 x 2 cells cut at the
+# edge), spacings from far below to far above a cell, a map whose clearances do not
+# fit LDS beside the bitmap
+MARCH_CASES = [(200, 180, 0.0625, 0.03125, 8.0), (61, 47, 0.05, 0.03, 3.0),
+               (33, 97, 0.1, 0.004, 2.5), (128, 65, 0.05, 0.33, 20.0), (40, 40, 0.05, 2.5, 6.0),
+               (512, 700, 0.05, 0.03, 20.0)]
+
+
+@pytest.mark.parametrize("case", range(len(MARCH_CASES)))
+def test_march_passes_free_samples_exactly(case):
+    """The fused march, which passes over samples that the staged clearances show
+    to be free, gives bitwise the plain kernel's march (every sample evaluated):
+    origins on grid lines and corners, headings along the axes and diagonals,
+    poses inside obstacles and outside the map; two launch shapes."""
+    from workloads import maps as gm
+    W, H, res, step, rmax = MARCH_CASES[case]
+    say(f"march {W}x{H} cells of {res} m, every {step} m to {rmax} m")
+    occ = gm.gen_rect_disc_map(31 + case, w=W, h=H, res=res, occupancy=0.06)
+    N = 192
+    cfg = configs.make_config(num_envs=N, num_beams=96, num_sectors=8, fov_rad=2 * math.pi,
+                              max_range_m=rmax, dt_s=0.1, footprint=0, radius_m=0.1,
+                              v_min=0.0, v_max=0.5, w_min=-1.0, w_max=1.0)
+    rng = np.random.default_rng(40 + case)
+    cells = rng.uniform((-3, -3), (W + 3, H + 3), (N, 2))
+    on_line = np.arange(N) % 3 == 0
+    cells[on_line] = np.round(cells[on_line] * 2) / 2
+    x, y = (cells.T * res).astype(np.float32)
+    th = np.where(np.arange(N) % 2, rng.uniform(-3, 3, N),
+                  rng.integers(-3, 4, N) * (math.pi / 4)).astype(np.float32)
+    acts = torch.from_numpy(np.tile(np.array([-1.0, 0.0], np.float32), (N, 1))).cuda()
+    runs = []
+    for kernel, shape in ((NAVSIM_KERNEL_PLAIN, None), (NAVSIM_KERNEL_FUSED, None),
+                          (NAVSIM_KERNEL_FUSED, dict(tile_envs=16, refill_at=24, groups=2,
+                                                     walk=0, threads=512, balance=1))):
+        sim = NavSim(cfg, [occ], [res], np.zeros(N, np.int32), device=0)
+        sim.set_scan(navsim.NAVSIM_SCAN_MARCH, step)
+        if shape:
+            sim.set_tuning(**shape)
+        z = np.zeros(N, np.float32)
+        sim.set_state(dict(x=x, y=y, th=th, v=z, w=z, gx=z + 1, gy=z + 1, dprev=z,
+                           t=np.zeros(N, np.int32), ep=np.zeros(N, np.uint32)))
+        g = sim.step_debug(acts, kernel)
+        torch.cuda.synchronize()
+        runs.append({k: v.cpu().numpy() for k, v in g.items()} |
+                    dict(obs=sim.obs.cpu().numpy(), final=sim.final_obs.cpu().numpy()))
+        sim.close()
+    for other in runs[1:]:
+        for k in runs[0]:
+            assert np.array_equal(runs[0][k], other[k]), k
+    assert runs[0]["visits"].max() > 1
