@@ -287,7 +287,9 @@ typedef struct {
                            at most tile_envs envs each.  Tiles always launch heaviest first */
 } navsim_tuning;
 
-/* Set the fused step's launch shape (defaults: 8, 40, 8, 0, 3, 0, 256, 0).  Changing tile_envs
+/* Set the fused step's launch shape.  Until it is called, navsim_load_maps (and
+ * navsim_set_scan) pick one for the number of envs and the maps' sizes; before
+ * maps are loaded navsim_get_tuning gives 8, 40, 8, 0, 3, 0, 256, 0.  Changing it
  * after navsim_load_maps waits for the device and re-groups the envs; returns
  * NAVSIM_E_UNSUPPORTED if the larger tile would not fit LDS. */
 navsim_status navsim_set_tuning(navsim_t h, const navsim_tuning *t);

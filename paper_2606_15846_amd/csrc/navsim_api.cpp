@@ -251,6 +251,77 @@ navsim_status fused_shape(const navsim_s *h, int max_words_row, int max_words_t,
     return NAVSIM_OK;
 }
 
+// Launch shape of a handle that has none set: workgroups of 1,024 threads while
+// 32 envs each would make at most half as many as run at once (so that `balance`
+// has room to even them out), else of 512; tiles of up to 32 envs, balanced; the
+// run walk, or with 1,024 threads and small maps the byte walk.  Measured against
+// tiles of 8 envs on 256 threads with the bitmap walk (us a step; the best shape
+// of a sweep of 45 in brackets): 16 envs of 36 beams 15.2 -> 12.6 (12.3); 256 of
+// 360 on one 256 x 256 map 83 -> 23 (22.9); 1,024 of 1,080 beams, one map, 20 m
+// 217 -> 46 (45.7); 4,096 of 360, 128 x 128 maps 91 -> 53 (52.2); 16,384 of 360,
+// 256 x 256 225 -> 171 (167); 8,192 mixed, 1,024 threads 229, 512 151 (151) from
+// 233; 65,536 of 360 761 -> 601 (601); the march of 4,096 194 -> 121 (121).
+// 2,048 envs of 100 beams on small maps 26.7 with the run walk, 24.9 with bytes.
+constexpr int kAutoByteCells = 24 << 10;  // byte copies up to this size take the byte walk
+
+void auto_tuning(const navsim_s *h, int max_words_row, navsim_tuning &t) {
+    const int64_t tiles = ((int64_t)h->cfg.num_envs + 31) / 32;
+    t = navsim_tuning{};
+    t.tile_envs = 32;
+    t.groups = 16;
+    t.balance = 1;
+    t.threads = tiles <= h->cus / 2 ? 1024 : 512;
+    t.walk = t.threads == 1024 && max_words_row * 32 <= kAutoByteCells ? 4 : 5;
+    t.refill_at = t.walk == 4 ? 40 : 32;
+}
+
+navsim_tuning default_tuning() {
+    navsim_tuning t{};
+    t.tile_envs = kDefaultTileEnvs;
+    t.refill_at = kDefaultRefillAt;
+    t.groups = kDefaultGroups;
+    t.walk = kDefaultWalk;
+    t.threads = 256;
+    return t;
+}
+
+navsim_tuning current_tuning(const navsim_s *h) {
+    return navsim_tuning{h->tile_envs, h->refill_at, h->groups, h->ray_slots, h->walk_mode,
+                         h->persist, h->wg_threads, h->balance};
+}
+
+void store_tuning(navsim_s *h, const navsim_tuning &t) {
+    h->tile_envs = t.tile_envs;
+    h->refill_at = t.refill_at;
+    h->groups = t.groups;
+    h->ray_slots = t.ray_slots;
+    h->walk_mode = t.walk;
+    h->persist = t.persist;
+    h->wg_threads = t.threads;
+    h->balance = t.balance;
+}
+
+// The handle's launch shape for these maps and scan mode, and its LDS layout: the
+// one set, or the automatic one, with the bitmap walk and then the default's
+// tiles of 8 envs where it does not fit LDS.
+navsim_status pick_shape(const navsim_s *h, int max_words_row, int max_words_t, int max_clear,
+                         int scan_mode, navsim_tuning &t, FusedShape &out) {
+    const auto fits = [&] {
+        out = FusedShape{};
+        return fused_shape(h, max_words_row, max_words_t, max_clear, t.tile_envs, t.threads,
+                           t.ray_slots, t.walk, scan_mode, out);
+    };
+    t = h->tuned ? current_tuning(h) : default_tuning();
+    const navsim_status s = fits();  // what the default cannot hold stays refused
+    if (s != NAVSIM_OK || h->tuned) return s;
+    auto_tuning(h, max_words_row, t);
+    if (fits() == NAVSIM_OK) return NAVSIM_OK;
+    t.walk = kDefaultWalk;
+    if (fits() == NAVSIM_OK) return NAVSIM_OK;
+    t = default_tuning();
+    return fits();
+}
+
 void apply_shape(navsim_s *h, const FusedShape &f) {
     h->ray_cap = f.ray_cap;
     h->cell_bytes = f.cell_bytes;
@@ -499,6 +570,26 @@ void build_tiles(const std::vector<int32_t> &env_map, int tile_envs,
     order_tiles_by_xcd(tiles, map_weight);
 }
 
+// The loaded envs regrouped for a launch shape, which becomes the handle's (waits
+// for the device: launches in flight read the old tiles).
+navsim_status retile(navsim_s *h, const navsim_tuning &t, const FusedShape &shape) {
+    std::vector<int32_t> perm;
+    std::vector<Tile> tiles;
+    build_tiles(h->host_env_map, t.tile_envs, h->host_map_weight, t.balance, shape.resident, perm,
+                tiles);
+    NS_HIP(hipDeviceSynchronize());
+    (void)hipFree(h->perm);
+    (void)hipFree(h->tiles);
+    h->perm = nullptr;
+    h->tiles = nullptr;
+    navsim_status s;
+    if ((s = upload(&h->perm, perm)) != NAVSIM_OK) return s;
+    if ((s = upload(&h->tiles, tiles)) != NAVSIM_OK) return s;
+    h->num_tiles = (int)tiles.size();
+    store_tuning(h, t);
+    return NAVSIM_OK;
+}
+
 navsim_status run(navsim_t h, const StepParams &p, int kernel, hipStream_t s) {
     DeviceGuard g(h->device);
     if (g.err != hipSuccess) return fail(NAVSIM_E_HIP, "hipSetDevice: %s", hipGetErrorString(g.err));
@@ -721,11 +812,13 @@ navsim_status navsim_create(const navsim_config *cfg, int hip_device, navsim_t *
     if (hipDeviceGetAttribute(&h->lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock,
                               hip_device) != hipSuccess ||
         hipDeviceGetAttribute(&h->lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
-                              hip_device) != hipSuccess) {
+                              hip_device) != hipSuccess ||
+        hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, hip_device) !=
+            hipSuccess) {
         (void)hipFree(h->step_ctr);
         (void)hipFree(h->state_buf);
         delete h;
-        return fail(NAVSIM_E_HIP, "LDS size query failed");
+        return fail(NAVSIM_E_HIP, "device query failed");
     }
     h->lds_block = std::max(h->lds_block, 65536);
     h->lds_cu = std::max(h->lds_cu, h->lds_block);
@@ -912,10 +1005,11 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     }
 
     FusedShape shape;
+    navsim_tuning tuning;
     {
         DeviceGuard g(h->device);
-        const navsim_status fs = fused_shape(h, max_words, max_words_t, max_clear, h->tile_envs,
-                                             h->wg_threads, h->ray_slots, h->walk_mode, h->scan_mode, shape);
+        const navsim_status fs =
+            pick_shape(h, max_words, max_words_t, max_clear, h->scan_mode, tuning, shape);
         if (fs != NAVSIM_OK) return fs;
     }
     std::vector<int32_t> host_env_map(env_map, env_map + N);
@@ -928,7 +1022,8 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
                                 : 0.0;
     std::vector<int32_t> perm;
     std::vector<Tile> tiles;
-    build_tiles(host_env_map, h->tile_envs, map_weight, h->balance, shape.resident, perm, tiles);
+    build_tiles(host_env_map, tuning.tile_envs, map_weight, tuning.balance, shape.resident, perm,
+                tiles);
 
     DeviceGuard g(h->device);
     if (g.err != hipSuccess) return fail(NAVSIM_E_HIP, "hipSetDevice: %s", hipGetErrorString(g.err));
@@ -951,6 +1046,7 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     h->max_words = max_words;
     h->max_words_t = max_words_t;
     h->max_clear = max_clear;
+    store_tuning(h, tuning);
     apply_shape(h, shape);
     h->host_env_map.swap(host_env_map);
     h->host_map_weight.swap(map_weight);
@@ -1112,15 +1208,20 @@ navsim_status navsim_set_scan(navsim_t h, int32_t mode, float step_m) {
         while (kmax > 0 && (double)kmax * hh > rmax) --kmax;
     }
     FusedShape shape;
+    navsim_tuning tuning;
     if (h->loaded) {
         DeviceGuard g(h->device);
-        const navsim_status fs = fused_shape(h, h->max_words, h->max_words_t, h->max_clear,
-                                             h->tile_envs, h->wg_threads, h->ray_slots,
-                                             h->walk_mode, mode, shape);
+        const navsim_status fs = pick_shape(h, h->max_words, h->max_words_t, h->max_clear, mode,
+                                            tuning, shape);
         if (fs != NAVSIM_OK) return fs;
         if (shape.clear && !h->clear) {
             const navsim_status cs = build_clearance(h, h->host_descs);
             if (cs != NAVSIM_OK) return cs;
+        }
+        const navsim_tuning now = current_tuning(h);
+        if (memcmp(&now, &tuning, sizeof now) != 0) {
+            const navsim_status ts = retile(h, tuning, shape);
+            if (ts != NAVSIM_OK) return ts;
         }
     }
     {
@@ -1171,30 +1272,13 @@ navsim_status navsim_set_tuning(navsim_t h, const navsim_tuning *t) {
         }
     }
     if (h->loaded) {
-        std::vector<int32_t> perm;
-        std::vector<Tile> tiles;
-        build_tiles(h->host_env_map, t->tile_envs, h->host_map_weight, t->balance, shape.resident,
-                    perm, tiles);
         DeviceGuard g(h->device);
         if (g.err != hipSuccess) return fail(NAVSIM_E_HIP, "hipSetDevice: %s", hipGetErrorString(g.err));
-        NS_HIP(hipDeviceSynchronize());
-        (void)hipFree(h->perm);
-        (void)hipFree(h->tiles);
-        h->perm = nullptr;
-        h->tiles = nullptr;
-        navsim_status s;
-        if ((s = upload(&h->perm, perm)) != NAVSIM_OK) return s;
-        if ((s = upload(&h->tiles, tiles)) != NAVSIM_OK) return s;
-        h->num_tiles = (int)tiles.size();
+        const navsim_status ts = retile(h, *t, shape);
+        if (ts != NAVSIM_OK) return ts;
     }
-    h->tile_envs = t->tile_envs;
-    h->refill_at = t->refill_at;
-    h->groups = t->groups;
-    h->ray_slots = t->ray_slots;
-    h->walk_mode = t->walk;
-    h->persist = t->persist;
-    h->wg_threads = t->threads;
-    h->balance = t->balance;
+    store_tuning(h, *t);
+    h->tuned = true;
     if (h->loaded) apply_shape(h, shape);
     return NAVSIM_OK;
 }
@@ -1202,14 +1286,7 @@ navsim_status navsim_set_tuning(navsim_t h, const navsim_tuning *t) {
 navsim_status navsim_get_tuning(navsim_t h, navsim_tuning *t) {
     if (!h) return fail(NAVSIM_E_BAD_HANDLE, "handle is NULL");
     if (!t) return fail(NAVSIM_E_INVALID_ARG, "tuning is NULL");
-    t->tile_envs = h->tile_envs;
-    t->refill_at = h->refill_at;
-    t->groups = h->groups;
-    t->ray_slots = h->ray_slots;
-    t->walk = h->walk_mode;
-    t->persist = h->persist;
-    t->threads = h->wg_threads;
-    t->balance = h->balance;
+    *t = current_tuning(h);
     return NAVSIM_OK;
 }
 

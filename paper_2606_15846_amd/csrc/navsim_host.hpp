@@ -71,6 +71,8 @@ struct navsim_s {
     int balance = 0;       // tiles sized per map by estimated scan work
     int cell_bytes = 0;    // walk 2, 4: LDS bytes of the byte-per-cell map copy
     int claim = 0;         // walk 3, 4 with the exact traversal: claim walk, no ray slots
+    bool tuned = false;    // a launch shape was set (navsim_set_tuning)
+    int cus = 256;         // compute units of the device
     int lds_block = 65536, lds_cu = 65536;  // device LDS bytes per workgroup and per CU
     int resident = 0;   // workgroups of the fused step resident at once on the device
     int32_t *queue = nullptr;  // device {next tile, finished workgroups}, zero between launches

@@ -739,3 +739,38 @@ def test_march_passes_free_samples_exactly(case):
         for k in runs[0]:
             assert np.array_equal(runs[0][k], other[k]), k
     assert runs[0]["visits"].max() > 1
+
+
+# (envs, maps, side, beams, sectors, scan): both sides of the automatic launch
+# shape's rules (4,096 and 4,097 envs on 256 CUs; byte copies up to 24 KiB: 128 and
+# 160 cells a side), sector pools and maps that leave it no room, the march
+@pytest.mark.parametrize("n,m,side,beams,sectors,scan",
+                         [(1, 1, 64, 36, 36, 0), (4096, 5, 128, 20, 10, 0), (4097, 5, 128, 20, 10, 0),
+                          (300, 7, 160, 90, 30, 0), (40, 2, 96, 1080, 1080, 0),
+                          (24, 1, 600, 720, 720, 0), (40, 2, 96, 540, 540, 1),
+                          (300, 7, 160, 90, 30, 1)])
+def test_automatic_launch_shape_agrees_with_plain(n, m, side, beams, sectors, scan):
+    from workloads import maps as gm
+    cfg = configs.make_config(num_envs=n, num_beams=beams, num_sectors=sectors,
+                              fov_rad=2 * math.pi, max_range_m=5.0, dt_s=0.1, footprint=0,
+                              radius_m=0.15, v_min=0.0, v_max=0.5, w_min=-1.0, w_max=1.0, horizon=3)
+    occ = [gm.gen_rect_disc_map(70 + k, w=side + 3 * k, h=side - k) for k in range(m)]
+    sims = [NavSim(cfg, occ, [0.05] * m, configs.contiguous_env_map(n, m), device=0) for _ in "ab"]
+    for sim in sims:
+        if scan:
+            sim.set_scan(navsim.NAVSIM_SCAN_MARCH, 0.03)
+        sim.reset()
+    say(f"{n} envs, {m} maps of about {side}, {beams}/{sectors}: {sims[0].get_tuning()}")
+    assert torch.equal(sims[0].obs, sims[1].obs)
+    acts = torch.from_numpy(configs.uniform_actions(4, n, seed=5)).cuda()
+    for t in range(4):
+        a = [v.clone() for v in sims[0].step(acts[t])[:4]]
+        b = sims[1].step(acts[t], plain=True)[:4]
+        torch.cuda.synchronize()
+        for x, y in zip(a, b):
+            assert torch.equal(x, y), t
+    sa, sb = (sim.get_state() for sim in sims)
+    for k in sa:
+        assert np.array_equal(sa[k], sb[k]), k
+    for sim in sims:
+        sim.close()
