@@ -570,6 +570,12 @@ void build_tiles(const std::vector<int32_t> &env_map, int tile_envs,
     order_tiles_by_xcd(tiles, map_weight);
 }
 
+int largest_tile(const std::vector<Tile> &tiles) {
+    int n = 0;
+    for (const Tile &t : tiles) n = std::max(n, t.count);
+    return n;
+}
+
 // The loaded envs regrouped for a launch shape, which becomes the handle's (waits
 // for the device: launches in flight read the old tiles).
 navsim_status retile(navsim_s *h, const navsim_tuning &t, const FusedShape &shape) {
@@ -586,6 +592,7 @@ navsim_status retile(navsim_s *h, const navsim_tuning &t, const FusedShape &shap
     if ((s = upload(&h->perm, perm)) != NAVSIM_OK) return s;
     if ((s = upload(&h->tiles, tiles)) != NAVSIM_OK) return s;
     h->num_tiles = (int)tiles.size();
+    h->tile_max = largest_tile(tiles);
     store_tuning(h, t);
     return NAVSIM_OK;
 }
@@ -769,6 +776,8 @@ StepParams navsim::make_step_params(const navsim_s *h) {
     p.chunk = h->persist;
     p.resident = h->resident;
     p.wg_threads = h->wg_threads;
+    p.tile_envs = h->tile_envs;
+    p.tile_max = h->tile_max;
     p.march_kmax = h->march_kmax;
     p.march_h = h->march_h;
     return p;
@@ -1043,6 +1052,7 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     if ((s = upload(&h->tiles, tiles)) != NAVSIM_OK) return s;
     h->num_maps = num_maps;
     h->num_tiles = (int)tiles.size();
+    h->tile_max = largest_tile(tiles);
     h->max_words = max_words;
     h->max_words_t = max_words_t;
     h->max_clear = max_clear;

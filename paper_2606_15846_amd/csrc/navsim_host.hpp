@@ -57,6 +57,7 @@ struct navsim_s {
     int32_t *perm = nullptr;
     navsim::Tile *tiles = nullptr;
     int num_maps = 0, num_tiles = 0, max_words = 0;
+    int tile_max = 0;  // envs of the largest tile
     int max_words_t = 0;  // largest transposed bitmap (staged beside the bitmap by walk 5)
     uint32_t *clear = nullptr;  // clearance pool, built when the march is first selected
     int max_clear = 0;          // largest map's clearance words

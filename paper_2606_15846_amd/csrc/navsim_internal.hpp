@@ -86,6 +86,7 @@ struct StepParams {
     int32_t chunk;              // persistent workgroups: tiles taken at a time
     int32_t resident;           // persistent workgroups: how many stay resident on the device
     int32_t wg_threads;         // fused step: threads per workgroup (256, 512, 1024)
+    int32_t tile_envs, tile_max;  // fused step: most envs of a tile, by the launch shape and in fact
     int32_t ray_cap;            // rays walked per chunk (LDS slots)
     int32_t beams_lds;          // stage the beam table in LDS
     int32_t scan_mode;          // 0 exact traversal, 1 fixed-step march

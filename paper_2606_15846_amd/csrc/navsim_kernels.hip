@@ -738,6 +738,17 @@ __device__ __forceinline__ void wait_job_ready(const int *s_misc, int job, int E
         __builtin_amdgcn_s_sleep(1);
 }
 
+// Early walk (fused_early_kernel): the number of reset jobs, whose rays come last
+// in claim order, is known once the `movers` wavefronts have all counted themselves
+// finished in s_misc[2], each after the reset jobs it appended (count s_misc[0],
+// list entries, poses).  The wait ends: a mover's work has bounded loops and no
+// barrier, and it is done before that wavefront claims rays.
+__device__ __forceinline__ int reset_jobs(const int *s_misc, int movers) {
+    while (__hip_atomic_load(s_misc + 2, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < movers)
+        __builtin_amdgcn_s_sleep(1);
+    return __builtin_amdgcn_readfirstlane(s_misc[0]);
+}
+
 // The 16 ballot bits of this lane's group of 16.
 __device__ __forceinline__ uint32_t group_ballot(bool pred) {
     const uint64_t b = __ballot(pred);
@@ -1535,16 +1546,19 @@ __device__ __forceinline__ void group_walk(const StepParams &p, const MapView &M
 // the walk of each ray it claims (the job's origin, the rotated beam) and
 // folds the ray's range into the sector pool once it is done.  The tile then
 // needs no ray slots, no chunks and no separate setup and finish passes, and
-// that work overlaps other wavefronts' walks.
-template <bool BYTES>
+// that work overlaps other wavefronts' walks.  movers >= 0 (the early walk): R counts
+// the main jobs' rays alone, the reset jobs' are added when those are used up.
+template <bool BYTES, bool EARLY>
 __device__ __forceinline__ void claim_walk(const StepParams &p, const MapView &M,
                                            const uint32_t *s_bits, const uint8_t *s_cells,
                                            const TileJob *s_jobs, const int *s_list,
                                            const double2 *s_beam, uint32_t *s_pool, int *s_misc,
                                            int R, int K, float inv_K, int per, float inv_per,
-                                           double rmax_c, int max_n, int E, int lane) {
+                                           double rmax_c, int max_n, int E, int lane,
+                                           int movers = 0) {
     int g = -1, job = 0, beam = 0;
     bool act = false, exhausted = false;
+    const int Rm = R;
     uint64_t S = 0, Dx = 0, Dy = 0;  // walk state and the two crossing steps (see walk_run)
     int n = 0, rem = 0, Bh = 0;
     uint32_t flags = 0u;
@@ -1566,11 +1580,12 @@ __device__ __forceinline__ void claim_walk(const StepParams &p, const MapView &M
             base = __builtin_amdgcn_readfirstlane(base);
             const int my = (int)__builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(idle >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)idle, (uint32_t)base));
+            if (EARLY && base + nidle >= Rm) R = Rm + reset_jobs(s_misc, movers) * K;
             if (!act && my < R) {
                 g = my;
                 const int jl = claim_decode(M, base, g, K, inv_K, beam);
                 job = s_list[jl];
-                wait_job_ready(s_misc, job, E);
+                if (!EARLY) wait_job_ready(s_misc, job, E);
                 const TileJob &j = job_ref(s_jobs, job);
                 n = 0;
                 if (!j.blocked) {
@@ -1699,16 +1714,18 @@ __device__ __forceinline__ void run_windows(const StepParams &p, const uint32_t 
 // The claim walk (see claim_walk) over runs: each claimed ray is set up for
 // run_windows, and a hit found in the transposed bitmap is turned back into
 // the bitmap's cell index for walk_result.
+template <bool EARLY>
 __device__ __forceinline__ void claim_run_walk(const StepParams &p, const MapView &M,
                                                const uint32_t *s_bits,
                                                const TileJob *s_jobs, const int *s_list,
                                                const double2 *s_beam, uint32_t *s_pool,
                                                int *s_misc, int R, int K, float inv_K, int per,
                                                float inv_per, double rmax_c, int max_n, int E,
-                                               int lane) {
+                                               int lane, int movers = 0) {
     const int pitch_t = M.pitch_t;
     int g = -1, job = 0, beam = 0;
     bool act = false, exhausted = false, xmaj = true;
+    const int Rm = R;
     RunRay c{};
     int X = 0, e = 0, pend = 0, n = 0, rem = 0, Xh = 0;
     uint32_t flags = 0u;
@@ -1737,11 +1754,12 @@ __device__ __forceinline__ void claim_run_walk(const StepParams &p, const MapVie
             base = __builtin_amdgcn_readfirstlane(base);
             const int my = (int)__builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(idle >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)idle, (uint32_t)base));
+            if (EARLY && base + nidle >= Rm) R = Rm + reset_jobs(s_misc, movers) * K;
             if (!act && my < R) {
                 g = my;
                 const int jl = claim_decode(M, base, g, K, inv_K, beam);
                 job = s_list[jl];
-                wait_job_ready(s_misc, job, E);
+                if (!EARLY) wait_job_ready(s_misc, job, E);
                 const TileJob &j = job_ref(s_jobs, job);
                 n = 0;
                 if (!j.blocked) {
@@ -1805,13 +1823,59 @@ __device__ __forceinline__ void claim_run_walk(const StepParams &p, const MapVie
 // reset jobs published, [2E + 6] tile vote, [2E + 7] next tile of a
 // persistent workgroup), beams [K] when staged, ray slots
 // [ray_cap] (none for the claim walk).
-template <int E>
-__device__ __forceinline__ int *fused_list(const StepParams &p) {
+__device__ __forceinline__ int *fused_list(const StepParams &p, int E) {
     extern __shared__ uint4 smem4[];
     uint32_t *s_bits = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(smem4) + p.cell_bytes);
     TileJob *s_jobs = reinterpret_cast<TileJob *>(s_bits + p.max_words);
     uint32_t *s_pool = reinterpret_cast<uint32_t *>(s_jobs + 2 * E);
     return reinterpret_cast<int *>(s_pool + pool_words(E, p.m));
+}
+
+template <int T>
+__device__ __forceinline__ void stage_bits(const StepParams &p, const MapDesc &md, uint32_t *s_bits,
+                                           int tid) {
+    const uint4 *g = reinterpret_cast<const uint4 *>(p.bits + md.word_off);
+    uint4 *b4 = reinterpret_cast<uint4 *>(s_bits);
+    for (int q = tid; q < md.words / 4; q += T) b4[q] = g[q];
+}
+
+template <int T>
+__device__ __forceinline__ void stage_transposed(const StepParams &p, const MapDesc &md,
+                                                 uint32_t *s_bits, int tid) {
+    const uint4 *gt = reinterpret_cast<const uint4 *>(p.bits + md.word_off_t);
+    uint4 *t4 = reinterpret_cast<uint4 *>(s_bits + p.tbits_off);
+    for (int q = tid; q < md.words_t / 4; q += T) t4[q] = gt[q];
+}
+
+// Byte copy: bit b of word q becomes byte 32 q + b (0 or 1); a nibble times
+// 0x00204081 moves its bit i to bit 8 i.
+template <int T>
+__device__ __forceinline__ void stage_bytes(const StepParams &p, const MapDesc &md, uint8_t *s_cells,
+                                            int tid) {
+    const uint32_t *gw = p.bits + md.word_off;
+    uint4 *c4 = reinterpret_cast<uint4 *>(s_cells);
+    for (int q = tid; q < md.words; q += T) {
+        const uint32_t w = gw[q];
+        uint32_t d[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) d[j] = (((w >> (4 * j)) & 0xFu) * 0x00204081u) & 0x01010101u;
+        c4[2 * q] = make_uint4(d[0], d[1], d[2], d[3]);
+        c4[2 * q + 1] = make_uint4(d[4], d[5], d[6], d[7]);
+    }
+}
+
+// Pooled sector minima of the listed jobs to their observation rows.
+template <int T>
+__device__ __forceinline__ void store_rows(const StepParams &p, const TileJob *s_jobs,
+                                           const int *s_list, const uint32_t *s_pool, int nj,
+                                           int tid) {
+    const int m = p.m;
+    for (int q = tid; q < nj * m; q += T) {
+        const int jl = q / m, sec = q - jl * m;
+        const TileJob &j = s_jobs[s_list[jl]];
+        float *dst = j.dst == 0 ? p.obs : (j.dst == 1 ? p.final_obs : nullptr);
+        if (dst) dst[(int64_t)j.env * (m + 4) + sec] = __uint_as_float(s_pool[s_list[jl] * m + sec]);
+    }
 }
 
 // One tile with a workgroup of T threads (T / 64 wavefronts).  SKIP: the march with
@@ -1825,7 +1889,7 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
     uint32_t *s_bits = reinterpret_cast<uint32_t *>(s_cells + p.cell_bytes);
     TileJob *s_jobs = reinterpret_cast<TileJob *>(s_bits + p.max_words);
     uint32_t *s_pool = reinterpret_cast<uint32_t *>(s_jobs + 2 * E);
-    int *s_list = fused_list<E>(p);
+    int *s_list = fused_list(p, E);
     int *s_misc = s_list + 2 * E;
     double2 *s_beam = reinterpret_cast<double2 *>(s_misc + 2 * E + 8);  // [K] beams, or global
     uint4 *s_ray = reinterpret_cast<uint4 *>(s_beam + (p.beams_lds ? p.K : 0));  // [ray_cap]
@@ -1872,33 +1936,14 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
         }
     }
     if (tile.map != staged_map) {  // a persistent workgroup keeps its map between tiles
-        const uint4 *g = reinterpret_cast<const uint4 *>(p.bits + md.word_off);
-        uint4 *b4 = reinterpret_cast<uint4 *>(s_bits);
-        for (int q = tid; q < md.words / 4; q += T) b4[q] = g[q];
-        if (!SKIP && p.tbits_off) {
-            const uint4 *gt = reinterpret_cast<const uint4 *>(p.bits + md.word_off_t);
-            uint4 *t4 = reinterpret_cast<uint4 *>(s_bits + p.tbits_off);
-            for (int q = tid; q < md.words_t / 4; q += T) t4[q] = gt[q];
-        }
+        stage_bits<T>(p, md, s_bits, tid);
+        if (!SKIP && p.tbits_off) stage_transposed<T>(p, md, s_bits, tid);
         if (SKIP) {
             const uint4 *gc = reinterpret_cast<const uint4 *>(p.clear + md.clr_off);
             uint4 *c4 = reinterpret_cast<uint4 *>(s_bits + p.clear_off);
             for (int q = tid; q < md.clr_words / 4; q += T) c4[q] = gc[q];
         }
-        if (!SKIP && p.cell_bytes) {
-            // byte copy: bit b of word q becomes byte 32 q + b (0 or 1); a
-            // nibble times 0x00204081 moves its bit i to bit 8 i
-            const uint32_t *gw = p.bits + md.word_off;
-            uint4 *c4 = reinterpret_cast<uint4 *>(s_cells);
-            for (int q = tid; q < md.words; q += T) {
-                const uint32_t w = gw[q];
-                uint32_t d[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) d[j] = (((w >> (4 * j)) & 0xFu) * 0x00204081u) & 0x01010101u;
-                c4[2 * q] = make_uint4(d[0], d[1], d[2], d[3]);
-                c4[2 * q + 1] = make_uint4(d[4], d[5], d[6], d[7]);
-            }
-        }
+        if (!SKIP && p.cell_bytes) stage_bytes<T>(p, md, s_cells, tid);
         if (p.beams_lds)
             for (int q = tid; q < K; q += T) s_beam[q] = beams[q];
         staged_map = tile.map;
@@ -2042,13 +2087,13 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
     if (!SKIP && p.claim) {
         // s_misc[1] (next ray) and the pool were cleared before the last barrier
         if (p.tbits_off)
-            claim_run_walk(p, M, s_bits, s_jobs, s_list, s_beam, s_pool, s_misc, R,
+            claim_run_walk<false>(p, M, s_bits, s_jobs, s_list, s_beam, s_pool, s_misc, R,
                            K, inv_K, per, inv_per, rmax_c, max_n, E, lane);
         else if (p.cell_bytes)
-            claim_walk<true>(p, M, s_bits, s_cells, s_jobs, s_list, s_beam, s_pool, s_misc, R, K,
+            claim_walk<true, false>(p, M, s_bits, s_cells, s_jobs, s_list, s_beam, s_pool, s_misc, R, K,
                              inv_K, per, inv_per, rmax_c, max_n, E, lane);
         else
-            claim_walk<false>(p, M, s_bits, s_cells, s_jobs, s_list, s_beam, s_pool, s_misc, R,
+            claim_walk<false, false>(p, M, s_bits, s_cells, s_jobs, s_list, s_beam, s_pool, s_misc, R,
                               K, inv_K, per, inv_per, rmax_c, max_n, E, lane);
         __syncthreads();
     }
@@ -2103,13 +2148,163 @@ __device__ __forceinline__ void fused_tile(const StepParams &p, int tile_index, 
         __syncthreads();
     }
 
-    // ---- pooled sector minima -> observation rows ----
-    for (int q = tid; q < nj * m; q += T) {
-        const int jl = q / m, sec = q - jl * m;
-        const TileJob &j = s_jobs[s_list[jl]];
-        float *dst = j.dst == 0 ? p.obs : (j.dst == 1 ? p.final_obs : nullptr);
-        if (dst) dst[(int64_t)j.env * (m + 4) + sec] = __uint_as_float(s_pool[s_list[jl] * m + sec]);
+    store_rows<T>(p, s_jobs, s_list, s_pool, nj, tid);
+}
+
+constexpr int kEarlyThreads = 1024;
+
+// The step (not a reset pass) with a claim walk, in workgroups of 1024 threads whose
+// envs occupy at most a quarter of the wavefronts: one such workgroup fills a CU, so
+// nothing else ran there while a few wavefronts worked out the motion (2 to 3 us).
+// Here the walk starts on the other wavefronts as soon as the new poses are known;
+// collisions, goal features, rewards and reset poses are worked out beside it.  A
+// kernel per walk, so that none carries the others' registers.  us a step, before
+// and now: 16 envs of 36 rays 11.3, 10.6; 4096 envs of 360 rays 51.0, 50.2; 16384
+// envs (tiles of 8) on bytes 240, 228, on runs 243, 233.
+template <int WALK>
+__global__ __launch_bounds__(kEarlyThreads) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerSimd)))
+void fused_early_kernel(StepParams p) {
+    constexpr int T = kEarlyThreads;
+    const int E = p.tile_envs;
+    extern __shared__ uint4 smem4[];
+    uint8_t *s_cells = reinterpret_cast<uint8_t *>(smem4);
+    uint32_t *s_bits = reinterpret_cast<uint32_t *>(s_cells + p.cell_bytes);
+    TileJob *s_jobs = reinterpret_cast<TileJob *>(s_bits + p.max_words);
+    uint32_t *s_pool = reinterpret_cast<uint32_t *>(s_jobs + 2 * E);
+    int *s_list = fused_list(p, E);
+    int *s_misc = s_list + 2 * E;
+    double2 *s_beam = reinterpret_cast<double2 *>(s_misc + 2 * E + 8);  // [K] beams, or global
+    const int tid = threadIdx.x, lane = tid & 63;
+    const Tile tile = p.tiles[blockIdx.x];
+    const MapDesc md = p.maps[tile.map];
+    const int K = md.K, m = p.m, per = K / m;
+    const double2 *beams = p.beams + md.beam_off;  // this map's beam directions
+    const int grp = tid >> 4, li = tid & 15;
+    const bool mover = grp < tile.count;
+    int me = 0, mt = 0;
+    uint32_t mep = 0u;
+    float2 ma = make_float2(0.0f, 0.0f);
+    float mx = 0.0f, my = 0.0f, mth = 0.0f, mgx = 0.0f, mgy = 0.0f, mdprev = 0.0f;
+    if (mover) {
+        me = p.perm[tile.first + grp];
+        mep = p.st.ep[me];
+        ma = env_action(p, me);
+        mx = p.st.x[me];
+        my = p.st.y[me];
+        mth = p.st.th[me];
+        mgx = p.st.gx[me];
+        mgy = p.st.gy[me];
+        mdprev = p.st.dprev[me];
+        mt = p.st.t[me] + 1;
     }
+    stage_bits<T>(p, md, s_bits, tid);
+    if (WALK == 5) stage_transposed<T>(p, md, s_bits, tid);
+    if (WALK == 4) stage_bytes<T>(p, md, s_cells, tid);
+    if (p.beams_lds)
+        for (int q = tid; q < K; q += T) s_beam[q] = beams[q];
+    if (!p.beams_lds) s_beam = const_cast<double2 *>(beams);
+    for (int q = tid; q < 2 * E * m; q += T) s_pool[q] = 0x7f800000u;  // +inf
+    if (tid < 3) s_misc[tid] = 0;
+    // the new poses, while other wavefronts stage; the tile waits for them, and its
+    // end for the rest of the motion: let the movers win issue slots from the walks
+    // on the same SIMD
+    const int movers = (tile.count + 3) >> 2;  // wavefronts with an env of the tile
+    if (grp < 4 * movers) __builtin_amdgcn_s_setprio(3);
+    Motion mo{};
+    double c1 = 1.0, sn1 = 0.0;
+    if (mover) {
+        mo = apply_action(p, ma.x, ma.y, mx, my, mth);
+        sincos((double)mo.th1, &sn1, &c1);
+    }
+    __syncthreads();
+    const MapView M = map_view(s_bits, md);
+    // every env's new pose is a job; its rays need nothing else, so the walk starts
+    // as soon as the jobs are there
+    const int nmain = tile.count;
+    if (mover && li == 0) make_tile_job(s_jobs[grp], M, mo.x1, mo.y1, c1, sn1, me, 0);
+    if (tid < nmain) s_list[tid] = tid;
+    __syncthreads();
+
+    // ---- the rest of the motion: one group of 16 lanes per env, in the first
+    // `movers` wavefronts; the others start walking ----
+    if (grp < 4 * movers) {
+        bool done = false, defer = false;
+        if (mover) {
+            const int e = me;
+            const int t = mt;
+            if (p.act_out && li == 0)
+                *reinterpret_cast<float2 *>(p.act_out + 2 * (int64_t)e) = ma;
+            const double x1 = (double)mo.x1, y1 = (double)mo.y1;
+            const bool coll = group_footprint_hits(M, robot_of(md), x1, y1, c1, sn1, li);
+            double d64;
+            float d32, phi;
+            goal_features(x1, y1, c1, sn1, mgx, mgy, d64, d32, phi);
+            const bool goal = d64 < (double)p.goal_r;
+            const bool term = goal || coll;
+            const bool trunc = (t >= p.horizon) && !term;
+            done = term || trunc;
+            defer = done && p.defer_bin && p.defer_bin[e] >= 0;
+            if (li == 0) {
+                if (p.defer_out) p.defer_out[e] = (uint8_t)defer;
+                const float rew =
+                    goal ? p.r_succ
+                         : (coll ? p.r_coll
+                                 : (float)((double)p.c1 * ((double)mdprev - (double)d32)));
+                p.reward[e] = rew;
+                p.term[e] = (uint8_t)term;
+                p.trunc[e] = (uint8_t)trunc;
+                if (p.d_coll) p.d_coll[e] = (uint8_t)coll;
+                if (p.d_goal) p.d_goal[e] = (uint8_t)goal;
+                if (p.d_reset) p.d_reset[e] = (uint8_t)done;
+                if (p.d_fb) p.d_fb[e] = 0;
+                float *row = done ? p.final_obs : p.obs;
+                if (row) {
+                    row += (int64_t)e * (m + 4);
+                    row[m] = d32;
+                    row[m + 1] = phi;
+                    row[m + 2] = mo.v;
+                    row[m + 3] = mo.w;
+                }
+                s_jobs[grp].dst = done ? (p.final_obs ? 1 : 2) : 0;
+                if (!done) {
+                    p.st.x[e] = mo.x1;
+                    p.st.y[e] = mo.y1;
+                    p.st.th[e] = mo.th1;
+                    p.st.v[e] = mo.v;
+                    p.st.w[e] = mo.w;
+                    p.st.dprev[e] = d32;
+                    p.st.t[e] = t;
+                }
+            }
+        }
+        if (done && !defer) {
+            // a done env's reset pose, drawn by its group of 16 lanes
+            double c = 1.0, sn = 0.0;
+            const ResetPose r = group_sample_reset(p, M, md, me, mep, li, c, sn);
+            if (li == 0) {
+                store_reset_cs(p, me, mep, r, c, sn);
+                make_tile_job(s_jobs[E + grp], M, r.x, r.y, c, sn, me, 0);
+                s_list[nmain + atomicAdd(&s_misc[0], 1)] = E + grp;
+            }
+        }
+        // this wavefront's jobs are in place (its lanes' writes precede in order)
+        if (lane == 0)
+            __hip_atomic_fetch_add(s_misc + 2, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_s_setprio(0);
+    }
+
+    // ---- scan ----
+    const float inv_K = 1.0f / (float)K, inv_per = 1.0f / (float)per;
+    const double rmax_c = walk_cells((double)p.rmax, M.s);
+    const int max_n = M.w + M.h + 2 * kPad;  // a walk meets the padding ring before this
+    if constexpr (WALK == 5)
+        claim_run_walk<true>(p, M, s_bits, s_jobs, s_list, s_beam, s_pool, s_misc, nmain * K, K, inv_K,
+                             per, inv_per, rmax_c, max_n, E, lane, movers);
+    else
+        claim_walk<WALK == 4, true>(p, M, s_bits, s_cells, s_jobs, s_list, s_beam, s_pool, s_misc,
+                                    nmain * K, K, inv_K, per, inv_per, rmax_c, max_n, E, lane, movers);
+    __syncthreads();
+    store_rows<T>(p, s_jobs, s_list, s_pool, nmain + s_misc[0], tid);
 }
 
 // One workgroup per tile (Q false), or persistent workgroups (Q true) that
@@ -2129,7 +2324,7 @@ void fused_step_kernel(StepParams p) {
         fused_tile<E, T, SKIP>(p, (int)blockIdx.x, staged);
         return;
     }
-    int *s_next = fused_list<E>(p) + 4 * E + 7;
+    int *s_next = fused_list(p, E) + 4 * E + 7;
     for (;;) {
         if (threadIdx.x == 0) *s_next = atomicAdd(&p.queue[0], p.chunk);
         __syncthreads();
@@ -2257,25 +2452,28 @@ __global__ __launch_bounds__(64) void plain_step_kernel(StepParams p) {
 }
 
 // ---------------------------------------------------------------------------
+// Dynamic LDS beyond 64 KiB (gfx950 allows up to 160 KiB per workgroup), raised once
+// per device and size.
+constexpr int kLdsDevices = 64;
+static hipError_t raise_lds(const void *kernel, std::atomic<int> *raised, size_t lds) {
+    if (lds <= 65536u) return hipSuccess;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < kLdsDevices && (int)lds <= raised[dev].load()) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess && dev >= 0 && dev < kLdsDevices) raised[dev].store((int)lds);
+    return e;
+}
+
 template <int E, int T, bool Q, bool SKIP>
 static hipError_t launch_fused_etq(const StepParams &p, hipStream_t s) {
     const size_t lds = fused_lds_bytes(p.max_words, p.m, E, p.beams_lds ? p.K : 0,
                                        p.claim ? 0 : p.ray_cap, p.cell_bytes);
-    if (lds > 65536u) {
-        // dynamic LDS beyond 64 KiB (gfx950 allows up to 160 KiB per workgroup),
-        // raised once per device and size
-        constexpr int kDevices = 64;
-        static std::atomic<int> raised[kDevices];
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= kDevices || (int)lds > raised[dev].load()) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(fused_step_kernel<E, T, Q, SKIP>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            if (dev >= 0 && dev < kDevices) raised[dev].store((int)lds);
-        }
-    }
+    static std::atomic<int> raised[kLdsDevices];
+    const hipError_t e = raise_lds(
+        reinterpret_cast<const void *>(fused_step_kernel<E, T, Q, SKIP>), raised, lds);
+    if (e != hipSuccess) return e;
     unsigned grid = (unsigned)p.num_tiles;
     if (p.queue) {
         // at most the resident workgroups, and one per chunk of tiles
@@ -2283,6 +2481,19 @@ static hipError_t launch_fused_etq(const StepParams &p, hipStream_t s) {
         grid = (unsigned)std::max(1, std::min(chunks, p.resident));
     }
     hipLaunchKernelGGL((fused_step_kernel<E, T, Q, SKIP>), dim3(grid), dim3(T), lds, s, p);
+    return hipGetLastError();
+}
+
+template <int WALK>
+static hipError_t launch_early(const StepParams &p, hipStream_t s) {
+    static std::atomic<int> raised[kLdsDevices];
+    const size_t lds =
+        fused_lds_bytes(p.max_words, p.m, p.tile_envs, p.beams_lds ? p.K : 0, 0, p.cell_bytes);
+    const hipError_t e =
+        raise_lds(reinterpret_cast<const void *>(fused_early_kernel<WALK>), raised, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fused_early_kernel<WALK>), dim3((unsigned)p.num_tiles), dim3(kEarlyThreads), lds,
+                       s, p);
     return hipGetLastError();
 }
 
@@ -2361,6 +2572,19 @@ int fused_ray_cap(int max_words, int m, int E, int K, bool beams_lds, int budget
 
 hipError_t launch_fused(const StepParams &p, int tile_envs, hipStream_t s) {
     if (p.num_tiles == 0) return hipSuccess;
+    // The walk beside the motion (fused_early_kernel).  us a step of 16384 envs of 360
+    // rays, by threads and envs of a tile, without and with it: runs 1024/8 243, 233,
+    // 1024/16 193, 191, 1024/32 166, 170, 512/8 189, 196, 256/4 189, 199; bytes 1024/32
+    // 172, 172, 256/16 529, 540.  Smaller workgroups share a CU and fill each other's
+    // motion with walks already; half a workgroup's wavefronts are too many to hold
+    // back.  Without final rows an env that ends needs no walk, and only the motion
+    // tells which end.
+    if (p.mode == 0 && p.claim && !p.queue && p.wg_threads == kEarlyThreads &&
+        p.tile_max * kGroupLanes * 4 <= kEarlyThreads &&
+        (p.final_obs || p.d_ranges || p.d_hits || p.d_visits))
+        return p.walk_mode == 5   ? launch_early<5>(p, s)
+               : p.walk_mode == 4 ? launch_early<4>(p, s)
+                                  : launch_early<3>(p, s);
 #define NAVSIM_X(e, t) \
     if (tile_envs == e && p.wg_threads == t) return launch_fused_et<e, t>(p, s);
     NAVSIM_FUSED_SHAPES(NAVSIM_X)

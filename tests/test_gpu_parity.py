@@ -774,3 +774,37 @@ def test_automatic_launch_shape_agrees_with_plain(n, m, side, beams, sectors, sc
         assert np.array_equal(sa[k], sb[k]), k
     for sim in sims:
         sim.close()
+
+
+# 1024 threads: up to 16 envs of a tile the walk starts beside the motion, from 17 on
+# after it; every env ends in every second step.
+@pytest.mark.parametrize("walk", [3, 4, 5])
+@pytest.mark.parametrize("n,m,tile", [(1, 1, 1), (13, 2, 8), (32, 2, 16), (33, 2, 32), (34, 2, 32)])
+def test_walk_beside_motion_agrees_with_plain(walk, n, m, tile):
+    from workloads import maps as gm
+    cfg = configs.make_config(num_envs=n, num_beams=60, num_sectors=12, fov_rad=2 * math.pi,
+                              max_range_m=3.0, dt_s=0.1, footprint=0, radius_m=0.15, v_min=0.0,
+                              v_max=0.5, w_min=-1.0, w_max=1.0, horizon=2)
+    occ = [gm.gen_rect_disc_map(90 + k, w=70 + 3 * k, h=66 - k) for k in range(m)]
+    sims = [NavSim(cfg, occ, [0.05] * m, configs.contiguous_env_map(n, m), device=0) for _ in "ab"]
+    sims[0].set_tuning(tile, 32, 16, 0, walk, 0, 1024, 0)
+    for sim in sims:
+        sim.reset()
+    assert torch.equal(sims[0].obs, sims[1].obs)
+    acts = torch.from_numpy(configs.uniform_actions(5, n, seed=8)).cuda()
+    for t in range(5):
+        for sim in sims:
+            sim.final_obs.zero_()
+        a = [v.clone() for v in sims[0].step(acts[t])[:4]] + [sims[0].final_obs]
+        b = list(sims[1].step(acts[t], plain=True)[:4]) + [sims[1].final_obs]
+        torch.cuda.synchronize()
+        for x, y in zip(a, b):
+            assert torch.equal(x, y), t
+        g, sa = gpu_step(sims[0], acts[t].cpu().numpy(), NAVSIM_KERNEL_FUSED)
+        r, sb = gpu_step(sims[1], acts[t].cpu().numpy(), navsim.NAVSIM_KERNEL_PLAIN)
+        for k in g:
+            assert np.array_equal(g[k], r[k]) or k == "final_obs", (t, k)
+        for k in sa:
+            assert np.array_equal(sa[k], sb[k]), (t, k)
+    for sim in sims:
+        sim.close()
