@@ -113,6 +113,20 @@ bool disc_clear_host(const uint8_t *occ, int W, int H, double s, double x, doubl
     return true;
 }
 
+// Cells of a map at whose centres the footprint's circumscribed disc is clear, in
+// row order.  On its own: within navsim_load_maps_ex the loop's registers go to the
+// (a load of 64 maps of 256 x 256 cells 185 to 230 ms, 143 on its own).
+__attribute__((noinline)) void append_free_cells(const uint8_t *occ, int W, int H, double s,
+                                                 double rc, std::vector<int32_t> &out) {
+    for (int iy = 0; iy < H; ++iy)
+        for (int ix = 0; ix < W; ++ix) {
+            const float cx = (float)(((double)ix + 0.5) * s);
+            const float cy = (float)(((double)iy + 0.5) * s);
+            if (disc_clear_host(occ, W, H, s, (double)cx, (double)cy, rc))
+                out.push_back(iy * W + ix);
+        }
+}
+
 void drop_graph(navsim_s *h) {
     if (h->graph) (void)hipGraphExecDestroy(h->graph);
     h->graph = nullptr;
@@ -1000,14 +1014,7 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
         clear_words += d.clr_words;
         max_clear = std::max(max_clear, d.clr_words);
         d.free_off = (int64_t)free_cells.size();
-        const double s = (double)res_m[k];
-        for (int iy = 0; iy < H; ++iy)
-            for (int ix = 0; ix < W; ++ix) {
-                const float cx = (float)(((double)ix + 0.5) * s);
-                const float cy = (float)(((double)iy + 0.5) * s);
-                if (disc_clear_host(m, W, H, s, (double)cx, (double)cy, d.rc))
-                    free_cells.push_back(iy * W + ix);
-            }
+        append_free_cells(m, W, H, (double)res_m[k], d.rc, free_cells);
         d.free_cnt = (int32_t)((int64_t)free_cells.size() - d.free_off);
         if (used[k] && d.free_cnt == 0)
             return fail(NAVSIM_E_NO_FREE_SPACE, "map %d has no cell where the footprint fits", k);

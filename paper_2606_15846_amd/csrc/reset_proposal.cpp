@@ -570,6 +570,15 @@ void detach_rp(navsim_rp_s *r) {
     r->at = navsim_rp_s::Attach{};
 }
 
+// The 16 even-numbered bits of a word side by side.
+uint32_t even_bits(uint32_t w) {
+    w &= 0x55555555u;
+    w = (w | (w >> 1)) & 0x33333333u;
+    w = (w | (w >> 2)) & 0x0f0f0f0fu;
+    w = (w | (w >> 4)) & 0x00ff00ffu;
+    return (w | (w >> 8)) & 0xffffu;
+}
+
 }  // namespace
 
 extern "C" {
@@ -642,9 +651,15 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
             }
             const int i = fl[q] - first;
             row[j * d.wpr + (i >> 5)] |= 1u << (i & 31);
-            if (d.pk > 0)
-                pk[((i + j) & 1) * d.pwords + j * d.pk + (i >> 6)] |= 1u << ((i >> 1) & 31);
         }
+        // cell i of row j is cell i / 2 of the row in colour (i + j) mod 2
+        for (int q = 0; q < (d.pk > 0 ? H : 0); ++q)
+            for (int wd = 0; wd < d.wpr; ++wd) {
+                const uint32_t w = row[q * d.wpr + wd];
+                uint32_t *at = pk + q * d.pk + (wd >> 1);
+                at[(q & 1) * d.pwords] |= even_bits(w) << (16 * (wd & 1));
+                at[(~q & 1) * d.pwords] |= even_bits(w >> 1) << (16 * (wd & 1));
+            }
         const uint8_t *occ = h->host_occ.data() + h->host_occ_off[k];
         for (int q = 0; q < 32; ++q)
             for (int p = 0; p < 32; ++p) {
