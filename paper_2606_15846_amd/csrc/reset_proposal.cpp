@@ -956,8 +956,10 @@ navsim_status navsim_rp_propose_noalloc(navsim_rp_t r, int32_t n, const int32_t 
     DeviceGuard dg(r->device);
     ProposeWork w;
     uint8_t *base = (uint8_t *)r->scratch;
-    // the pending list takes part of what the other parts leave, if it fits
-    const size_t tb = tail_bytes(n, proposals, max_tries);
+    // the pending list takes part of what the other parts leave, if it fits; the
+    // rejection sampler alone keeps off the array, which every proposer of the
+    // device shares (such a call may overlap another)
+    const size_t tb = proposals > 0 ? tail_bytes(n, proposals, max_tries) : 0;
     if (tb > 0 && need + tb <= kRpScratchBytes) w.pend = base + need;
     if (proposals > 0) {
         // carve the fixed workspace in the order noalloc_bytes() counts it

@@ -1,0 +1,64 @@
+"""Proposal calls as programs overlap and capture them: rejection-only calls of
+two proposers on two streams."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_15846_amd.navsim import NavSim
+from paper_2606_15846_amd.reset_proposal import ResetProposer
+from workloads import configs
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("pose", "hops", "source", "checks")
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def make_sim(num_maps=4):
+    w = configs.build_workload("c5", num_envs=64)
+    return NavSim(w["cfg"], w["maps"][:num_maps], w["res"][:num_maps],
+                  (np.arange(64) % num_maps).astype(np.int32), device=0), w["proposer"]
+
+
+def requests(n, seed, num_maps=4):
+    r = np.random.default_rng(seed)
+    q = [r.integers(0, num_maps, n), r.integers(0, 8, n), r.integers(0, 1 << 20, n),
+         r.integers(0, 50, n)]
+    return [torch.from_numpy(v.astype(np.int32)).cuda() for v in q]
+
+
+def outputs(n):
+    z = dict(device="cuda", dtype=torch.int32)
+    return dict(pose=torch.zeros(n, 5, device="cuda"), hops=torch.zeros(n, **z),
+                source=torch.zeros(n, **z), checks=torch.zeros(n, **z))
+
+
+def same(a, b):
+    return all(torch.equal(a[k], b[k]) for k in KEYS)
+
+
+def test_overlapping_rejection_only_noalloc_calls():
+    """Two proposers' rejection-only noalloc calls of different sizes, in flight on
+    two streams at once, give what each gives alone."""
+    sim, cfg = make_sim()
+    rps = [ResetProposer(sim, **dict(cfg, seed=s)) for s in (5, 6)]
+    reqs = [requests(2000, 1), requests(150, 2)]
+    say("rejection-only noalloc proposals: 2,000 and 150 requests on two streams")
+    alone = [rp.propose_into(*q, 0, 64, outputs(q[0].numel())) for rp, q in zip(rps, reqs)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in rps]
+    got = [[outputs(q[0].numel()) for _ in range(4)] for q in reqs]
+    torch.cuda.synchronize()
+    for t in range(4):
+        for s, rp, q, o in zip(streams, rps, reqs, got):
+            with torch.cuda.stream(s):
+                rp.propose_into(*q, 0, 64, o[t], noalloc=True)
+    torch.cuda.synchronize()
+    for a, o in zip(alone, got):
+        assert all(same(a, x) for x in o)
+    for rp in rps:
+        rp.close()
+    sim.close()

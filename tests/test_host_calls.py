@@ -1,0 +1,26 @@
+"""What the library's host code asks of the HIP runtime, on the CPU (see
+stand_in.py): which kernels a call launches, what it allocates, frees and waits
+for, and what is left when an allocation fails."""
+import pytest
+
+from tests import stand_in
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("stand_in")
+    return lambda body: stand_in.run(tmp, body)
+
+
+def test_rejection_only_noalloc_calls_keep_nothing_on_the_device(run):
+    """The rejection sampler alone takes nothing from the array that all proposers
+    of a device share: one launch, no count, list or second launch."""
+    run("""
+    r = proposer(handle(8, [(256, 256)] * 3))
+    for n in (1, 31, 200, 3000, 8192):
+        for tries in (0, 1, 16, 64, 5000):
+            clear()
+            assert propose(r, n, 0, tries, noalloc=True) == 0
+            assert launches() == ["propose_kernel<%d>" % (8 if n <= 2048 else 4)], (n, tries)
+            assert counts()[1:4] == (0, 0, 0)
+    """)
