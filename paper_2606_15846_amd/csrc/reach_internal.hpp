@@ -104,7 +104,6 @@ struct NoiseArgs {
     const int32_t *n_dev = nullptr;  // optional: requests = min(n, *n_dev) read on the device
     int32_t *clear = nullptr;  // optional: a count set to 0 for the launches that follow
 };
-hipError_t launch_clear_count(int32_t *count, hipStream_t s);
 hipError_t launch_noise(const NoiseArgs &a, uint32_t key0, uint32_t key1, hipStream_t s);
 
 // Requests of the envs that deferred their reset in a step: in env order,

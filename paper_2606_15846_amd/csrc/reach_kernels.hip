@@ -971,10 +971,6 @@ __global__ void noise_kernel(NoiseArgs a, uint32_t key0, uint32_t key1) {
     }
 }
 
-__global__ void clear_count_kernel(int32_t *count) {
-    if (threadIdx.x == 0) *count = 0;
-}
-
 __global__ void pool_rows_kernel(int num_maps, int nbins, const float *pool, uint16_t *rows) {
     const int width = kPoolCells + nbins;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1210,11 +1206,6 @@ hipError_t launch_noise(const NoiseArgs &a, uint32_t key0, uint32_t key1, hipStr
     const int64_t total = (int64_t)a.n * a.per * ((a.nz + 3) / 4);
     if (total <= 0) return hipSuccess;
     hipLaunchKernelGGL(noise_kernel, dim3(nblocks(total, 256)), dim3(256), 0, s, a, key0, key1);
-    return hipGetLastError();
-}
-
-hipError_t launch_clear_count(int32_t *count, hipStream_t s) {
-    hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(64), 0, s, count);
     return hipGetLastError();
 }
 

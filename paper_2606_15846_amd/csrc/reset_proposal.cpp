@@ -411,16 +411,17 @@ int64_t tail_rounds_of(int32_t n, int32_t proposals, int32_t max_tries) {
 }
 
 // Bytes of the tail launch's pending count, list, best candidates and round
-// slots; 0 for a call whose requests' workgroups rather check every round: with
-// one round left its place does not matter (2 rounds of 16 attempts, 128
-// requests: 139 us, with a tail 172); a few requests with network draws mostly
-// end in their first rounds, and the two launches cost more than the slowest
-// one's rounds (32 draws, 64 attempts: 64 requests 176 against 207 us, 128
-// requests 290 against 236; without draws the tail pays from 32 requests,
-// 293 against 151 us); and 2^22 slots (64 MiB) bound the workspace.
+// slots; 0 for a call whose requests' workgroups rather check every round.  The
+// rejection sampler alone has no workspace: its calls may be captured, run with
+// no memory left, and overlap (in the fixed array too, which every proposer of a
+// device shares).  With one round left its place does not matter (2 rounds of 16
+// attempts, 128 requests: 139 us, with a tail 172); a few requests mostly end in
+// their first rounds, and the two launches cost more than the slowest one's
+// rounds (32 draws, 64 attempts: 64 requests 176 against 207 us, 128 requests 290
+// against 236); and 2^22 slots (64 MiB) bound the workspace.
 size_t tail_bytes(int32_t n, int32_t proposals, int32_t max_tries) {
     const int64_t rounds = tail_rounds_of(n, proposals, max_tries);
-    if (rounds < 2 || (proposals > 0 && n < 128) || (int64_t)n * rounds > (1 << 22)) return 0;
+    if (proposals <= 0 || rounds < 2 || n < 128 || (int64_t)n * rounds > (1 << 22)) return 0;
     return 256 + 2 * align_up((size_t)n * 4) + (size_t)(n * rounds) * 16;
 }
 
@@ -477,7 +478,6 @@ navsim_status propose_run(navsim_rp_s *r, int32_t n, const int32_t *map, const i
         pa.pend = (int32_t *)(w.pend + 256);
         pa.best = (int32_t *)(w.pend + 256 + align_up((size_t)n * 4));
         pa.tail = (int4 *)(w.pend + 256 + 2 * align_up((size_t)n * 4));
-        if (proposals == 0) RP_HIP(launch_clear_count(pa.n_pend, s));
     }
     RP_HIP(launch_propose(r->rp, pa, s));
     if (tail_rounds > 0) RP_HIP(launch_propose_tail(r->rp, pa, tail_rounds, s));
@@ -956,10 +956,8 @@ navsim_status navsim_rp_propose_noalloc(navsim_rp_t r, int32_t n, const int32_t 
     DeviceGuard dg(r->device);
     ProposeWork w;
     uint8_t *base = (uint8_t *)r->scratch;
-    // the pending list takes part of what the other parts leave, if it fits; the
-    // rejection sampler alone keeps off the array, which every proposer of the
-    // device shares (such a call may overlap another)
-    const size_t tb = proposals > 0 ? tail_bytes(n, proposals, max_tries) : 0;
+    // the pending list takes part of what the other parts leave, if it fits
+    const size_t tb = tail_bytes(n, proposals, max_tries);
     if (tb > 0 && need + tb <= kRpScratchBytes) w.pend = base + need;
     if (proposals > 0) {
         // carve the fixed workspace in the order noalloc_bytes() counts it

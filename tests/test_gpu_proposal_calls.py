@@ -1,5 +1,4 @@
-"""Proposal calls as programs overlap and capture them: rejection-only calls of
-two proposers on two streams."""
+"""Proposal calls as programs overlap them on streams and capture them into graphs."""
 import numpy as np
 import pytest
 import torch
@@ -61,4 +60,28 @@ def test_overlapping_rejection_only_noalloc_calls():
         assert all(same(a, x) for x in o)
     for rp in rps:
         rp.close()
+    sim.close()
+
+
+def test_rejection_only_proposals_captured_first():
+    """A proposer's first rejection-only call can be captured into a graph; every
+    replay gives the eager call's pairs, eager calls in between."""
+    sim, cfg = make_sim()
+    rp = ResetProposer(sim, **cfg)
+    q = requests(300, 3)
+    got = outputs(300)
+    torch.cuda.synchronize()
+    say("rejection-only proposal captured: 300 requests")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rp.propose_into(*q, 0, 64, got)
+    want = rp.propose_into(*q, 0, 64, outputs(300))
+    for t in range(3):
+        for v in got.values():
+            v.zero_()
+        graph.replay()
+        rp.propose_into(*requests(500, t), 0, 16, outputs(500))
+        torch.cuda.synchronize()
+        assert same(got, want), t
+    rp.close()
     sim.close()

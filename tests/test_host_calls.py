@@ -24,3 +24,19 @@ def test_rejection_only_noalloc_calls_keep_nothing_on_the_device(run):
             assert launches() == ["propose_kernel<%d>" % (8 if n <= 2048 else 4)], (n, tries)
             assert counts()[1:4] == (0, 0, 0)
     """)
+
+
+def test_rejection_only_proposals_need_no_workspace(run):
+    """Rejection-only calls allocate nothing and work during a stream capture and
+    with no device memory left: one launch each, whatever their size."""
+    run("""
+    r = proposer(handle(8, [(256, 256)] * 3))
+    R.stand_in_capturing(1)
+    R.stand_in_fail_malloc(0)
+    for n in (1, 31, 200, 3000, 8192):
+        for tries in (0, 16, 64, 5000):
+            clear()
+            assert propose(r, n, 0, tries) == 0, lib.navsim_last_error()
+            assert launches() == ["propose_kernel<%d>" % (8 if n <= 2048 else 4)], (n, tries)
+            assert counts()[1:4] == (0, 0, 0)
+    """)
