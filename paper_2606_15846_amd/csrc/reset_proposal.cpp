@@ -112,7 +112,7 @@ struct navsim_rp_s {
     } at;
     // workspaces
     DevBuf ctable, x, hid[4], y, dzf, dzb, lrows, zc, ridx, yc, hc[2],
-        bmap, bbin, target, chosen, zp, rp_idx, yp, pend;
+        bmap, bbin, target, chosen, zp, rp_idx, yp;
 };
 
 namespace {
@@ -135,7 +135,7 @@ void free_rp(navsim_rp_s *r) {
     DevBuf *bufs[] = {&r->ctable, &r->x, &r->hid[0], &r->hid[1], &r->hid[2],
                       &r->hid[3], &r->y, &r->dzf, &r->dzb, &r->lrows,
                       &r->zc, &r->ridx, &r->yc, &r->hc[0], &r->hc[1], &r->bmap, &r->bbin,
-                      &r->target, &r->chosen, &r->zp, &r->rp_idx, &r->yp, &r->pend};
+                      &r->target, &r->chosen, &r->zp, &r->rp_idx, &r->yp};
     for (DevBuf *b : bufs) b->release();
 }
 
@@ -410,19 +410,34 @@ int64_t tail_rounds_of(int32_t n, int32_t proposals, int32_t max_tries) {
     return std::max<int64_t>(0, rounds - propose_head_rounds(n));
 }
 
-// Bytes of the tail launch's pending count, list, best candidates and round
-// slots; 0 for a call whose requests' workgroups rather check every round.  The
-// rejection sampler alone has no workspace: its calls may be captured, run with
-// no memory left, and overlap (in the fixed array too, which every proposer of a
-// device shares).  With one round left its place does not matter (2 rounds of 16
-// attempts, 128 requests: 139 us, with a tail 172); a few requests mostly end in
-// their first rounds, and the two launches cost more than the slowest one's
-// rounds (32 draws, 64 attempts: 64 requests 176 against 207 us, 128 requests 290
-// against 236); and 2^22 slots (64 MiB) bound the workspace.
+// Bytes of the tail launch's pending count, list, best candidates and round slots.
+size_t tail_list_bytes(int64_t n, int64_t slots) {
+    return 256 + 2 * align_up((size_t)n * 4) + (size_t)slots * 16;
+}
+
+// Room for them behind a call's network outputs, by its draws R alone: what a call
+// allocates does not depend on its number of attempts (see tail_bytes).
+constexpr int64_t kTailSlots = 1 << 22, kTailSlotsPerDraw = 64;
+
+size_t tail_room(int64_t R) {
+    return tail_list_bytes(std::min(R, kTailSlots / 2), std::min(R * kTailSlotsPerDraw, kTailSlots));
+}
+
+// Bytes of the tail launch's list for a call, 0 for one whose requests' workgroups
+// rather check every round.  The rejection sampler alone has no workspace: its
+// calls may be captured, run with no memory left, and overlap (in the fixed array
+// too, which every proposer of a device shares).  With one round left its place
+// does not matter (2 rounds of 16 attempts, 128 requests: 139 us, with a tail 172);
+// a few requests mostly end in their first rounds, and the two launches cost more
+// than the slowest one's rounds (32 draws, 64 attempts: 64 requests 176 against
+// 207 us, 128 requests 290 against 236); 2^22 slots (64 MiB) and 64 slots a draw
+// (500 attempts behind a single draw) bound the workspace.
 size_t tail_bytes(int32_t n, int32_t proposals, int32_t max_tries) {
     const int64_t rounds = tail_rounds_of(n, proposals, max_tries);
-    if (proposals <= 0 || rounds < 2 || n < 128 || (int64_t)n * rounds > (1 << 22)) return 0;
-    return 256 + 2 * align_up((size_t)n * 4) + (size_t)(n * rounds) * 16;
+    if (proposals <= 0 || rounds < 2 || n < 128 || n * rounds > kTailSlots ||
+        rounds > kTailSlotsPerDraw * proposals)
+        return 0;
+    return tail_list_bytes(n, n * rounds);
 }
 
 // Fixed-workspace bytes of a call with n requests x `proposals` draws (0
@@ -915,10 +930,12 @@ navsim_status navsim_rp_propose(navsim_rp_t r, int32_t n, const int32_t *map, co
     if (proposals > 0) {
         const int64_t R = (int64_t)n * proposals;
         const int Hd = hidden_width(r);
+        const size_t y_bytes = align_up((size_t)R * 5 * 4);
         RP_BUF(r->ctable, ctable_bytes(r));
-        RP_BUF(r->yp, (size_t)R * 5 * 4);
+        RP_BUF(r->yp, y_bytes + tail_room(R));
         w.ct = r->ctable.as<float>();
         w.y = r->yp.as<float>();
+        if (tail_bytes(n, proposals, max_tries) > 0) w.pend = r->yp.as<uint8_t>() + y_bytes;
         if (!one_launch(r)) {
             RP_BUF(r->zp, (size_t)R * r->cfg.noise_dim * 2);
             RP_BUF(r->rp_idx, (size_t)R * 4);
@@ -927,10 +944,6 @@ navsim_status navsim_rp_propose(navsim_rp_t r, int32_t n, const int32_t *map, co
             w.nw = NoiseWork{r->zp.as<uint16_t>(), r->rp_idx.as<int32_t>(),
                              r->hc[0].as<uint16_t>(), r->hc[1].as<uint16_t>()};
         }
-    }
-    if (const size_t tb = tail_bytes(n, proposals, max_tries)) {
-        RP_BUF(r->pend, tb);
-        w.pend = r->pend.as<uint8_t>();
     }
     return propose_run(r, n, map, bin, env, episode, proposals, max_tries, pose, hops, source,
                        checks, y_out, w, (hipStream_t)stream);

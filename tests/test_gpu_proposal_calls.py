@@ -85,3 +85,29 @@ def test_rejection_only_proposals_captured_first():
         assert same(got, want), t
     rp.close()
     sim.close()
+
+
+@pytest.mark.parametrize("hidden", [64, 256])
+def test_proposals_captured_with_more_attempts(hidden):
+    """A call with network draws is captured after one with as many draws and no
+    attempts has run; replays agree with the eager call, other calls in between."""
+    sim, cfg = make_sim()
+    rp = ResetProposer(sim, **dict(cfg, hidden=hidden))
+    q = requests(260, 4)
+    rp.propose_into(*q, 4, 0, outputs(260))
+    got = outputs(260)
+    torch.cuda.synchronize()
+    say(f"proposal captured: 260 requests of 4 draws and 64 attempts, hidden width {hidden}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rp.propose_into(*q, 4, 64, got)
+    want = rp.propose_into(*q, 4, 64, outputs(260))
+    for t in range(3):
+        for v in got.values():
+            v.zero_()
+        graph.replay()
+        rp.propose_into(*requests(200, t), 5, 300, outputs(200))
+        torch.cuda.synchronize()
+        assert same(got, want), t
+    rp.close()
+    sim.close()

@@ -40,3 +40,32 @@ def test_rejection_only_proposals_need_no_workspace(run):
             assert launches() == ["propose_kernel<%d>" % (8 if n <= 2048 else 4)], (n, tries)
             assert counts()[1:4] == (0, 0, 0)
     """)
+
+
+def test_more_attempts_need_no_more_workspace(run):
+    """The workspace of a call with network draws depends on requests times draws
+    alone, as its activations' does: once a call has run, one with the same draws
+    and any number of attempts can be captured, and a captured call's workspace
+    stays where it is."""
+    run("""
+    for hidden in (64, 256):
+        h = handle(8, [(256, 256)] * 3)
+        for n, proposals in ((1, 1), (100, 8), (128, 1), (256, 8), (2000, 32), (4096, 2), (70000, 1)):
+            r = proposer(h, hidden=hidden)
+            assert propose(r, n, proposals, 0) == 0
+            R.stand_in_capturing(1)
+            for tries in (16, 64, 100, 512, 5000, 100000):
+                clear()
+                assert propose(r, n, proposals, tries) == 0, (n, proposals, tries)
+                assert counts()[1:4] == (0, 0, 0), (n, proposals, tries)
+            # the usual calls are still split into head and tail launches
+            clear()
+            assert propose(r, n, proposals, 64) == 0
+            assert ("propose_final_kernel" in launches()) == (n >= 128), launches()
+            # fewer requests of as many draws in all
+            clear()
+            assert propose(r, max(1, n // 2), proposals, 64) == 0
+            assert counts()[1:4] == (0, 0, 0)
+            R.stand_in_capturing(0)
+            assert lib.navsim_rp_destroy(r) == 0
+    """)
