@@ -80,9 +80,11 @@ struct ProposeArgs {
     int4 *tail = nullptr;
 };
 // Candidates checked together per request (one per wavefront), and the rounds a
-// request's own workgroup checks before its other rounds go to the tail launch.
+// request's own workgroup checks before its other rounds go to the tail launch: in
+// a call of n requests, and inside a step, where n is the most there can be.
 int propose_width(int n);
 int propose_head_rounds(int n);
+constexpr int kProposeStepHeadRounds = 1;
 hipError_t launch_propose(const ReachParams &rp, const ProposeArgs &a, hipStream_t s);
 // The rounds head_rounds .. head_rounds + tail_rounds - 1 of the pending
 // requests (a.n = the most there can be), then their outputs.

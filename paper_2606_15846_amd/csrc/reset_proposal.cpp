@@ -402,12 +402,11 @@ struct ProposeWork {
 
 constexpr size_t align_up(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Rounds of a call's requests that its tail launch takes (0: none left after
-// the head rounds).
-int64_t tail_rounds_of(int32_t n, int32_t proposals, int32_t max_tries) {
+// Rounds of n requests left for a tail launch after `head` rounds.
+int64_t tail_rounds_of(int32_t n, int32_t proposals, int32_t max_tries, int head) {
     const int W = propose_width(n);
     const int64_t rounds = ((int64_t)proposals + max_tries + W - 1) / W;
-    return std::max<int64_t>(0, rounds - propose_head_rounds(n));
+    return std::max<int64_t>(0, rounds - head);
 }
 
 // Bytes of the tail launch's pending count, list, best candidates and round slots.
@@ -433,7 +432,7 @@ size_t tail_room(int64_t R) {
 // 207 us, 128 requests 290 against 236); 2^22 slots (64 MiB) and 64 slots a draw
 // (500 attempts behind a single draw) bound the workspace.
 size_t tail_bytes(int32_t n, int32_t proposals, int32_t max_tries) {
-    const int64_t rounds = tail_rounds_of(n, proposals, max_tries);
+    const int64_t rounds = tail_rounds_of(n, proposals, max_tries, propose_head_rounds(n));
     if (proposals <= 0 || rounds < 2 || n < 128 || n * rounds > kTailSlots ||
         rounds > kTailSlotsPerDraw * proposals)
         return 0;
@@ -486,9 +485,10 @@ navsim_status propose_run(navsim_rp_s *r, int32_t n, const int32_t *map, const i
     pa.hops = hops;
     pa.source = source;
     pa.checks = checks;
-    const int tail_rounds = w.pend ? (int)tail_rounds_of(n, proposals, max_tries) : 0;
+    const int head = propose_head_rounds(n);
+    const int tail_rounds = w.pend ? (int)tail_rounds_of(n, proposals, max_tries, head) : 0;
     if (tail_rounds > 0) {
-        pa.head_rounds = propose_head_rounds(n);
+        pa.head_rounds = head;
         pa.n_pend = (int32_t *)w.pend;
         pa.pend = (int32_t *)(w.pend + 256);
         pa.best = (int32_t *)(w.pend + 256 + align_up((size_t)n * 4));
@@ -562,9 +562,10 @@ navsim_status rp_hook_run(void *ctx, hipStream_t s) {
     // the few requests with no valid candidate in their head rounds set the
     // launch's time when their rounds run one after another: their remaining
     // rounds go to one tail launch, one workgroup per round
-    const int tail_rounds = (int)tail_rounds_of(A.cap, A.props, A.tries);
+    const int tail_rounds =
+        (int)tail_rounds_of(A.cap, A.props, A.tries, kProposeStepHeadRounds);
     if (tail_rounds > 0) {
-        pa.head_rounds = propose_head_rounds(A.cap);
+        pa.head_rounds = kProposeStepHeadRounds;
         pa.pend = A.pend;
         pa.n_pend = A.n_dev + 1;
         pa.best = A.best;
@@ -1088,7 +1089,8 @@ navsim_status navsim_rp_attach(navsim_rp_t r, const int32_t *bin, int32_t propos
     if (dg.err != hipSuccess) return fail(NAVSIM_E_HIP, "hipSetDevice: %s", hipGetErrorString(dg.err));
     navsim_rp_s::Attach &A = r->at;
     // rounds of candidates after the head rounds (one tail workgroup each)
-    const int tail_rounds = (int)tail_rounds_of(max_per_step, proposals, max_tries);
+    const int tail_rounds =
+        (int)tail_rounds_of(max_per_step, proposals, max_tries, kProposeStepHeadRounds);
     if ((int64_t)max_per_step * tail_rounds > (1 << 24))
         return fail(NAVSIM_E_INVALID_ARG, "max_per_step * candidate rounds must be at most 2^24");
     if (!(A.on && A.cap == max_per_step && A.props == proposals && A.tail_rounds >= tail_rounds)) {

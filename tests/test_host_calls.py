@@ -69,3 +69,22 @@ def test_more_attempts_need_no_more_workspace(run):
             R.stand_in_capturing(0)
             assert lib.navsim_rp_destroy(r) == 0
     """)
+
+
+def test_attach_limit_counts_every_round_after_the_first(run):
+    """navsim_rp_attach refuses more than 2^24 rounds of candidates after each
+    request's first, whatever the width of a round."""
+    run("""
+    h = handle(4096, [(256, 256)])
+    r = proposer(h)
+    bins = np.zeros(4096, np.int32)
+    attach = lambda proposals, tries, cap: lib.navsim_rp_attach(r, bins.ctypes.data, proposals, tries, cap)
+    # 4 candidates a round past 2,048 requests a step, 8 up to there
+    for cap, width in ((4096, 4), (2048, 8)):
+        most = width * ((1 << 24) // cap + 1)
+        assert attach(8, most - 8, cap) == 0
+        clear()
+        assert attach(8, most - 7, cap) == -1
+        assert counts().malloc == 0
+        assert lib.navsim_rp_detach(r) == 0
+    """)
