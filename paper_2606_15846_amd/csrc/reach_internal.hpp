@@ -47,6 +47,7 @@ struct ReachParams {
     double gmd2;             // smallest double whose square root is at least gmd
     int32_t max_pwords;      // largest pwords among the maps
     int32_t all_pair, all_label;  // pair_ok (label_ok) on every map
+    int32_t any_label;            // label_ok on some map
     uint32_t key0, key1;     // Philox key
 };
 

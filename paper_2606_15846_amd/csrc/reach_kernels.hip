@@ -207,8 +207,16 @@ __global__ __launch_bounds__(kReachThreads) void label_kernel(ReachParams rp, co
     const int mk = map[i];
     const ReachDesc d = rp.maps[(mk >= 0 && mk < rp.num_maps) ? mk : 0];
     const uint32_t sid = first_sid + (uint32_t)i;
-    // those without a start, and those of label_wave_kernel
-    if (d.free_cnt == 0 || mk < 0 || mk >= rp.num_maps || d.label_ok) return;
+    if (d.free_cnt == 0 || mk < 0 || mk >= rp.num_maps) {
+        if (rp.any_label) return;  // label_wave_kernel wrote these
+        if (tid < rp.nbins) {
+            goal[(int64_t)i * rp.nbins + tid] = -1;
+            hops[(int64_t)i * rp.nbins + tid] = -1;
+        }
+        if (tid == 0) start[i] = -1;
+        return;
+    }
+    if (d.label_ok) return;  // and those
     uint32_t *fb = lds, *vis = fb + kReachMaxWords, *fr = vis + kReachMaxWords,
              *nx = fr + kReachMaxWords;
     uint32_t c[4] = {sid, 0u, 0u, 6u};
@@ -1081,10 +1089,12 @@ size_t propose_lds(const ReachParams &rp) {
 hipError_t launch_label(const ReachParams &rp, int n, const int32_t *map, uint32_t first_sid,
                         int32_t *start, int32_t *goal, int32_t *hops, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(label_wave_kernel, dim3(nblocks(n, kLabelWaves)), dim3(64 * kLabelWaves), 0,
-                       s, rp, n, map, first_sid, start, goal, hops);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || rp.all_label) return e;
+    if (rp.any_label) {
+        hipLaunchKernelGGL(label_wave_kernel, dim3(nblocks(n, kLabelWaves)), dim3(64 * kLabelWaves),
+                           0, s, rp, n, map, first_sid, start, goal, hops);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || rp.all_label) return e;
+    }
     hipLaunchKernelGGL(label_kernel, dim3((unsigned)n), dim3(kReachThreads), kSearchLds, s, rp,
                        map, first_sid, start, goal, hops);
     return hipGetLastError();

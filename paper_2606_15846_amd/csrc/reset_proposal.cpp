@@ -807,10 +807,12 @@ navsim_status navsim_rp_create(navsim_t h, const navsim_rp_config *cfg, navsim_r
     while (rp.gmd2 > 0.0 && sqrt(rp.gmd2) >= rp.gmd) rp.gmd2 = nextafter(rp.gmd2, 0.0);
     while (sqrt(rp.gmd2) < rp.gmd) rp.gmd2 = nextafter(rp.gmd2, INFINITY);
     rp.all_pair = rp.all_label = 1;
+    rp.any_label = 0;
     rp.max_pwords = 0;
     for (const ReachDesc &d : descs) {
         rp.all_pair = rp.all_pair && d.pair_ok;
         rp.all_label = rp.all_label && d.label_ok;
+        rp.any_label = rp.any_label || d.label_ok;
         rp.max_pwords = std::max(rp.max_pwords, d.pwords);
     }
     rp.key0 = (uint32_t)(c.seed & 0xffffffffu);

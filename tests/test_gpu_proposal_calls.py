@@ -111,3 +111,23 @@ def test_proposals_captured_with_more_attempts(hidden):
         assert same(got, want), t
     rp.close()
     sim.close()
+
+
+def test_labels_of_wide_maps_alone_and_beside_others():
+    """Labels on maps that no register search holds, from a proposer of such maps
+    alone and from one that has others too; unknown maps get none from either."""
+    rng = np.random.default_rng(8)
+    occ = [(rng.random(s) < 0.02).astype(np.uint8) for s in ((40, 1040), (36, 1100), (60, 200))]
+    cfg = dict(configs.build_workload("c5", num_envs=6)["cfg"], radius_m=0.02)
+    ids = np.array([0, 1, -1, 1, 0, 7, 1])
+    got = []
+    for maps in (occ[:2], occ):
+        sim = NavSim(cfg, maps, [0.05] * len(maps), np.arange(6) % len(maps), device=0)
+        rp = ResetProposer(sim, d_lo_m=0.5, d_hi_m=6.0)
+        got.append({k: v.cpu().numpy() for k, v in rp.label(ids, first_sid=30).items()})
+        rp.close()
+        sim.close()
+    for k in got[0]:
+        assert np.array_equal(got[0][k], got[1][k]), k
+        assert (got[0][k][[2, 5]] == -1).all(), k
+    assert (got[0]["goal"][[0, 1, 3, 4, 6]] >= 0).mean() > 0.5

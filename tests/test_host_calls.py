@@ -88,3 +88,21 @@ def test_attach_limit_counts_every_round_after_the_first(run):
         assert counts().malloc == 0
         assert lib.navsim_rp_detach(r) == 0
     """)
+
+
+def test_labels_of_wide_maps_take_one_launch(run):
+    """Maps that no register search holds are labelled by one launch, mixed sets by
+    two, the others by one."""
+    run("""
+    def label(sides):
+        r = proposer(handle(8, sides))
+        m = np.arange(40, dtype=np.int32) % len(sides)
+        o = np.zeros((3, 40, 8), np.int32)
+        clear()
+        assert lib.navsim_rp_label(r, 40, m.ctypes.data, 0, *[o[i].ctypes.data for i in range(3)], None) == 0
+        assert counts()[1:4] == (0, 0, 0)
+        return launches()
+    assert label([(256, 256)] * 2) == ["label_wave_kernel"]
+    assert label([(1040, 40)] * 2) == ["label_kernel"]
+    assert label([(256, 256), (1040, 40)]) == ["label_wave_kernel", "label_kernel"]
+    """)
