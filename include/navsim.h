@@ -240,7 +240,12 @@ navsim_status navsim_rollout(navsim_t h, int32_t steps, uint64_t first_step, flo
  * (double precision) is occupied or outside the map ends the beam at
  * range = tau, else range = r_max; visits = samples evaluated.  It can step
  * over a cell the beam only clips.  Errors: INVALID_ARG (unknown mode,
- * step_m <= 0, r_max / step_m > 2^20).  Drops a captured rollout graph. */
+ * step_m <= 0, r_max / step_m > 2^20), UNSUPPORTED (the march's ray slots do
+ * not fit LDS).  Waits for nothing and leaves launches in flight, and captured
+ * ones, as they are; it may be called while a stream is captured.  The march
+ * first selected after navsim_load_maps puts the maps' clearances (half a byte
+ * per 2 x 2 cells) on the device; without the memory for them it evaluates every
+ * sample, with the same results.  Drops a captured rollout graph. */
 enum { NAVSIM_SCAN_TRAVERSAL = 0, NAVSIM_SCAN_MARCH = 1 };
 navsim_status navsim_set_scan(navsim_t h, int32_t mode, float step_m);
 
@@ -287,8 +292,8 @@ typedef struct {
                            at most tile_envs envs each.  Tiles always launch heaviest first */
 } navsim_tuning;
 
-/* Set the fused step's launch shape.  Until it is called, navsim_load_maps (and
- * navsim_set_scan) pick one for the number of envs and the maps' sizes; before
+/* Set the fused step's launch shape.  Until it is called, navsim_load_maps picks
+ * one for the number of envs and the maps' sizes, which holds either scan; before
  * maps are loaded navsim_get_tuning gives 8, 40, 8, 0, 3, 0, 256, 0.  Changing it
  * after navsim_load_maps waits for the device and re-groups the envs; returns
  * NAVSIM_E_UNSUPPORTED if the larger tile would not fit LDS. */

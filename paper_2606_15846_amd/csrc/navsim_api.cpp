@@ -209,7 +209,7 @@ int staged_words(int max_words, int max_words_t, int walk, int scan_mode) {
 // byte-per-cell copy, walk 5 the transposed bitmap.  Fails with UNSUPPORTED
 // when nothing fits.
 // The march stages the maps' clearances after the bitmaps where they fit beside
-// at least as many ray slots as there are threads.
+// at least as many ray slots as there are threads (max_clear 0: there are none).
 struct FusedShape {
     int ray_cap = 0, cell_bytes = 0, claim = 0, resident = 0;
     bool beams_lds = true, clear = false;
@@ -221,7 +221,7 @@ navsim_status fused_shape(const navsim_s *h, int max_words_row, int max_words_t,
     const navsim_config &c = h->cfg;
     const int m = c.num_sectors, K = c.num_beams;
     int max_words = staged_words(max_words_row, max_words_t, walk, scan_mode);
-    if (scan_mode == NAVSIM_SCAN_MARCH) {
+    if (scan_mode == NAVSIM_SCAN_MARCH && max_clear > 0) {
         bool beams = false;
         out.clear = choose_ray_cap(max_words + max_clear, c, tile_envs, threads, slots,
                                    h->lds_block, h->lds_cu, 0, beams) >= threads;
@@ -315,25 +315,46 @@ void store_tuning(navsim_s *h, const navsim_tuning &t) {
     h->balance = t.balance;
 }
 
-// The handle's launch shape for these maps and scan mode, and its LDS layout: the
-// one set, or the automatic one, with the bitmap walk and then the default's
-// tiles of 8 envs where it does not fit LDS.
+// The launch shape at load for these maps, and its LDS layout for the handle's scan
+// mode: the one set, or the automatic one.  That holds both scans (but one that the
+// default cannot hold, which stays refused), so that navsim_set_scan never
+// regroups the envs: launches in flight, and captured ones, keep reading the tiles.
+// Where it does not fit LDS: workgroups of 1,024 threads, which have a CU's LDS to
+// themselves, then smaller tiles, each first with its own walk and then the bitmap
+// walk (which the march does not use), and last the default's.  us a step, by the
+// default's tiles, 32 envs on 512 threads (a CU holds one such workgroup here) and
+// on 1,024: 20,000 envs of 720 beams in 360 sectors on 256 x 256 maps 609, 713, 504;
+// 8,192 of 180 in 180 on 600 x 600 156, 102, 82, and their march 1,104, -, 252.
 navsim_status pick_shape(const navsim_s *h, int max_words_row, int max_words_t, int max_clear,
-                         int scan_mode, navsim_tuning &t, FusedShape &out) {
-    const auto fits = [&] {
+                         navsim_tuning &t, FusedShape &out) {
+    const auto fits = [&](const navsim_tuning &q, int scan_mode) {
         out = FusedShape{};
-        return fused_shape(h, max_words_row, max_words_t, max_clear, t.tile_envs, t.threads,
-                           t.ray_slots, t.walk, scan_mode, out);
+        return fused_shape(h, max_words_row, max_words_t, max_clear, q.tile_envs, q.threads,
+                           q.ray_slots, q.walk, scan_mode, out);
     };
-    t = h->tuned ? current_tuning(h) : default_tuning();
-    const navsim_status s = fits();  // what the default cannot hold stays refused
-    if (s != NAVSIM_OK || h->tuned) return s;
-    auto_tuning(h, max_words_row, t);
-    if (fits() == NAVSIM_OK) return NAVSIM_OK;
-    t.walk = kDefaultWalk;
-    if (fits() == NAVSIM_OK) return NAVSIM_OK;
-    t = default_tuning();
-    return fits();
+    if (h->tuned) {
+        t = current_tuning(h);
+        return fits(t, h->scan_mode);
+    }
+    const int mode = h->scan_mode, other = 1 - mode;
+    const std::string message = g_err;  // shapes that do not fit are no failure of the call
+    const bool both = fits(default_tuning(), other) == NAVSIM_OK;
+    const navsim_status s = fits(t = default_tuning(), mode);
+    if (s != NAVSIM_OK) return s;  // what the default cannot hold stays refused
+    for (int e = 32; e >= 8; e /= 2)
+        for (const bool wide : {false, true})
+            for (const bool own_walk : {true, false}) {
+                auto_tuning(h, max_words_row, t);
+                t.tile_envs = e;
+                if (wide) t.threads = 1024;
+                if (!own_walk) t.walk = kDefaultWalk;
+                if ((!both || fits(t, other) == NAVSIM_OK) && fits(t, mode) == NAVSIM_OK) {
+                    g_err = message;
+                    return NAVSIM_OK;
+                }
+            }
+    g_err = message;
+    return fits(t = default_tuning(), mode);
 }
 
 void apply_shape(navsim_s *h, const FusedShape &f) {
@@ -345,9 +366,9 @@ void apply_shape(navsim_s *h, const FusedShape &f) {
     h->use_clear = f.clear;
 }
 
-// Clearances of the loaded maps (see MapDesc) into the device pool: chessboard
-// distance by two passes over the cells, outside counting as occupied.
-navsim_status build_clearance(navsim_s *h, const std::vector<MapDesc> &descs) {
+// Clearances of the loaded maps (see MapDesc): chessboard distance by two passes
+// over the cells, outside counting as occupied.
+std::vector<uint32_t> clearances(const navsim_s *h, const std::vector<MapDesc> &descs) {
     std::vector<uint32_t> pool;
     std::vector<uint8_t> dist;
     for (int k = 0; k < h->num_maps; ++k) {
@@ -381,7 +402,48 @@ navsim_status build_clearance(navsim_s *h, const std::vector<MapDesc> &descs) {
                 pool[(size_t)d.clr_off + (b >> 3)] |= (uint32_t)v << (4 * (b & 7));
             }
     }
-    return upload(&h->clear, pool);
+    return pool;
+}
+
+// The clearances into the device pool; false if they cannot be.  A scan may be
+// selected while a stream is captured: the thread's capture mode allows the
+// allocation, and the copy goes over a stream that waits for no other.
+bool build_clearance(navsim_s *h, const std::vector<MapDesc> &descs) {
+    std::vector<uint32_t> pool;
+    try {
+        pool = clearances(h, descs);
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    uint32_t *p = nullptr;
+    const size_t bytes = pool.size() * sizeof pool[0];
+    bool ok = h->capture_stream ||
+              hipStreamCreateWithFlags(&h->capture_stream, hipStreamNonBlocking) == hipSuccess;
+    ok = ok && hipMalloc((void **)&p, bytes) == hipSuccess;
+    ok = ok && hipMemcpyAsync(p, pool.data(), bytes, hipMemcpyHostToDevice, h->capture_stream) ==
+                   hipSuccess;
+    ok = ok && hipStreamSynchronize(h->capture_stream) == hipSuccess;
+    if (!ok && p) (void)hipFree(p);
+    if (!ok) (void)hipGetLastError();
+    if (ok) h->clear = p;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return ok;
+}
+
+// The LDS layout of launch shape t for the loaded maps and a scan mode, whose
+// clearances, if it takes them, are on the device (or left out when they cannot
+// be: the march then evaluates every sample).
+navsim_status loaded_shape(navsim_s *h, const navsim_tuning &t, int scan_mode, FusedShape &out) {
+    for (const int max_clear : {h->max_clear, 0}) {
+        out = FusedShape{};
+        const navsim_status s =
+            fused_shape(h, h->max_words, h->max_words_t, max_clear, t.tile_envs, t.threads,
+                        t.ray_slots, t.walk, scan_mode, out);
+        if (s != NAVSIM_OK || !out.clear || h->clear || build_clearance(h, h->host_descs)) return s;
+    }
+    return NAVSIM_OK;
 }
 
 // Envs grouped by map (stable in env order) into tiles of up to tile_envs envs,
@@ -1024,8 +1086,7 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     navsim_tuning tuning;
     {
         DeviceGuard g(h->device);
-        const navsim_status fs =
-            pick_shape(h, max_words, max_words_t, max_clear, h->scan_mode, tuning, shape);
+        const navsim_status fs = pick_shape(h, max_words, max_words_t, max_clear, tuning, shape);
         if (fs != NAVSIM_OK) return fs;
     }
     std::vector<int32_t> host_env_map(env_map, env_map + N);
@@ -1064,7 +1125,6 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     h->max_words_t = max_words_t;
     h->max_clear = max_clear;
     store_tuning(h, tuning);
-    apply_shape(h, shape);
     h->host_env_map.swap(host_env_map);
     h->host_map_weight.swap(map_weight);
     h->host_occ.assign(occ, occ + occ_off[num_maps]);
@@ -1082,7 +1142,8 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     }
     h->host_free.swap(free_cells);
     h->host_descs.swap(descs);
-    if (h->use_clear && (s = build_clearance(h, h->host_descs)) != NAVSIM_OK) return s;
+    if ((s = loaded_shape(h, tuning, h->scan_mode, shape)) != NAVSIM_OK) return s;
+    apply_shape(h, shape);
     h->loaded = true;
     return NAVSIM_OK;
 }
@@ -1225,21 +1286,16 @@ navsim_status navsim_set_scan(navsim_t h, int32_t mode, float step_m) {
         while (kmax > 0 && (double)kmax * hh > rmax) --kmax;
     }
     FusedShape shape;
-    navsim_tuning tuning;
     if (h->loaded) {
         DeviceGuard g(h->device);
-        const navsim_status fs = pick_shape(h, h->max_words, h->max_words_t, h->max_clear, mode,
-                                            tuning, shape);
+        navsim_status fs = NAVSIM_OK;
+        if (!h->tuned) {  // what the default shape cannot hold is refused
+            const navsim_tuning t = default_tuning();
+            fs = fused_shape(h, h->max_words, h->max_words_t, h->max_clear, t.tile_envs, t.threads,
+                             t.ray_slots, t.walk, mode, shape);
+        }
+        if (fs == NAVSIM_OK) fs = loaded_shape(h, current_tuning(h), mode, shape);
         if (fs != NAVSIM_OK) return fs;
-        if (shape.clear && !h->clear) {
-            const navsim_status cs = build_clearance(h, h->host_descs);
-            if (cs != NAVSIM_OK) return cs;
-        }
-        const navsim_tuning now = current_tuning(h);
-        if (memcmp(&now, &tuning, sizeof now) != 0) {
-            const navsim_status ts = retile(h, tuning, shape);
-            if (ts != NAVSIM_OK) return ts;
-        }
     }
     {
         DeviceGuard g(h->device);
@@ -1279,14 +1335,8 @@ navsim_status navsim_set_tuning(navsim_t h, const navsim_tuning *t) {
     FusedShape shape;
     if (h->loaded) {
         DeviceGuard g(h->device);
-        const navsim_status fs = fused_shape(h, h->max_words, h->max_words_t, h->max_clear,
-                                             t->tile_envs, t->threads, t->ray_slots, t->walk,
-                                             h->scan_mode, shape);
+        const navsim_status fs = loaded_shape(h, *t, h->scan_mode, shape);
         if (fs != NAVSIM_OK) return fs;
-        if (shape.clear && !h->clear) {
-            const navsim_status cs = build_clearance(h, h->host_descs);
-            if (cs != NAVSIM_OK) return cs;
-        }
     }
     if (h->loaded) {
         DeviceGuard g(h->device);

@@ -17,7 +17,7 @@ static struct { const void *f; const char *name; } kernels[MAX_KERNELS];
 static int n_kernels;
 static const char *launches[MAX_LAUNCHES];
 static uint32_t launch_block[MAX_LAUNCHES];
-static int n_launches, n_malloc, n_free, n_sync, n_copy, fail_malloc = -1, capturing, mode;
+static int n_launches, n_malloc, n_free, n_sync, n_copy, fail_malloc = -1, fail_one = -1, capturing, mode;
 static unsigned char *scratch;
 
 /* --- read and set by the tests --- */
@@ -31,7 +31,8 @@ void stand_in_counts(int *o) {
 }
 const char *stand_in_launch(int i) { return i < n_launches && i < MAX_LAUNCHES ? launches[i] : ""; }
 int stand_in_block(int i) { return i < n_launches && i < MAX_LAUNCHES ? (int)launch_block[i] : 0; }
-void stand_in_fail_malloc(int after) { fail_malloc = after; } /* that many succeed; -1: all */
+void stand_in_fail_malloc(int after) { fail_malloc = after; }    /* that many succeed; -1: all */
+void stand_in_fail_one_malloc(int after) { fail_one = after; }  /* only the one after that many */
 void stand_in_capturing(int on) { capturing = on; }
 
 static int forbidden(void) { return capturing && mode == 0; }
@@ -51,6 +52,7 @@ int hipMalloc(void **p, size_t n) {
     ++n_malloc;
     *p = NULL;
     if (forbidden()) return CAPTURE;
+    if (fail_one >= 0 && fail_one-- == 0) return OOM;
     if (fail_malloc == 0) return OOM;
     if (fail_malloc > 0) --fail_malloc;
     *p = malloc(n ? n : 1);

@@ -106,3 +106,71 @@ def test_labels_of_wide_maps_take_one_launch(run):
     assert label([(1040, 40)] * 2) == ["label_kernel"]
     assert label([(256, 256), (1040, 40)]) == ["label_wave_kernel", "label_kernel"]
     """)
+
+
+# shapes on both sides of what a launch shape's LDS holds, of either scan
+SCAN_SHAPES = """
+    shapes = [(n, side, s, per * s) for n in (1, 64, 5000) for side in (64, 128, 256, 384, 512, 600)
+              for s in (1, 36, 180, 360, 720) for per in (1, 4)]
+"""
+
+
+def test_set_scan_leaves_the_envs_and_the_device_alone(run):
+    """Selecting a scan regroups no envs, frees nothing and waits for nothing, so
+    launches in flight or captured stay valid; it works during a stream capture,
+    and the launch shape stays as loaded."""
+    run(SCAN_SHAPES + """
+    seen = set()
+    for n, side, sectors, beams in shapes:
+        for first in (0, 1):
+            h = ns.navsim_create(configs.make_config(
+                num_envs=n, num_beams=beams, num_sectors=sectors, fov_rad=6.28, max_range_m=4.0,
+                dt_s=0.1, footprint=0, radius_m=0.18, v_min=0.0, v_max=0.5, w_min=-1.0, w_max=1.0))
+            assert lib.navsim_set_scan(h, first, 0.03) == 0
+            try:
+                load(h, n, [(side, side)])
+            except ns.NavsimError as e:
+                assert e.status == -7
+                lib.navsim_destroy(h)
+                continue
+            obs = np.zeros((n, sectors + 4), np.float32)
+            assert lib.navsim_reset(h, None, obs.ctypes.data, None) == 0
+            shape = ns.navsim_get_tuning(h)
+            for scan in (1 - first, first, 1 - first):
+                clear()
+                R.stand_in_capturing(1)
+                rc = lib.navsim_set_scan(h, scan, 0.03)
+                assert rc in (0, -7), lib.navsim_last_error()
+                c = counts()
+                assert (c.launches, c.free, c.sync) == (0, 0, 0), (n, side, sectors, c)
+                seen.add((scan, rc, c.malloc))
+                assert step(h, n, sectors) == 0
+                R.stand_in_capturing(0)
+                assert ns.navsim_get_tuning(h) == shape
+            assert lib.navsim_destroy(h) == 0
+    # refused, with clearances to build, built already or without, both scans
+    assert {(1, 0, 0), (1, 0, 1), (1, -7, 0), (0, 0, 0)} <= seen, seen
+    """)
+
+
+def test_march_without_memory_for_clearances(run):
+    """The march needs no device memory: without the clearances every sample is
+    evaluated (and they are built once a later selection finds the memory)."""
+    run("""
+    march = lambda: (clear(), step(h, 64), launches())[2][0]
+    h = handle(64, [(128, 128)] * 2, beams=360)
+    R.stand_in_fail_malloc(0)
+    assert lib.navsim_set_scan(h, 1, 0.03) == 0
+    assert march() == "fused_step_kernel<32, 1024, false, false>"
+    t = ns.NavsimTuning(8, 40, 8, 0, 3, 0, 256, 0)
+    R.stand_in_fail_malloc(-1)
+    R.stand_in_fail_one_malloc(0)
+    assert lib.navsim_set_tuning(h, C.byref(t)) == 0
+    assert march() == "fused_step_kernel<8, 256, false, false>"
+    assert lib.navsim_set_scan(h, 1, 0.03) == 0
+    assert march() == "fused_step_kernel<8, 256, false, true>"
+    R.stand_in_fail_one_malloc(7)  # after what a load of maps takes otherwise
+    load(h, 64, [(100, 100)] * 2)
+    assert lib.navsim_reset(h, None, np.zeros((64, 40), np.float32).ctypes.data, None) == 0
+    assert march() == "fused_step_kernel<8, 256, false, false>"
+    """)
