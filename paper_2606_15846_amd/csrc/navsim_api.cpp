@@ -653,20 +653,28 @@ int largest_tile(const std::vector<Tile> &tiles) {
 }
 
 // The loaded envs regrouped for a launch shape, which becomes the handle's (waits
-// for the device: launches in flight read the old tiles).
+// for the device: launches in flight read the old tiles, which go only once the
+// new ones are there).
 navsim_status retile(navsim_s *h, const navsim_tuning &t, const FusedShape &shape) {
     std::vector<int32_t> perm;
     std::vector<Tile> tiles;
     build_tiles(h->host_env_map, t.tile_envs, h->host_map_weight, t.balance, shape.resident, perm,
                 tiles);
-    NS_HIP(hipDeviceSynchronize());
+    int32_t *d_perm = nullptr;
+    Tile *d_tiles = nullptr;
+    navsim_status s = upload(&d_perm, perm);
+    if (s == NAVSIM_OK) s = upload(&d_tiles, tiles);
+    if (s == NAVSIM_OK && hipDeviceSynchronize() != hipSuccess)
+        s = fail(NAVSIM_E_HIP, "hipDeviceSynchronize failed");
+    if (s != NAVSIM_OK) {
+        if (d_perm) (void)hipFree(d_perm);
+        if (d_tiles) (void)hipFree(d_tiles);
+        return s;
+    }
     (void)hipFree(h->perm);
     (void)hipFree(h->tiles);
-    h->perm = nullptr;
-    h->tiles = nullptr;
-    navsim_status s;
-    if ((s = upload(&h->perm, perm)) != NAVSIM_OK) return s;
-    if ((s = upload(&h->tiles, tiles)) != NAVSIM_OK) return s;
+    h->perm = d_perm;
+    h->tiles = d_tiles;
     h->num_tiles = (int)tiles.size();
     h->tile_max = largest_tile(tiles);
     store_tuning(h, t);

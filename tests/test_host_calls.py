@@ -174,3 +174,25 @@ def test_march_without_memory_for_clearances(run):
     assert lib.navsim_reset(h, None, np.zeros((64, 40), np.float32).ctypes.data, None) == 0
     assert march() == "fused_step_kernel<8, 256, false, false>"
     """)
+
+
+def test_launch_shape_without_memory_leaves_the_handle_as_it_was(run):
+    """A launch shape whose tiles cannot be put on the device is refused: the old
+    tiles are neither freed nor replaced, and the next one starts from them."""
+    run("""
+    h = handle(300, [(64, 64)] * 3)
+    t = ns.NavsimTuning(4, 40, 8, 0, 3, 0, 256, 0)
+    before = ns.navsim_get_tuning(h)
+    for nth in (0, 1):  # the order of the envs, the tiles
+        clear()
+        R.stand_in_fail_one_malloc(nth)
+        assert lib.navsim_set_tuning(h, C.byref(t)) == -5
+        c = counts()
+        assert c.free == c.malloc - 1 and c.free == nth, c  # what this call allocated
+        assert ns.navsim_get_tuning(h) == before
+        clear()
+        assert step(h, 300) == 0 and launches() == ["fused_early_kernel<4>"]
+    assert lib.navsim_set_tuning(h, C.byref(t)) == 0
+    clear()
+    assert step(h, 300) == 0 and launches() == ["fused_step_kernel<4, 256, false, false>"]
+    """)
