@@ -7,7 +7,8 @@
 namespace navsim {
 
 // C[m, n] = sum_k A(m, k) B(n, k), bfloat16 operands, float accumulation.
-// A(m, k) = A[m lda + k] when a_kmajor, else A[k lda + m]; B likewise.
+// A(m, k) = A[m lda + k] when a_kmajor, else A[k lda + m] (launch_gradient's
+// products alone); B likewise.
 // Epilogue: + bias[n] (optional) + bias_rows[row_idx[m] ldbr + n] (optional),
 // activation (0 none, 1 leaky ReLU with `slope`, 2 tanh, 3 the derivative of leaky
 // ReLU: times slope where the layer's bfloat16 output H[m, n] is not positive), then

@@ -88,7 +88,7 @@ __device__ __forceinline__ void gemm_store(const GemmArgs &g, int m, int n, floa
 // Fragment layout of v_mfma_f32_16x16x32_bf16: lane l supplies row l % 16 of
 // A and column l % 16 of B, k = 8 (l / 16) .. 8 (l / 16) + 7; it receives
 // C[4 (l / 16) + r][l % 16], r = 0..3.
-template <bool AK, bool BK>
+template <bool BK>
 __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(GemmArgs g) {
     __shared__ __attribute__((aligned(16))) uint16_t As[kBM][kLdsK];
     __shared__ __attribute__((aligned(16))) uint16_t Bs[kBN][kLdsK];
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(GemmArgs g) {
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const int fr = lane & 15, fk = (lane >> 4) * 8;
     for (int k0 = 0; k0 < g.K; k0 += kBK) {
-        stage_tile<AK>(As, g.A, g.lda, M, g.K, m0, k0, a_vec, tid);
+        stage_tile<true>(As, g.A, g.lda, M, g.K, m0, k0, a_vec, tid);
         stage_tile<BK>(Bs, g.B, g.ldb, g.N, g.K, n0, k0, b_vec, tid);
         __syncthreads();
         bf16x8 a[2], b[2];
@@ -279,9 +279,9 @@ __device__ __forceinline__ void gemm_small_block(const GemmArgs &g, int bm, int 
     }
 }
 
-template <bool AK, bool BK>
+template <bool BK>
 __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs g) {
-    gemm_small_block<AK, BK>(g, (int)blockIdx.y, (int)blockIdx.x);
+    gemm_small_block<true, BK>(g, (int)blockIdx.y, (int)blockIdx.x);
 }
 
 // out[n] = sum over m of X[m, n] for 32 columns: chunks of 32 rows in order, 8
@@ -855,29 +855,22 @@ hipError_t launch_forward_noise(const ForwardNoiseArgs &a, int hidden, hipStream
 constexpr int64_t kLargeBlocks = 512;
 
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
+    if (!g.a_kmajor) return hipErrorInvalidValue;  // launch_gradient's products
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
     const int64_t blocks = (int64_t)((g.M + kBM - 1) / kBM) * ((g.N + kBN - 1) / kBN);
     if (blocks < kLargeBlocks) {
         const dim3 sg((unsigned)((g.N + kSB - 1) / kSB), (unsigned)((g.M + kSB - 1) / kSB));
-        if (g.a_kmajor && g.b_kmajor)
-            hipLaunchKernelGGL((gemm_small_kernel<true, true>), sg, dim3(256), 0, s, g);
-        else if (g.a_kmajor)
-            hipLaunchKernelGGL((gemm_small_kernel<true, false>), sg, dim3(256), 0, s, g);
-        else if (g.b_kmajor)
-            hipLaunchKernelGGL((gemm_small_kernel<false, true>), sg, dim3(256), 0, s, g);
+        if (g.b_kmajor)
+            hipLaunchKernelGGL(gemm_small_kernel<true>, sg, dim3(256), 0, s, g);
         else
-            hipLaunchKernelGGL((gemm_small_kernel<false, false>), sg, dim3(256), 0, s, g);
+            hipLaunchKernelGGL(gemm_small_kernel<false>, sg, dim3(256), 0, s, g);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)((g.N + kBN - 1) / kBN), (unsigned)((g.M + kBM - 1) / kBM));
-    if (g.a_kmajor && g.b_kmajor)
-        hipLaunchKernelGGL((gemm_kernel<true, true>), grid, dim3(kGemmThreads), 0, s, g);
-    else if (g.a_kmajor)
-        hipLaunchKernelGGL((gemm_kernel<true, false>), grid, dim3(kGemmThreads), 0, s, g);
-    else if (g.b_kmajor)
-        hipLaunchKernelGGL((gemm_kernel<false, true>), grid, dim3(kGemmThreads), 0, s, g);
+    if (g.b_kmajor)
+        hipLaunchKernelGGL(gemm_kernel<true>, grid, dim3(kGemmThreads), 0, s, g);
     else
-        hipLaunchKernelGGL((gemm_kernel<false, false>), grid, dim3(kGemmThreads), 0, s, g);
+        hipLaunchKernelGGL(gemm_kernel<false>, grid, dim3(kGemmThreads), 0, s, g);
     return hipGetLastError();
 }
 

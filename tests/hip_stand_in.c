@@ -16,7 +16,6 @@ enum { MAX_KERNELS = 1 << 16, MAX_LAUNCHES = 4096, SCRATCH = 16 << 20 };
 static struct { const void *f; const char *name; } kernels[MAX_KERNELS];
 static int n_kernels;
 static const char *launches[MAX_LAUNCHES];
-static uint32_t launch_block[MAX_LAUNCHES];
 static int n_launches, n_malloc, n_free, n_sync, n_copy, fail_malloc = -1, fail_one = -1, capturing, mode;
 static unsigned char *scratch;
 
@@ -30,7 +29,7 @@ void stand_in_counts(int *o) {
     o[4] = n_copy;
 }
 const char *stand_in_launch(int i) { return i < n_launches && i < MAX_LAUNCHES ? launches[i] : ""; }
-int stand_in_block(int i) { return i < n_launches && i < MAX_LAUNCHES ? (int)launch_block[i] : 0; }
+const char *stand_in_kernel(int i) { return i < n_kernels ? kernels[i].name : ""; } /* compiled in */
 void stand_in_fail_malloc(int after) { fail_malloc = after; }    /* that many succeed; -1: all */
 void stand_in_fail_one_malloc(int after) { fail_one = after; }  /* only the one after that many */
 void stand_in_capturing(int on) { capturing = on; }
@@ -129,16 +128,14 @@ int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, void **s) {
 }
 int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, void *s) {
     (void)g;
+    (void)b;
     (void)args;
     (void)lds;
     (void)s;
     const char *name = "?";
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].f == f) name = kernels[i].name;
-    if (n_launches < MAX_LAUNCHES) {
-        launches[n_launches] = name;
-        launch_block[n_launches] = b.x;
-    }
+    if (n_launches < MAX_LAUNCHES) launches[n_launches] = name;
     ++n_launches;
     return OK;
 }

@@ -32,12 +32,22 @@ def counts():
     R.stand_in_counts(v)
     return Counts(*v)
 
-def launches():
-    """Kernel names (without namespace, template arguments kept) since clear()."""
+def names(raw):
     import re, subprocess
-    raw = [R.stand_in_launch(i).decode() for i in range(counts().launches)]
     out = subprocess.run(["c++filt"], input="\n".join(raw), capture_output=True, text=True).stdout
     return [re.search(r"(\w+_kernel(?:<[^(]*>)?)\(", n).group(1) for n in out.split("\n") if n]
+
+def launches():
+    """Kernel names (without namespace, with template arguments) since clear()."""
+    return names([R.stand_in_launch(i).decode() for i in range(counts().launches)])
+
+def kernels():
+    """Names of the kernels in the library."""
+    R.stand_in_kernel.restype = C.c_char_p
+    raw = []
+    while R.stand_in_kernel(len(raw)):
+        raw.append(R.stand_in_kernel(len(raw)).decode())
+    return names(raw)
 
 def handle(n, sides, beams=36, sectors=36, res=0.05, rmax=3.5, **k):
     """A handle with one map per (W, H) of `sides`, loaded and reset."""

@@ -196,3 +196,23 @@ def test_launch_shape_without_memory_leaves_the_handle_as_it_was(run):
     clear()
     assert step(h, 300) == 0 and launches() == ["fused_step_kernel<4, 256, false, false>"]
     """)
+
+
+def test_every_product_kernel_is_launched(run):
+    """Small and large products of both layouts, and the gradients' own: no compiled
+    product variant is out of reach."""
+    run("""
+    seen = set()
+    for hidden in (64, 512):
+        r = proposer(handle(8, [(64, 64)]), hidden=hidden)
+        cnt = C.c_int64()
+        assert lib.navsim_rp_layout(r, None, None, None, C.byref(cnt)) == 0
+        g = np.zeros(cnt.value, np.float32)
+        for n in (40, 9000):
+            x, t = np.zeros((n, 1048), np.uint16), np.zeros((n, 5), np.float32)
+            clear()
+            assert lib.navsim_rp_loss_grad(r, n, x.ctypes.data, t.ctypes.data, None, g.ctypes.data, None) == 0
+            seen |= set(launches())
+    made = {n for n in kernels() if "gemm" in n or "gradient" in n}
+    assert made and made <= seen, (made, seen)
+    """)
