@@ -216,3 +216,29 @@ def test_every_product_kernel_is_launched(run):
     made = {n for n in kernels() if "gemm" in n or "gradient" in n}
     assert made and made <= seen, (made, seen)
     """)
+
+
+# 256 CUs: 1,024 threads up to 128 tiles of 32 envs; byte copies up to 24 KiB
+@pytest.mark.parametrize("n,sides,beams,sectors,shape,kernel", [
+    (1, [(64, 64)], 36, 36, (32, 4, 1024), "fused_early_kernel<4>"),
+    (4096, [(128, 128)] * 5, 20, 10, (32, 4, 1024), "fused_step_kernel<32, 1024, false, false>"),
+    (4097, [(128, 128)] * 5, 20, 10, (32, 5, 512), "fused_step_kernel<32, 512, false, false>"),
+    (300, [(136, 128)] * 2, 90, 30, (32, 4, 1024), None),
+    (300, [(160, 160)] * 7, 90, 30, (32, 5, 1024), None),
+    (5000, [(64, 64)], 360, 360, (32, 5, 1024), "fused_step_kernel<32, 1024, false, false>"),
+    (64, [(512, 512)], 360, 360, (32, 3, 1024), None),
+    (40, [(96, 96)] * 2, 1080, 1080, (16, 4, 1024), None),
+    (24, [(600, 600)], 720, 720, (16, 3, 1024), None),
+])
+def test_automatic_launch_shape(run, n, sides, beams, sectors, shape, kernel):
+    """The shape picked at load on both sides of its rules, the kernel it leads to,
+    and no message of a shape that did not fit."""
+    run(f"""
+    h = handle({n}, {sides}, {beams}, {sectors})
+    t = ns.navsim_get_tuning(h)
+    assert (t["tile_envs"], t["walk"], t["threads"]) == {shape}, t
+    assert lib.navsim_last_error() == b""
+    clear()
+    assert step(h, {n}, {sectors}) == 0
+    assert {kernel!r} in (None, *launches()), launches()
+    """)
