@@ -212,15 +212,16 @@ int staged_words(int max_words, int max_words_t, int walk, int scan_mode) {
 // The march stages the maps' clearances after the bitmaps where they fit beside
 // at least as many ray slots as there are threads (max_clear 0: there are none).
 struct FusedShape {
-    int ray_cap = 0, cell_bytes = 0, claim = 0, resident = 0;
+    int ray_cap = 0, cell_bytes = 0, claim = 0, resident = 0, words = 0;
     bool beams_lds = true, clear = false;
 };
 
-navsim_status fused_shape(const navsim_s *h, int max_words_row, int max_words_t, int max_clear,
-                          int tile_envs, int threads, int slots, int walk, int scan_mode,
-                          FusedShape &out) {
+navsim_status fused_layout(const navsim_s *h, int max_words_row, int max_words_t, int max_clear,
+                           const navsim_tuning &t, int scan_mode, FusedShape &out) {
     const navsim_config &c = h->cfg;
     const int m = c.num_sectors, K = c.num_beams;
+    const int tile_envs = t.tile_envs, threads = t.threads, slots = t.ray_slots, walk = t.walk;
+    out = FusedShape{};
     int max_words = staged_words(max_words_row, max_words_t, walk, scan_mode);
     if (scan_mode == NAVSIM_SCAN_MARCH && max_clear > 0) {
         bool beams = false;
@@ -260,7 +261,18 @@ navsim_status fused_shape(const navsim_s *h, int max_words_row, int max_words_t,
                         "%d beams, %d sectors do not fit the LDS of one workgroup (%d bytes)",
                         tile_envs, threads, walk, K, m, h->lds_block);
     }
-    out.resident = fused_resident_groups(max_words, m, tile_envs, threads, K, out.beams_lds,
+    out.words = max_words;
+    return NAVSIM_OK;
+}
+
+// fused_layout, and the number of workgroups that run at once.
+navsim_status fused_shape(const navsim_s *h, int max_words_row, int max_words_t, int max_clear,
+                          const navsim_tuning &t, int scan_mode, FusedShape &out) {
+    const navsim_status s =
+        fused_layout(h, max_words_row, max_words_t, max_clear, t, scan_mode, out);
+    if (s != NAVSIM_OK) return s;
+    out.resident = fused_resident_groups(out.words, h->cfg.num_sectors, t.tile_envs, t.threads,
+                                         h->cfg.num_beams, out.beams_lds,
                                          out.claim ? 0 : out.ray_cap, out.cell_bytes);
     if (out.resident <= 0) return fail(NAVSIM_E_HIP, "occupancy query of the fused step failed");
     return NAVSIM_OK;
@@ -329,33 +341,33 @@ void store_tuning(navsim_s *h, const navsim_tuning &t) {
 navsim_status pick_shape(const navsim_s *h, int max_words_row, int max_words_t, int max_clear,
                          navsim_tuning &t, FusedShape &out) {
     const auto fits = [&](const navsim_tuning &q, int scan_mode) {
-        out = FusedShape{};
-        return fused_shape(h, max_words_row, max_words_t, max_clear, q.tile_envs, q.threads,
-                           q.ray_slots, q.walk, scan_mode, out);
+        return fused_layout(h, max_words_row, max_words_t, max_clear, q, scan_mode, out) ==
+               NAVSIM_OK;
     };
+    const int mode = h->scan_mode, other = 1 - mode;
     if (h->tuned) {
         t = current_tuning(h);
-        return fits(t, h->scan_mode);
+        return fused_shape(h, max_words_row, max_words_t, max_clear, t, mode, out);
     }
-    const int mode = h->scan_mode, other = 1 - mode;
+    t = default_tuning();
     const std::string message = g_err;  // shapes that do not fit are no failure of the call
-    const bool both = fits(default_tuning(), other) == NAVSIM_OK;
-    const navsim_status s = fits(t = default_tuning(), mode);
-    if (s != NAVSIM_OK) return s;  // what the default cannot hold stays refused
-    for (int e = 32; e >= 8; e /= 2)
-        for (const bool wide : {false, true})
-            for (const bool own_walk : {true, false}) {
-                auto_tuning(h, max_words_row, t);
-                t.tile_envs = e;
-                if (wide) t.threads = 1024;
-                if (!own_walk) t.walk = kDefaultWalk;
-                if ((!both || fits(t, other) == NAVSIM_OK) && fits(t, mode) == NAVSIM_OK) {
-                    g_err = message;
-                    return NAVSIM_OK;
+    const bool both = fits(t, other);
+    if (!fits(t, mode)) return NAVSIM_E_UNSUPPORTED;  // what the default cannot hold stays refused
+    const auto pick = [&] {
+        for (int e = 32; e >= 8; e /= 2)
+            for (const bool wide : {false, true})
+                for (const bool own_walk : {true, false}) {
+                    auto_tuning(h, max_words_row, t);
+                    t.tile_envs = e;
+                    if (wide) t.threads = 1024;
+                    if (!own_walk) t.walk = kDefaultWalk;
+                    if (fits(t, mode) && (!both || fits(t, other))) return;
                 }
-            }
+        t = default_tuning();
+    };
+    pick();
     g_err = message;
-    return fits(t = default_tuning(), mode);
+    return fused_shape(h, max_words_row, max_words_t, max_clear, t, mode, out);
 }
 
 void apply_shape(navsim_s *h, const FusedShape &f) {
@@ -438,10 +450,8 @@ bool build_clearance(navsim_s *h, const std::vector<MapDesc> &descs) {
 // be: the march then evaluates every sample).
 navsim_status loaded_shape(navsim_s *h, const navsim_tuning &t, int scan_mode, FusedShape &out) {
     for (const int max_clear : {h->max_clear, 0}) {
-        out = FusedShape{};
         const navsim_status s =
-            fused_shape(h, h->max_words, h->max_words_t, max_clear, t.tile_envs, t.threads,
-                        t.ray_slots, t.walk, scan_mode, out);
+            fused_shape(h, h->max_words, h->max_words_t, max_clear, t, scan_mode, out);
         if (s != NAVSIM_OK || !out.clear || h->clear || build_clearance(h, h->host_descs)) return s;
     }
     return NAVSIM_OK;
@@ -1151,7 +1161,7 @@ navsim_status navsim_load_maps_ex(navsim_t h, int32_t num_maps, const int32_t *w
     }
     h->host_free.swap(free_cells);
     h->host_descs.swap(descs);
-    if ((s = loaded_shape(h, tuning, h->scan_mode, shape)) != NAVSIM_OK) return s;
+    if (shape.clear && (s = loaded_shape(h, tuning, h->scan_mode, shape)) != NAVSIM_OK) return s;
     apply_shape(h, shape);
     h->loaded = true;
     return NAVSIM_OK;
@@ -1298,11 +1308,9 @@ navsim_status navsim_set_scan(navsim_t h, int32_t mode, float step_m) {
     if (h->loaded) {
         DeviceGuard g(h->device);
         navsim_status fs = NAVSIM_OK;
-        if (!h->tuned) {  // what the default shape cannot hold is refused
-            const navsim_tuning t = default_tuning();
-            fs = fused_shape(h, h->max_words, h->max_words_t, h->max_clear, t.tile_envs, t.threads,
-                             t.ray_slots, t.walk, mode, shape);
-        }
+        if (!h->tuned)  // what the default shape cannot hold is refused
+            fs = fused_layout(h, h->max_words, h->max_words_t, h->max_clear, default_tuning(), mode,
+                              shape);
         if (fs == NAVSIM_OK) fs = loaded_shape(h, current_tuning(h), mode, shape);
         if (fs != NAVSIM_OK) return fs;
     }
