@@ -411,7 +411,19 @@ def tuning_for(w, args) -> tuple[dict, bool]:
     return tuning, tuning == tuned
 
 
-def roofline(workload: str, visits: int, steps: int, ms_per_step: float, lds_peak, profiled):
+def step_kernel(tuning: dict) -> str:
+    """The kernel of a step at this launch shape: claim walks in one workgroup of
+    1024 threads per tile start beside the motion where every tile has at most 16
+    envs."""
+    if tuning["threads"] != 1024 or tuning["walk"] < 3 or tuning["persist"]:
+        return "fused_step_kernel"
+    if tuning["tile_envs"] <= 16:
+        return "fused_early_kernel"
+    return "fused_early_kernel (fused_step_kernel if a tile has more than 16 envs)"
+
+
+def roofline(workload: str, visits: int, steps: int, ms_per_step: float, lds_peak, profiled,
+             kernel: str):
     lds_bytes_per_launch = 4.0 * visits / steps
     # one launch per step, back to back: the timed region's time per step is
     # the launch's duration plus the dispatch gap (the roofline's denominator)
@@ -420,7 +432,7 @@ def roofline(workload: str, visits: int, steps: int, ms_per_step: float, lds_pea
     out = {"bound": "lds", "achieved": achieved, "peak": NOMINAL_LDS_GBS, "unit": "GB/s",
            "frac": achieved / NOMINAL_LDS_GBS,
            "traffic": hbm_traffic_from_profile(workload) if profiled else None,
-           "kernel": "fused_step_kernel", "avg_launch_us": avg_launch_s * 1e6,
+           "kernel": kernel, "avg_launch_us": avg_launch_s * 1e6,
            "algorithmic_bytes_per_launch": lds_bytes_per_launch,
            "bytes_per_unit": "4 B of bitmap word per grid-cell visit of the step's pre-reset scan",
            "peak_nominal": NOMINAL_LDS_GBS,
@@ -478,7 +490,8 @@ def run_fused_leg(name: str, args, steps: int, warmup: int, lds_peak, full: bool
            "fallback_goal": work["fallback_goal"],
            "extra_rays_per_s": work["resets"] * (rays_per_step / N) / (total_ms / 1e3),
            "cell_visits_per_env_step": work["visits"] / (N * steps),
-           "roofline": roofline(name, work["visits"], steps, ms_per_step, lds_peak, profiled),
+           "roofline": roofline(name, work["visits"], steps, ms_per_step, lds_peak, profiled,
+                                step_kernel(tuning)),
            "tuning": sim.get_tuning()}
     if not full:
         sim.close()

@@ -97,8 +97,10 @@ navsim_status navsim_rp_train(navsim_rp_t rp, int32_t num_pairs, const int32_t *
  * proposals + t: rejection attempt t; -1: nothing valid, pose = the last
  * rejection attempt's pair, zeros when none ran), checks int32 [n] (exact
  * checks run), y_out float [n][proposals][5] the network's raw outputs (may
- * be NULL).  proposals = 0 is the rejection sampler alone; n * proposals
- * <= 2^24. */
+ * be NULL).  proposals = 0 is the rejection sampler alone, which needs no
+ * workspace; n * proposals <= 2^24.  The workspace of other calls grows with
+ * n * proposals alone (an allocation, and a wait for the device when it grows),
+ * so a call can be captured once one of as many draws has run. */
 navsim_status navsim_rp_propose(navsim_rp_t rp, int32_t n, const int32_t *map, const int32_t *bin,
                                 const uint32_t *env, const uint32_t *episode, int32_t proposals,
                                 int32_t max_tries, float *pose, int32_t *hops, int32_t *source,
@@ -107,14 +109,17 @@ navsim_status navsim_rp_propose(navsim_rp_t rp, int32_t n, const int32_t *map, c
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * call, arguments, outputs and kernels as navsim_rp_propose, with every
- * workspace it needs (the constant first-layer table, noise inputs, network
- * outputs and two hidden activations) carved from one fixed 16 MiB array per
- * device that the library's code object holds until the process ends; it
+ * workspace it needs (the constant first-layer table and network outputs; for
+ * hidden widths other than 128 and 256 also noise inputs and two hidden
+ * activations, which count for every width) carved from one fixed 16 MiB array
+ * per device that the library's code object holds until the process ends; it
  * calls no hipMalloc or hipFree.  Workspace bytes, each part rounded up to
  * 256: maps x num_bins x hidden x 4 + R x (2 noise_dim + 4 + 20 + 4 hidden)
  * with R = n x proposals (0 when proposals = 0: the rejection sampler alone
  * uses none); e.g. 64 maps, 8 bins, hidden 256, noise 16: up to ~15,000
- * draws per call.  Errors: as navsim_rp_propose, and INVALID_ARG when the
+ * draws per call.  Where what is left of the array holds the list of requests
+ * whose late candidates two further launches check at once, it takes that
+ * too; otherwise one launch checks all of them.  Errors: as navsim_rp_propose, and INVALID_ARG when the
  * workspace would exceed 16 MiB (nothing is launched).  Every call on a
  * device shares that device's array and leaves its contents there (nothing in
  * it needs to start at zero): calls that overlap on one device, on different

@@ -2159,8 +2159,9 @@ constexpr int kEarlyThreads = 1024;
 // Here the walk starts on the other wavefronts as soon as the new poses are known;
 // collisions, goal features, rewards and reset poses are worked out beside it.  A
 // kernel per walk, so that none carries the others' registers.  us a step, before
-// and now: 16 envs of 36 rays 11.3, 10.6; 4096 envs of 360 rays 51.0, 50.2; 16384
-// envs (tiles of 8) on bytes 240, 228, on runs 243, 233.
+// and now: 16 envs of 36 rays 11.3, 10.6; 4096 envs of 360 rays 50.9, 50.2 (1 %, on
+// some cards within their noise); 16384 envs (tiles of 8) on bytes 240, 228, on
+// runs 243, 233.
 template <int WALK>
 __global__ __launch_bounds__(kEarlyThreads) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerSimd)))
 void fused_early_kernel(StepParams p) {

@@ -82,7 +82,9 @@ struct ProposeArgs {
 };
 // Candidates checked together per request (one per wavefront), and the rounds a
 // request's own workgroup checks before its other rounds go to the tail launch: in
-// a call of n requests, and inside a step, where n is the most there can be.
+// a call of n requests, and inside a step, where n is the most there can be (a step
+// of 8,192 envs with about 120 resets, at most 8,192: 358 us with 1 head round, 488
+// with 3).
 int propose_width(int n);
 int propose_head_rounds(int n);
 constexpr int kProposeStepHeadRounds = 1;

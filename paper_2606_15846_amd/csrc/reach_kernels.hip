@@ -1,6 +1,6 @@
 // Reachability kernels of the learned reset proposal: breadth-first search on
-// C-free bitsets, by one wavefront in its registers, or (labelling, and maps
-// whose searches do not fit a wavefront's registers) by a workgroup in LDS.
+// C-free bitsets, by one wavefront in its registers, or (maps whose searches do
+// not fit a wavefront's registers) by a workgroup in LDS.
 // Each search level dilates the frontier by one 4-neighbour move with word
 // shifts (left/right within a row, carries across words) and row offsets
 // (up/down), masks it with the C-free cells not yet reached, and stops as soon

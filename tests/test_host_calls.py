@@ -242,3 +242,16 @@ def test_automatic_launch_shape(run, n, sides, beams, sectors, shape, kernel):
     assert step(h, {n}, {sectors}) == 0
     assert {kernel!r} in (None, *launches()), launches()
     """)
+
+
+def test_bench_names_the_step_kernel_that_runs(run):
+    run("""
+    import bench
+    for tile, walk, persist, threads in ((16, 4, 0, 1024), (8, 5, 0, 1024), (16, 3, 2, 1024),
+                                         (16, 2, 0, 1024), (32, 5, 0, 512), (8, 3, 0, 256)):
+        h = handle(64, [(64, 64)] * 2)
+        ns.navsim_set_tuning(h, tile, 32, 16, 0, walk, persist, threads, 1)
+        clear()
+        assert step(h, 64) == 0
+        assert launches()[0].split("<")[0] == bench.step_kernel(ns.navsim_get_tuning(h))
+    """)
