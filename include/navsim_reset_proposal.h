@@ -98,7 +98,8 @@ navsim_status navsim_rp_train(navsim_rp_t rp, int32_t num_pairs, const int32_t *
  * rejection attempt's pair, zeros when none ran), checks int32 [n] (exact
  * checks run), y_out float [n][proposals][5] the network's raw outputs (may
  * be NULL).  proposals = 0 is the rejection sampler alone, which needs no
- * workspace; n * proposals <= 2^24.  The workspace of other calls grows with
+ * workspace (hops, source and checks hold its state until it is done);
+ * n * proposals <= 2^24.  The workspace of other calls grows with
  * n * proposals alone (an allocation, and a wait for the device when it grows),
  * so a call can be captured once one of as many draws has run. */
 navsim_status navsim_rp_propose(navsim_rp_t rp, int32_t n, const int32_t *map, const int32_t *bin,

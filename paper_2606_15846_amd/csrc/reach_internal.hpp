@@ -17,6 +17,8 @@ constexpr int kPackedMaxRow = 16;
 // propose_kernel: one candidate check per wavefront, 8 at a time for launches
 // of at most this many requests, else 4
 constexpr int kProposeWideMax = 2048;
+// most requests of a call of the rejection sampler alone that has a tail launch
+constexpr int kOwnTailMax = 8192;
 constexpr int kPoolCells = 1024;      // 32 x 32 pooled occupancy
 
 // One map's C-free cells, twice: a plain bitset (row j, column i is bit i & 31
@@ -75,7 +77,8 @@ struct ProposeArgs {
     // first head_rounds rounds (0: no limit) is appended to pend (count
     // *n_pend, best[p] = INT_MAX) instead of written; the tail launch checks
     // its remaining rounds all at once (round slots in tail) and the final
-    // launch writes it
+    // launch writes it.  Without these arrays (n_pend NULL; the rejection sampler
+    // alone) its state lies in its own output rows (see propose_tail_own_kernel)
     int head_rounds = 0;
     int32_t *pend = nullptr, *n_pend = nullptr, *best = nullptr;
     int4 *tail = nullptr;

@@ -784,9 +784,15 @@ __device__ void propose_waves(const ReachParams &rp, const ProposeArgs &pa, cons
         if (pa.head_rounds > 0 && round == pa.head_rounds) {
             // the rest of this request's rounds go to the tail launch
             if (threadIdx.x == 0) {
-                const int p = atomicAdd(pa.n_pend, 1);
-                pa.pend[p] = i;
-                pa.best[p] = INT_MAX;
+                if (pa.n_pend) {
+                    const int p = atomicAdd(pa.n_pend, 1);
+                    pa.pend[p] = i;
+                    pa.best[p] = INT_MAX;
+                } else {
+                    pa.checks[o] = -1;  // pending, see propose_tail_own_kernel
+                    pa.source[o] = INT_MAX;
+                    pa.hops[o] = -1;
+                }
             }
             return;
         }
@@ -1100,46 +1106,129 @@ hipError_t launch_label(const ReachParams &rp, int n, const int32_t *map, uint32
     return hipGetLastError();
 }
 
+// Tail round r of pending request i by one workgroup: the lowest valid candidate
+// of the round with its pair, hop count and heading, or -1; a round that starts
+// above a valid candidate already found (*best) is skipped, it cannot win.
+template <int W>
+__device__ __forceinline__ int tail_round(const ReachParams &rp, const ProposeArgs &pa, uint4 *lds4,
+                                          int i, int r, const int *best, int &a, int &b, int &h,
+                                          float &th) {
+    __shared__ int s_skip;
+    const int mk = pa.map[i], k = pa.bin[i];
+    const ReachDesc d = rp.maps[mk];
+    const int total = pa.props + (d.free_cnt > 0 ? pa.tries : 0);
+    const int c0 = (pa.head_rounds + r) * W;
+    // uniform across the workgroup: one read of *best, then a barrier before any
+    // thread moves on
+    if (threadIdx.x == 0) s_skip = c0 >= total || __atomic_load_n(best, __ATOMIC_RELAXED) < c0;
+    __syncthreads();
+    const bool skip = s_skip != 0;
+    __syncthreads();
+    if (skip) return -1;
+    stage_packed(rp, d, lds4);
+    __syncthreads();
+    return check_round<W>(rp, pa, d, reinterpret_cast<uint32_t *>(lds4), i, k, c0, total, a, b, h,
+                          th, best);
+}
+
 // Tail rounds: every (pending request, round) is one work item, taken by the
 // workgroups of a fixed grid in round-major order (all requests' first tail
 // round, then their second, ...), so a request's rounds run at once on
 // different workgroups.  A round's lowest valid candidate goes to its slot and
-// into the request's best index (atomic minimum); a round that starts above a
-// valid candidate already found is skipped (it cannot win).  Requests reach
-// the pending list only from the register search, so the same path serves.
+// into the request's best index (atomic minimum).  Requests reach the pending
+// list only from the register search, so the same path serves.
 template <int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4)))
 void propose_tail_kernel(ReachParams rp, ProposeArgs pa, int tail_rounds) {
     extern __shared__ uint4 lds4[];
-    uint32_t *fb = reinterpret_cast<uint32_t *>(lds4);
     const int np = *pa.n_pend;
     const int items = np * tail_rounds;
     for (int g = blockIdx.x; g < items; g += gridDim.x) {
         const int p = g % np, r = g / np;
-        const int i = pa.pend[p];
-        const int mk = pa.map[i], k = pa.bin[i];
-        const ReachDesc d = rp.maps[mk];
-        const int total = pa.props + (d.free_cnt > 0 ? pa.tries : 0);
-        const int c0 = (pa.head_rounds + r) * W;
-        // uniform across the workgroup: one read of best, then a barrier
-        // before any thread moves on
-        __shared__ int s_skip;
-        if (threadIdx.x == 0) s_skip = c0 >= total || __atomic_load_n(&pa.best[p], __ATOMIC_RELAXED) < c0;
-        __syncthreads();
-        const bool skip = s_skip != 0;
-        __syncthreads();
-        if (skip) continue;
-        stage_packed(rp, d, lds4);
-        __syncthreads();
         int a = -1, b = -1, h = -1;
         float th = 0.0f;
-        const int win = check_round<W>(rp, pa, d, fb, i, k, c0, total, a, b, h, th, &pa.best[p]);
+        const int win = tail_round<W>(rp, pa, lds4, pa.pend[p], r, &pa.best[p], a, b, h, th);
         if (threadIdx.x == 0 && win >= 0) {
             pa.tail[(int64_t)p * tail_rounds + r] = make_int4(a, b, h, __float_as_int(th));
             atomicMin(&pa.best[p], win);
         }
         __syncthreads();  // the map in LDS is restaged by the next item
     }
+}
+
+// The same for a call of the rejection sampler alone, which has no workspace: a
+// pending request's state lies in its own output rows until the final launch.
+// checks is -1; source holds the lowest valid attempt found so far, or INT_MAX;
+// hops, unsigned, that attempt's number << 16 | its hop count (both below 2^16).
+// The pair and heading come from the attempt's number again.  Every workgroup
+// looks through the marks itself and lists the pending requests in order, so all
+// agree on the items' numbers (marks change only in the final launch).  A call thus
+// allocates nothing, may be captured first and may overlap any other.
+template <int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4)))
+void propose_tail_own_kernel(ReachParams rp, ProposeArgs pa, int tail_rounds) {
+    extern __shared__ uint4 lds4[];
+    constexpr int T = 64 * W, N = W == 8 ? kProposeWideMax : kOwnTailMax;
+    static_assert(N % (4 * T) == 0 && N <= 1 << 16, "4 requests a thread and pass");
+    __shared__ uint16_t s_req[N];
+    __shared__ int s_cnt[N / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // ballots of the marks of requests q + j T .., their loads together
+    const auto pending = [&](int q, uint64_t(&m)[4]) {
+        int c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = pa.checks[min(q + j * T + tid, pa.n - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m[j] = __ballot(q + j * T + tid < pa.n && c[j] == -1);
+    };
+    uint64_t m[4];
+    for (int q = 0; q < pa.n; q += 4 * T) {
+        pending(q, m);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (lane == 0) s_cnt[(q >> 6) + j * W + wave] = __popcll(m[j]);
+    }
+    __syncthreads();
+    int np = 0;
+    for (int q = 0; q < pa.n; q += 4 * T) {
+        pending(q, m);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            int at = np;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int c = s_cnt[(q >> 6) + j * W + w];
+                at += w < wave ? c : 0;
+                np += c;
+            }
+            if ((m[j] >> lane) & 1ull)
+                s_req[at + __popcll(m[j] & ((1ull << lane) - 1ull))] = (uint16_t)(q + j * T + tid);
+        }
+    }
+    __syncthreads();
+    const int items = np * tail_rounds;
+    for (int g = blockIdx.x; g < items; g += gridDim.x) {
+        const int i = s_req[g % np];
+        int a = -1, b = -1, h = -1;
+        float th = 0.0f;
+        const int win = tail_round<W>(rp, pa, lds4, i, g / np, &pa.source[i], a, b, h, th);
+        if (tid == 0 && win >= 0) {
+            atomicMin(&pa.source[i], win);
+            atomicMin(reinterpret_cast<uint32_t *>(&pa.hops[i]),
+                      ((uint32_t)win << 16) | (uint32_t)h);
+        }
+        __syncthreads();  // the map in LDS is restaged by the next item
+    }
+}
+
+// Pair and heading of rejection attempt t of request i.
+__device__ void attempt_pair(const ReachParams &rp, const ProposeArgs &pa, const ReachDesc &d,
+                             int i, int t, int &a, int &b, float &th) {
+    uint32_t q[4] = {pa.env[i], pa.episode[i], (uint32_t)t, 7u};
+    philox4x32_10(q, rp.key0, rp.key1);
+    a = rp.free_cells[d.free_off + pick_of(q[0], d.free_cnt)];
+    b = rp.free_cells[d.free_off + pick_of(q[1], d.free_cnt)];
+    th = (float)((((double)q[2] + 0.5) / kTwo32) * (2.0 * kPiR) - kPiR);
 }
 
 // Outputs of the pending requests: the lowest valid candidate any tail round
@@ -1160,13 +1249,21 @@ __global__ void propose_final_kernel(ReachParams rp, ProposeArgs pa, int tail_ro
         lh = q.z;
         lth = __int_as_float(q.w);
     } else if (total - 1 >= pa.props) {
-        uint32_t q[4] = {pa.env[i], pa.episode[i], (uint32_t)(total - 1 - pa.props), 7u};
-        philox4x32_10(q, rp.key0, rp.key1);
-        la = rp.free_cells[d.free_off + pick_of(q[0], d.free_cnt)];
-        lb = rp.free_cells[d.free_off + pick_of(q[1], d.free_cnt)];
-        lth = (float)((((double)q[2] + 0.5) / kTwo32) * (2.0 * kPiR) - kPiR);
+        attempt_pair(rp, pa, d, i, total - 1 - pa.props, la, lb, lth);
     }
     write_request(pa, d, o, win, la, lb, lh, lth, total);
+}
+
+__global__ void propose_final_own_kernel(ReachParams rp, ProposeArgs pa) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= pa.n || pa.checks[i] != -1) return;
+    const ReachDesc d = rp.maps[pa.map[i]];
+    const int win = pa.source[i] == INT_MAX ? -1 : pa.source[i];
+    const int lh = (int)((uint32_t)pa.hops[i] & 0xffffu);
+    int la, lb;
+    float lth;
+    attempt_pair(rp, pa, d, i, win >= 0 ? win : pa.tries - 1, la, lb, lth);
+    write_request(pa, d, i, win, la, lb, lh, lth, pa.tries);
 }
 
 int propose_width(int n) { return n <= kProposeWideMax ? 8 : 4; }
@@ -1182,6 +1279,20 @@ hipError_t launch_propose_tail(const ReachParams &rp, const ProposeArgs &a, int 
     // a fixed grid: the pending count is only known on the device
     const unsigned g = (unsigned)std::min<int64_t>((int64_t)a.n * tail_rounds, 1024);
     const int W = propose_width(a.n);
+    const dim3 grid(g), block(64 * W);
+    if (!a.n_pend) {
+        if (a.n > kOwnTailMax) return hipErrorInvalidValue;
+        if (W == 8)
+            hipLaunchKernelGGL(propose_tail_own_kernel<8>, grid, block, propose_lds(rp), s, rp, a,
+                               tail_rounds);
+        else
+            hipLaunchKernelGGL(propose_tail_own_kernel<4>, grid, block, propose_lds(rp), s, rp, a,
+                               tail_rounds);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(propose_final_own_kernel, dim3(nblocks(a.n, 256)), dim3(256), 0, s, rp, a);
+        return hipGetLastError();
+    }
     if (W == 8)
         hipLaunchKernelGGL(propose_tail_kernel<8>, dim3(g), dim3(512), propose_lds(rp), s, rp, a,
                            tail_rounds);

@@ -423,20 +423,36 @@ size_t tail_room(int64_t R) {
 }
 
 // Bytes of the tail launch's list for a call, 0 for one whose requests' workgroups
-// rather check every round.  The rejection sampler alone has no workspace: its
-// calls may be captured, run with no memory left, and overlap (in the fixed array
-// too, which every proposer of a device shares).  With one round left its place
-// does not matter (2 rounds of 16 attempts, 128 requests: 139 us, with a tail 172);
-// a few requests mostly end in their first rounds, and the two launches cost more
-// than the slowest one's rounds (32 draws, 64 attempts: 64 requests 176 against
-// 207 us, 128 requests 290 against 236); 2^22 slots (64 MiB) and 64 slots a draw
-// (500 attempts behind a single draw) bound the workspace.
+// rather check every round (or that keeps its state elsewhere, see own_tail).  With
+// one round left its place does not matter (2 rounds of 16 attempts, 128 requests:
+// 139 us, with a tail 172); a few requests mostly end in their first rounds, and the
+// two launches cost more than the slowest one's rounds (32 draws, 64 attempts: 64
+// requests 176 against 207 us, 128 requests 290 against 236); 2^22 slots (64 MiB)
+// and 64 slots a draw (500 attempts behind a single draw) bound the workspace.
 size_t tail_bytes(int32_t n, int32_t proposals, int32_t max_tries) {
     const int64_t rounds = tail_rounds_of(n, proposals, max_tries, propose_head_rounds(n));
     if (proposals <= 0 || rounds < 2 || n < 128 || n * rounds > kTailSlots ||
         rounds > kTailSlotsPerDraw * proposals)
         return 0;
     return tail_list_bytes(n, n * rounds);
+}
+
+// Whether a call of the rejection sampler alone has a tail launch.  Such a call has
+// no workspace: it may be captured first, run with no memory left, and overlap any
+// other (in the fixed array too, which every proposer of a device shares); a pending
+// request's state lies in its own output rows, which therefore may not share memory.
+// us with one launch and with the tail: 64 attempts on 256 x 256 maps, bins to 12 m,
+// 1 request 20, 28; 8 requests 87, 95; 31, 219, 144; 512, 430, 235; 2,049, 864, 463;
+// 8,192, 1,405, 1,187; 16,384, 2,069, 2,050.  Past 8,192 the chip is full without it,
+// and it costs where most requests end early (16,384 on 40 x 36 maps 568, 799); for
+// few it pays where they do not (8 requests, bins to 60 m: 639, 223).
+bool own_tail(int32_t n, int32_t proposals, int32_t max_tries, const int32_t *hops,
+              const int32_t *source, const int32_t *checks) {
+    const int64_t rounds = tail_rounds_of(n, proposals, max_tries, propose_head_rounds(n));
+    const auto apart = [n](const int32_t *a, const int32_t *b) { return a + n <= b || b + n <= a; };
+    return proposals == 0 && rounds >= 2 && n <= kOwnTailMax && n * rounds <= kTailSlots &&
+           max_tries < 1 << 16 && apart(hops, source) && apart(hops, checks) &&
+           apart(source, checks);
 }
 
 // Fixed-workspace bytes of a call with n requests x `proposals` draws (0
@@ -486,9 +502,11 @@ navsim_status propose_run(navsim_rp_s *r, int32_t n, const int32_t *map, const i
     pa.source = source;
     pa.checks = checks;
     const int head = propose_head_rounds(n);
-    const int tail_rounds = w.pend ? (int)tail_rounds_of(n, proposals, max_tries, head) : 0;
-    if (tail_rounds > 0) {
-        pa.head_rounds = head;
+    const bool own = own_tail(n, proposals, max_tries, hops, source, checks);
+    const int tail_rounds =
+        w.pend || own ? (int)tail_rounds_of(n, proposals, max_tries, head) : 0;
+    if (tail_rounds > 0) pa.head_rounds = head;
+    if (w.pend) {
         pa.n_pend = (int32_t *)w.pend;
         pa.pend = (int32_t *)(w.pend + 256);
         pa.best = (int32_t *)(w.pend + 256 + align_up((size_t)n * 4));

@@ -18,9 +18,11 @@ static int n_kernels;
 static const char *launches[MAX_LAUNCHES];
 static int n_launches, n_malloc, n_free, n_sync, n_copy, fail_malloc = -1, fail_one = -1, capturing, mode;
 static unsigned char *scratch;
+static int n_scratch; /* pointers into it among the proposal launches' arguments */
 
 /* --- read and set by the tests --- */
-void stand_in_clear(void) { n_launches = n_malloc = n_free = n_sync = n_copy = 0; }
+int stand_in_scratch_pointers(void) { return n_scratch; }
+void stand_in_clear(void) { n_scratch = n_launches = n_malloc = n_free = n_sync = n_copy = 0; }
 void stand_in_counts(int *o) {
     o[0] = n_launches;
     o[1] = n_malloc;
@@ -129,12 +131,17 @@ int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, void **s) {
 int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, void *s) {
     (void)g;
     (void)b;
-    (void)args;
     (void)lds;
     (void)s;
     const char *name = "?";
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].f == f) name = kernels[i].name;
+    if (strstr(name, "propose"))
+        for (int i = 0; i < 19; ++i) { /* ProposeArgs: 152 bytes */
+            unsigned char *p;
+            memcpy(&p, (char *)args[1] + 8 * i, 8);
+            n_scratch += scratch && p >= scratch && p < scratch + SCRATCH;
+        }
     if (n_launches < MAX_LAUNCHES) launches[n_launches] = name;
     ++n_launches;
     return OK;

@@ -131,3 +131,25 @@ def test_labels_of_wide_maps_alone_and_beside_others():
         assert np.array_equal(got[0][k], got[1][k]), k
         assert (got[0][k][[2, 5]] == -1).all(), k
     assert (got[0]["goal"][[0, 1, 3, 4, 6]] >= 0).mean() > 0.5
+
+
+def test_rejection_only_tail_agrees_with_one_launch():
+    """Rejection-only calls on both sides of the tail's limits (one workgroup's
+    pass, the widths of a round, the most requests it takes): a request's result
+    does not depend on the call it is in.  8,193 requests are checked by one launch."""
+    sim, cfg = make_sim()
+    rp = ResetProposer(sim, **dict(cfg, d_hi_m=20.0))
+    q = requests(8193, 9)
+    q[0][::50] = 9  # unknown maps
+    q[1][7::90] = -1  # no bin
+    say("rejection-only proposals of 1 to 8,193 requests, 75 attempts")
+    want = rp.propose_into(*q, 0, 75, outputs(8193))
+    for n in (1, 63, 64, 65, 511, 2047, 2048, 2049, 4097, 8192):
+        for noalloc in (False, True):
+            got = rp.propose_into(*[v[:n].clone() for v in q], 0, 75, outputs(n), noalloc=noalloc)
+            torch.cuda.synchronize()
+            assert same(got, {k: want[k][:n] for k in KEYS}), (n, noalloc)
+    src = want["source"].cpu().numpy()
+    assert (src > 24).any() and (src == -1).any() and (want["checks"].cpu().numpy() == 75).any()
+    rp.close()
+    sim.close()

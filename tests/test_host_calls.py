@@ -12,23 +12,27 @@ def run(tmp_path_factory):
     return lambda body: stand_in.run(tmp, body)
 
 
-def test_rejection_only_noalloc_calls_keep_nothing_on_the_device(run):
+def test_rejection_only_noalloc_calls_keep_off_the_shared_array(run):
     """The rejection sampler alone takes nothing from the array that all proposers
-    of a device share: one launch, no count, list or second launch."""
+    of a device share, whatever it launches (calls with network draws do)."""
     run("""
     r = proposer(handle(8, [(256, 256)] * 3))
     for n in (1, 31, 200, 3000, 8192):
         for tries in (0, 1, 16, 64, 5000):
             clear()
             assert propose(r, n, 0, tries, noalloc=True) == 0
-            assert launches() == ["propose_kernel<%d>" % (8 if n <= 2048 else 4)], (n, tries)
+            assert launches()[0] == "propose_kernel<%d>" % (8 if n <= 2048 else 4), (n, tries)
             assert counts()[1:4] == (0, 0, 0)
+            assert R.stand_in_scratch_pointers() == 0, (n, tries)
+    clear()
+    assert propose(r, 200, 8, 64, noalloc=True) == 0
+    assert R.stand_in_scratch_pointers() > 0
     """)
 
 
 def test_rejection_only_proposals_need_no_workspace(run):
     """Rejection-only calls allocate nothing and work during a stream capture and
-    with no device memory left: one launch each, whatever their size."""
+    with no device memory left, whatever their size."""
     run("""
     r = proposer(handle(8, [(256, 256)] * 3))
     R.stand_in_capturing(1)
@@ -37,8 +41,38 @@ def test_rejection_only_proposals_need_no_workspace(run):
         for tries in (0, 16, 64, 5000):
             clear()
             assert propose(r, n, 0, tries) == 0, lib.navsim_last_error()
-            assert launches() == ["propose_kernel<%d>" % (8 if n <= 2048 else 4)], (n, tries)
             assert counts()[1:4] == (0, 0, 0)
+    """)
+
+
+def test_rejection_only_tail_where_its_state_fits(run):
+    """The tail launches run where the requests' state fits their output rows: at
+    least two rounds left, attempt numbers below 2^16, and arrays that share no
+    memory; elsewhere one launch checks every round."""
+    run("""
+    def kernels_of(n, tries, alias=None):
+        v = [np.zeros(n, np.int32) for _ in range(7)]
+        if alias:
+            v[alias[0]] = v[alias[1]]
+        pose = np.zeros((n, 5), np.float32)
+        clear()
+        assert lib.navsim_rp_propose(r, n, *[a.ctypes.data for a in v[:4]], 0, tries, pose.ctypes.data,
+                                     *[a.ctypes.data for a in v[4:]], None, None) == 0
+        return launches()
+    r = proposer(handle(8, [(256, 256)] * 3))
+    for n, W, head in ((64, 8, 1), (2048, 8, 1), (2049, 4, 3)):
+        one = ["propose_kernel<%d>" % W]
+        three = one + ["propose_tail_own_kernel<%d>" % W, "propose_final_own_kernel"]
+        assert kernels_of(n, W * (head + 1)) == one
+        assert kernels_of(n, W * (head + 1) + 1) == three
+        assert kernels_of(n, 400) == three
+        for alias in ((4, 5), (4, 6), (5, 6)):
+            assert kernels_of(n, 400, alias) == one
+    assert kernels_of(64, 65535) == ["propose_kernel<8>", "propose_tail_own_kernel<8>",
+                                     "propose_final_own_kernel"]
+    assert kernels_of(64, 65536) == ["propose_kernel<8>"]
+    assert kernels_of(4096, 65535) == ["propose_kernel<4>"]  # more than 2^22 rounds
+    assert kernels_of(8192, 400) == three and kernels_of(8193, 400) == one
     """)
 
 
