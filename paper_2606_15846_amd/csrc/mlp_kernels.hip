@@ -317,7 +317,7 @@ __device__ __forceinline__ void col_sum_block(const ColSum &c, int block) {
 // each alone leaves most of the chip idle: a batch of 1,024 on the 1048-256-256-
 // 256-5 network took 4 x 13 us for the products and 4 x 13 us for the sums (two
 // launches each), together 20 us.
-__global__ __launch_bounds__(256) void gradient_kernel(GradientArgs a) {
+__global__ __launch_bounds__(256) __attribute__((aligned(4096))) void gradient_kernel(GradientArgs a) {
     int b = (int)blockIdx.x;
     for (int l = 0; l < a.gemms; ++l) {
         const GemmArgs &g = a.gemm[l];
@@ -622,7 +622,10 @@ __global__ __launch_bounds__(kActorThreads) void actor_fused_kernel(ActorArgs a)
 // 256-5 network (36 GFLOP) in 67 us, 262,144 in 126 us (570 TFLOP/s), a step's
 // 15,700 in 17 us, against 260, 430 and 62 us with the noise kernel and four
 // GEMMs; 64 rows and 4 wavefronts a workgroup: 84, 157 and 20 us; weights from
-// the row-major matrix instead of the packed image: 109, 217 and 28 us.
+// the row-major matrix instead of the packed image: 109, 217 and 28 us.  The code
+// is 13 KB without a loop and starts at a page, so that its speed does not depend
+// on the kernels before it (65.1 us, 66.6 at another offset; gradient_kernel 19.1,
+// 19.8).
 constexpr int kFwdThreads = 512;
 constexpr int kFwdRows = kFwdThreads / 4;
 constexpr int kFwdZPitch = 72;  // bf16 per noise row in LDS: up to 64 columns, 16 bytes of padding
@@ -641,7 +644,7 @@ __device__ __forceinline__ uint2 hidden_bf16(f32x4 v, float4 b, float slope) {
 }
 
 template <int H>
-__global__ __launch_bounds__(kFwdThreads) void forward_noise_kernel(ForwardNoiseArgs a) {
+__global__ __launch_bounds__(kFwdThreads) __attribute__((aligned(4096))) void forward_noise_kernel(ForwardNoiseArgs a) {
     constexpr int KS = H / 32;          // k blocks of a hidden layer
     constexpr int WN = H / 64;          // wavefronts across the columns
     constexpr int MT = WN;              // 16-row tiles per wavefront: 64 / (4 / WN) / 16
