@@ -317,7 +317,8 @@ __device__ __forceinline__ void col_sum_block(const ColSum &c, int block) {
 // each alone leaves most of the chip idle: a batch of 1,024 on the 1048-256-256-
 // 256-5 network took 4 x 13 us for the products and 4 x 13 us for the sums (two
 // launches each), together 20 us.
-__global__ __launch_bounds__(256) __attribute__((aligned(4096))) void gradient_kernel(GradientArgs a) {
+__global__ __launch_bounds__(256) __attribute__((aligned(4096)))
+void gradient_kernel(GradientArgs a) {
     int b = (int)blockIdx.x;
     for (int l = 0; l < a.gemms; ++l) {
         const GemmArgs &g = a.gemm[l];
@@ -644,7 +645,8 @@ __device__ __forceinline__ uint2 hidden_bf16(f32x4 v, float4 b, float slope) {
 }
 
 template <int H>
-__global__ __launch_bounds__(kFwdThreads) __attribute__((aligned(4096))) void forward_noise_kernel(ForwardNoiseArgs a) {
+__global__ __launch_bounds__(kFwdThreads) __attribute__((aligned(4096)))
+void forward_noise_kernel(ForwardNoiseArgs a) {
     constexpr int KS = H / 32;          // k blocks of a hidden layer
     constexpr int WN = H / 64;          // wavefronts across the columns
     constexpr int MT = WN;              // 16-row tiles per wavefront: 64 / (4 / WN) / 16
